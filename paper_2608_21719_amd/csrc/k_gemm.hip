@@ -5,10 +5,8 @@
 // workgroup streams is then one contiguous 8 KiB (bf16) block of HBM rather
 // than 64 strided 128-byte pieces. fp32 accumulation (gfx950).
 //
-//  * gemm_tile_kernel: prefill-sized M. 256x256 workgroup tile, four waves
-//    of 128x128 (one per SIMD), v_mfma_f32_32x32x16_bf16 with accumulators
-//    in AGPRs, 64-k stages in two XOR-swizzled LDS slots (128 KiB) filled
-//    by direct global->LDS loads spread over the stage. MFMA-bound.
+//  * gemm_tile_kernel (gemm_tile.h): M > 64, 256x256 down to 64x64 workgroup
+//    tiles chosen by gemm_tile_plan.
 //  * gemm_skinny_kernel: decode-sized M (<= 64). Streams W once from HBM
 //    with 16-byte loads, one 16-column MFMA block per wave, activations
 //    staged in LDS and shared by the workgroup's four waves; K may be split
@@ -18,407 +16,11 @@
 //
 // Epilogues: store, residual add (C = R + A W^T) and SwiGLU (W rows
 // interleaved gate/up in blocks of 32; C[:, j] = silu(gate_j) * up_j).
-#include "common.h"
-#include "launch.h"
+#include "gemm_tile.h"
 
 #include <mutex>
-#include <type_traits>
 
 namespace ps {
-
-__device__ __forceinline__ float silu_f(float x) { return x / (1.f + expf(-x)); }
-// silu on the hardware exp2 and reciprocal (v_exp_f32, v_rcp_f32): a few
-// fp32 ulp, far below the bf16 rounding of the GEMM operands; four vector
-// instructions instead of the ~30 of expf and an IEEE divide, which matter
-// in an epilogue that no matrix work overlaps. x -> -inf gives -0, x -> inf
-// gives x.
-__device__ __forceinline__ float silu_fast(float x) {
-  return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
-}
-
-template <typename T> __device__ __forceinline__ float ld_elt(const T* p, long i);
-template <> __device__ __forceinline__ float ld_elt<float>(const float* p, long i) { return p[i]; }
-template <> __device__ __forceinline__ float ld_elt<bf16_t>(const bf16_t* p, long i) { return bf2f(p[i]); }
-template <typename T> __device__ __forceinline__ void st_elt(T* p, long i, float v);
-template <> __device__ __forceinline__ void st_elt<float>(float* p, long i, float v) { p[i] = v; }
-template <> __device__ __forceinline__ void st_elt<bf16_t>(bf16_t* p, long i, float v) { p[i] = f2bf(v); }
-
-// ================================================================== helpers
-// One 16-byte global->LDS fill per lane through a buffer resource
-// (buffer_load_dwordx4 ... lds): a wave instruction fills 1 KiB of LDS, lane
-// l landing at +16 l; `voffset` is the lane's byte offset from the resource
-// base. The compiler counts this form on vmcnt alone, so LDS reads issued
-// around it keep exact lgkmcnt waits (around the FLAT global_load_lds form
-// it waits for every outstanding LDS read before each use of a fragment).
-__device__ __forceinline__ void load_lds16_buf(__amdgpu_buffer_rsrc_t r, uint32_t voffset, bf16_t* lds) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voffset, 0, 0, 0);
-}
-// The same with a wave-uniform byte offset in the scalar offset operand: a
-// per-stage step added there costs no vector address arithmetic.
-__device__ __forceinline__ void load_lds16_buf_so(__amdgpu_buffer_rsrc_t r, uint32_t voffset, uint32_t soffset,
-                                                  bf16_t* lds) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voffset, soffset, 0, 0);
-}
-// The same with the non-temporal hint (cache policy bit 1), for data read
-// exactly once per call (decode weight streams).
-__device__ __forceinline__ void load_lds16_buf_nt(__amdgpu_buffer_rsrc_t r, uint32_t voffset, bf16_t* lds) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voffset, 0, 0, 2);
-}
-// Raw (stride 0) buffer resource over `bytes` bytes from `base`; loads past
-// the end return zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-
-// s_waitcnt vmcnt(n) lgkmcnt(0): this wave's global->LDS fills older than
-// its n most recent have landed, and its own LDS reads have returned.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt_lgkm0() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
-}
-
-// Workgroup barrier without the release/acquire fences of __syncthreads():
-// those wait for every outstanding global->LDS fill (vmcnt(0)) and would
-// collapse a ring deeper than two stages. Callers wait explicitly first; the
-// memory clobber keeps LDS accesses on their side of the barrier.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
-// The same barrier pinned in the instruction schedule: register-only work
-// (MFMAs) may not move across it either.
-__device__ __forceinline__ void lds_barrier_pinned() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// f(std::integral_constant<int, i>) for i = B .. E-1, unrolled at compile
-// time (register arrays indexed by i stay in registers).
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-// ====================================================================== tile
-// Prefill-sized M. Workgroup tile 256 x 256, four waves of 128 x 128 (one
-// per SIMD), v_mfma_f32_32x32x16_bf16 with the 256 accumulators per lane in
-// AGPRs. K runs in 64-wide stages through two LDS slots (128 KiB) filled by
-// global->LDS DMA (buffer form); LDS rows are 128 B, their 16-byte chunks
-// XOR-swizzled by (row / 2) % 8 so that the operand reads of 16 consecutive
-// rows hit 16 distinct bank groups (the DMA lane addresses are chosen so
-// that the linear fill lands swizzled).
-//
-// Schedule of stage st (slot st & 1), four 16-k slices of 16 MFMAs each.
-// Every slice interleaves with its MFMAs:
-//  * the reads of the next slice's eight fragments, one after each of the
-//    first eight MFMAs, in the order the next slice first uses them
-//    (a0 b0 b1 b2 b3 a1 a2 a3), so its MFMAs wait only for their own;
-//  * DMA instructions, one after every other MFMA from the second: in
-//    slices 0 and 1 the rest of stage st+1, in slice 3 the first part of
-//    stage st+2 into slot st & 1.
-// After slice 2: wait for stage st+1 and this stage's reads, one barrier
-// (slot st & 1 is free from there, and slice 3 reads stage st+1's first
-// fragments). Issued in bursts, DMA or reads back up the address unit and
-// the LDS queue and stall the waves' instruction streams. The split over
-// slices 3, 0, 1 is 7 / 7 / 2: loads issued in slice 1 have only a slice and
-// a half to land before that wait, which an L2 miss outlasts (6 / 5 / 5 was
-// 2% slower on the gate_up shape).
-namespace tile {
-constexpr int BM = 256, BN = 256, BK = 64, NT = 256, WT = 128;
-constexpr int CPR = BK / 8, RPL = 64 / CPR;                         // 8 chunks per row, 8 rows per DMA
-constexpr int A_ELTS = BM * BK, STAGE = (BM + BN) * BK;             // bf16 elements
-constexpr int A_LOADS = BM / RPL / 4, B_LOADS = BN / RPL / 4, LOADS = A_LOADS + B_LOADS;  // per wave
-constexpr int Q = WT / 32;                                           // 4 x 4 blocks of 32 x 32
-constexpr int D3 = 7, D0 = 7, D1 = LOADS - D3 - D0;                  // DMA split over slices 3, 0, 1
-constexpr int DMA_AT = 1, DMA_EVERY = 2;                             // after MFMAs 1, 3, 5, ...
-static_assert(DMA_AT + (D3 - 1) * DMA_EVERY < Q * Q && DMA_AT + (D0 - 1) * DMA_EVERY < Q * Q &&
-                  DMA_AT + (D1 - 1) * DMA_EVERY < Q * Q, "DMA slots in a slice");
-constexpr size_t LDS_BYTES = 2 * (size_t)STAGE * 2;
-__device__ __forceinline__ int swz(int row, int ch) { return row * BK + ((ch ^ ((row >> 1) & 7)) << 3); }
-}  // namespace tile
-
-template <int EPI, typename TR, typename TC>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
-                                                        const TR* __restrict__ R, TC* __restrict__ C, int M, int N,
-                                                        int K, int tiles_n, int group, int splits) {
-  using namespace tile;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-
-  // XCD-aware tile order: consecutive workgroup ids go round-robin over the
-  // 8 XCDs; give each XCD a contiguous range of tiles, walked in groups of
-  // `group` tile-rows across N, so that tiles sharing A and W panels meet in
-  // the same L2.
-  // With splits > 1 (EPI 0, fp32 C) the grid holds every tile once per K
-  // split, split-major: split s covers stages [s T / splits, (s + 1) T /
-  // splits) and stores its partial at C + s M N.
-  const int nwg = gridDim.x;
-  int id = blockIdx.x;
-  if ((nwg & 7) == 0) id = (id & 7) * (nwg >> 3) + (id >> 3);
-  const int n_tiles = nwg / splits;
-  const int ks = id / n_tiles;
-  id -= ks * n_tiles;
-  const int tiles_m = n_tiles / tiles_n;
-  const int group_sz = group * tiles_n;
-  const int first_m = (id / group_sz) * group;
-  const int gm = min(group, tiles_m - first_m);
-  const int tm = first_m + (id % group_sz) % gm;
-  const int tn = (id % group_sz) / gm;
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int wm = wave >> 1, wn = wave & 1;
-  // DMA sources: buffer resources at the tile's A rows and W blocks, 32-bit
-  // lane byte offsets (rows past M read row M-1, results unused)
-  const int lrow = lane / CPR, lpos = lane % CPR;
-  uint32_t aoff[A_LOADS], boff[B_LOADS];
-#pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) {
-    const int row = (wave * A_LOADS + i) * RPL + lrow;
-    aoff[i] = ((uint32_t)(min(m0 + row, M - 1) - m0) * K + (lpos ^ ((row >> 1) & 7)) * 8) * 2;
-  }
-#pragma unroll
-  for (int i = 0; i < B_LOADS; ++i) {  // tiled W: rows of 64-row block row/64, k-tile added per stage
-    const int row = (wave * B_LOADS + i) * RPL + lrow;
-    boff[i] = ((uint32_t)(row >> 6) * (K / 64) * kWTileElts + (row & 63) * 64 + (lpos ^ ((row >> 1) & 7)) * 8) * 2;
-  }
-  static_assert(BK == kWTile, "one W tile per stage");
-  const __amdgpu_buffer_rsrc_t rA = buffer_rsrc(A + (long)m0 * K, (uint32_t)min(M - m0, BM) * K * 2);
-  const __amdgpu_buffer_rsrc_t rW =
-      buffer_rsrc(W + (long)(n0 >> 6) * (K / 64) * kWTileElts, (uint32_t)(BN / 64) * (K / 64) * kWTileElts * 2);
-  const int T_all = K / BK;
-  const int st0 = ks * T_all / splits, T = (ks + 1) * T_all / splits - st0;  // this workgroup's stages
-  // DMA instruction l (0..LOADS-1) of stage s into slot dslot (= s & 1);
-  // the stage's step rides in the scalar offset
-  auto dma = [&](int s, int dslot, int l) __attribute__((always_inline)) {
-    bf16_t* st = smem + dslot * STAGE;
-    if (l < A_LOADS)
-      load_lds16_buf_so(rA, aoff[l], (s + st0) * BK * 2, st + (wave * A_LOADS + l) * RPL * BK);
-    else
-      load_lds16_buf_so(rW, boff[l - A_LOADS], (s + st0) * kWTileElts * 2,
-                        st + A_ELTS + (wave * B_LOADS + l - A_LOADS) * RPL * BK);
-  };
-
-  // 32x32x16 operands: lane (h, r) holds row r of a 32-row block, k 8h..8h+7
-  // of a 16-k slice; fragments double-buffered by slice parity
-  const int h = lane >> 5, r32 = lane & 31;
-  bf16x8_t fa[2][Q], fb[2][Q];
-  // fragment r (0..2Q-1) of slice sl, in first-use order: a0 b0 .. b(Q-1) a1 .. a(Q-1)
-  auto read_frag = [&](int slot, int sl, int r) __attribute__((always_inline)) {
-    const bf16_t* a = smem + slot * STAGE;
-    if (r == 0)
-      fa[sl & 1][0] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(a + swz(wm * WT + r32, 2 * sl + h)));
-    else if (r <= Q)
-      fb[sl & 1][r - 1] =
-          __builtin_bit_cast(bf16x8_t, *(const uint4*)(a + A_ELTS + swz(wn * WT + (r - 1) * 32 + r32, 2 * sl + h)));
-    else
-      fa[sl & 1][r - Q] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(a + swz(wm * WT + (r - Q) * 32 + r32, 2 * sl + h)));
-  };
-  f32x16_t acc[Q][Q];
-#pragma unroll
-  for (int i = 0; i < Q; ++i)
-#pragma unroll
-    for (int j = 0; j < Q; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  // an (empty) AGPR operand makes the compiler select the AGPR form of the
-  // MFMAs, which keeps the accumulators in place in the AGPR file
-  asm volatile("" ::"a"(0.f));
-  auto mfma = [&](int sl, int q) __attribute__((always_inline)) {
-    acc[q / Q][q % Q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[sl & 1][q / Q], fb[sl & 1][q % Q], acc[q / Q][q % Q], 0, 0, 0);
-  };
-
-  // stage st; `full` = st + 2 < T (every condition below holds)
-  // slotc: std::integral_constant<int, st & 1> where the caller knows the
-  // parity (LDS slot addresses then fold into instruction offsets), else an
-  // int and the slot is computed
-  auto stage = [&](int st, bool full, auto slotc) __attribute__((always_inline)) {
-    int slot;
-    if constexpr (std::is_same_v<decltype(slotc), int>) slot = st & 1;
-    else slot = decltype(slotc)::value;
-    const bool more = full || st + 1 < T;
-    const bool dma_next = st > 0 && st + 1 < T;  // rest of stage st+1 (stage 1 comes whole with the prologue)
-    const bool dma_far = full || st + 2 < T;     // first part of stage st+2
-    auto slice = [&](auto slc) __attribute__((always_inline)) {
-      constexpr int sl = decltype(slc)::value;
-      constexpr int DN = sl == 0 ? D0 : sl == 1 ? D1 : sl == 3 ? D3 : 0;
-      constexpr int DB = sl == 0 ? D3 : sl == 1 ? D3 + D0 : 0;
-      const int rslot = sl == 3 ? slot ^ 1 : slot;
-      const bool rd = sl < 3 || more;
-      const bool dd = sl == 3 ? dma_far : dma_next;
-      const int ds = sl == 3 ? st + 2 : st + 1;
-      static_for<0, Q * Q>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value;
-        mfma(sl, q);
-        if constexpr (q < 2 * Q) {
-          if (rd) read_frag(rslot, (sl + 1) & 3, q);
-        }
-        if constexpr (q >= DMA_AT && (q - DMA_AT) % DMA_EVERY == 0 && (q - DMA_AT) / DMA_EVERY < DN) {
-          if (dd) dma(ds, sl == 3 ? slot : slot ^ 1, DB + (q - DMA_AT) / DMA_EVERY);
-        }
-      });
-      if (full) {
-        static_for<0, Q * Q>([&](auto qc) __attribute__((always_inline)) {
-          constexpr int q = decltype(qc)::value;
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // MFMA
-          if constexpr (q < 2 * Q) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
-          if constexpr (q >= DMA_AT && (q - DMA_AT) % DMA_EVERY == 0 && (q - DMA_AT) / DMA_EVERY < DN)
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                  // VMEM read (DMA)
-        });
-      }
-      if constexpr (sl == 2) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) {
-          wait_vmcnt_lgkm0<0>();  // stage st+1 landed, this stage's reads returned
-          lds_barrier_pinned();
-        }
-      }
-    };
-    slice(std::integral_constant<int, 0>{});
-    slice(std::integral_constant<int, 1>{});
-    slice(std::integral_constant<int, 2>{});
-    slice(std::integral_constant<int, 3>{});
-  };
-
-  // prologue: stages 0 and 1 whole, stage 0 landed everywhere, its first
-  // fragments read
-#pragma unroll
-  for (int l = 0; l < LOADS; ++l) dma(0, 0, l);
-  if (T > 1) {
-#pragma unroll
-    for (int l = 0; l < LOADS; ++l) dma(1, 1, l);
-    wait_vmcnt_lgkm0<LOADS>();
-  } else {
-    wait_vmcnt_lgkm0<0>();
-  }
-  lds_barrier_pinned();
-#pragma unroll
-  for (int r = 0; r < 2 * Q; ++r) read_frag(0, 0, r);
-  int st = 0;
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  for (; st + 3 < T; st += 2) {  // two stages per trip: both slots known at compile time
-    stage(st, true, S0{});
-    stage(st + 1, true, S1{});
-  }
-  if (st + 2 < T) stage(st++, true, S0{});  // st is even here
-  for (; st < T; ++st) stage(st, false, 0);
-
-  // epilogue: acc[i][j][r] is C[32 i + 8 (r / 4) + 4 h + r % 4][32 j + r32]
-  // of the wave tile. Each 32-row block goes through a wave-private LDS
-  // staging area (fp32, rows padded to 136 floats: the two lane halves,
-  // 4 rows apart, land 32 banks apart), then every lane reads V consecutive
-  // columns and the global stores (and residual loads) are 16 bytes per
-  // lane: a few wide VMEM instructions instead of one per (row group,
-  // column block). SwiGLU: the wave's column blocks alternate gate and up
-  // (the 32-row interleave of w_gate_up), block 2p pairs with 2p + 1.
-  constexpr int ROWF = 136;
-  const int rbase = m0 + wm * WT, cbase = n0 + wn * WT;
-  constexpr int V = std::is_same<TC, bf16_t>::value ? 8 : 4;  // columns per lane
-  constexpr int OUT_COLS = EPI == 2 ? WT / 2 : WT;
-  constexpr int LPR = OUT_COLS / V, RPP = 64 / LPR;  // lanes per row, rows per pass
-  const long ldc = EPI == 2 ? N / 2 : N;
-  const long ccol = EPI == 2 ? cbase / 2 : cbase;
-  C += (long)ks * M * ldc;  // this split's partial
-  constexpr int NPASS = 32 / RPP;
-  // residual operand of one pass: V values of row `row` from column `oc`
-  using RRaw = typename std::conditional<std::is_same<TR, float>::value, float4,
-                                         typename std::conditional<V == 8, uint4, uint2>::type>::type;
-  constexpr int RCH = std::is_same<TR, float>::value ? V / 4 : 1;  // RRaw loads per pass
-  // Residual loads run one 32-row block ahead of the block being stored
-  // (two register sets), the first block's issued before the staging
-  // barrier, so that the HBM latency of the loads, which every CU issues at
-  // about the same moment, is exposed once per tile instead of once per
-  // block. Block i + 1's rows are disjoint from block i's, so the loads may
-  // precede block i's stores even where R aliases C, and every element is
-  // still read before it is written.
-  RRaw rr[2][EPI == 1 ? NPASS : 1][RCH];
-  auto load_r = [&](int i) __attribute__((always_inline)) {
-    if constexpr (EPI == 1) {
-#pragma unroll
-      for (int pass = 0; pass < NPASS; ++pass) {
-        const int row = rbase + i * 32 + pass * RPP + lane / LPR, oc = (lane % LPR) * V;
-        const long idx = (long)min(row, M - 1) * ldc + ccol + oc;  // rows past M: a valid row, result unused
-#pragma unroll
-        for (int q = 0; q < RCH; ++q) rr[i & 1][pass][q] = *(const RRaw*)(R + idx + q * 4);
-      }
-    }
-  };
-  load_r(0);
-  lds_barrier_pinned();  // every wave is done reading operand slots
-  float* stg = (float*)smem + wave * (32 * ROWF);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    if (i + 1 < Q) load_r(i + 1);
-#pragma unroll
-    for (int j = 0; j < Q; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) stg[(8 * (r >> 2) + 4 * h + (r & 3)) * ROWF + j * 32 + r32] = acc[i][j][r];
-    // LDS accesses of one wave complete in order: the reads below see the writes
-#pragma unroll
-    for (int pass = 0; pass < NPASS; ++pass) {
-      const int lr = pass * RPP + lane / LPR, oc = (lane % LPR) * V;
-      const int row = rbase + i * 32 + lr;
-      float v[V];
-      if constexpr (EPI == 2) {
-        const int p = oc / 32, c = oc % 32;
-        const float* g = stg + lr * ROWF + p * 64 + c;
-#pragma unroll
-        for (int e = 0; e < V; e += 4) {
-          const float4 gv = *(const float4*)(g + e), uv = *(const float4*)(g + 32 + e);
-          v[e] = silu_fast(gv.x) * uv.x;
-          v[e + 1] = silu_fast(gv.y) * uv.y;
-          v[e + 2] = silu_fast(gv.z) * uv.z;
-          v[e + 3] = silu_fast(gv.w) * uv.w;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < V; e += 4) {
-          const float4 a4 = *(const float4*)(stg + lr * ROWF + oc + e);
-          v[e] = a4.x;
-          v[e + 1] = a4.y;
-          v[e + 2] = a4.z;
-          v[e + 3] = a4.w;
-        }
-      }
-      if constexpr (EPI == 1) {
-        if constexpr (std::is_same<TR, float>::value) {
-#pragma unroll
-          for (int q = 0; q < RCH; ++q) {
-            v[4 * q] += rr[i & 1][pass][q].x;
-            v[4 * q + 1] += rr[i & 1][pass][q].y;
-            v[4 * q + 2] += rr[i & 1][pass][q].z;
-            v[4 * q + 3] += rr[i & 1][pass][q].w;
-          }
-        } else if constexpr (V == 8) {
-          const uint32_t w4[4] = {rr[i & 1][pass][0].x, rr[i & 1][pass][0].y, rr[i & 1][pass][0].z, rr[i & 1][pass][0].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[2 * e] += bf_lo(w4[e]);
-            v[2 * e + 1] += bf_hi(w4[e]);
-          }
-        } else {
-          v[0] += bf_lo(rr[i & 1][pass][0].x);
-          v[1] += bf_hi(rr[i & 1][pass][0].x);
-          v[2] += bf_lo(rr[i & 1][pass][0].y);
-          v[3] += bf_hi(rr[i & 1][pass][0].y);
-        }
-      }
-      if (row >= M) continue;
-      const long idx = (long)row * ldc + ccol + oc;
-      if constexpr (std::is_same<TC, bf16_t>::value) {
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(u32x4{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]),
-                                          pack_bf2(v[6], v[7])}, (u32x4*)(C + idx));
-      } else {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, (f32x4*)(C + idx));
-      }
-    }
-  }
-}
 
 // ==================================================================== skinny
 // Decode-sized M (<= 64): the weight stream is the whole cost (AI = M
@@ -692,22 +294,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 }
 
 // ==================================================================== launch
-template <int EPI, typename TR, typename TC>
-static int launch_tile(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st,
-                       int splits = 1) {
-  static_assert(tile::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
-  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tile_kernel<EPI, TR, TC>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)tile::LDS_BYTES);
-  if (attr != hipSuccess) return -1;
-  const int tiles_m = (M + tile::BM - 1) / tile::BM, tiles_n = N / tile::BN;
-  // wide outputs walk 8 tile-rows per group (more W reuse per XCD), narrow 4
-  const int group = tiles_n >= 64 ? 8 : 4;
-  hipLaunchKernelGGL((gemm_tile_kernel<EPI, TR, TC>), dim3(tiles_m * tiles_n * splits), dim3(tile::NT),
-                     tile::LDS_BYTES, st, (const bf16_t*)A, (const bf16_t*)W, (const TR*)R, (TC*)C, M, N, K, tiles_n,
-                     group, splits);
-  return 0;
-}
-
 int compute_units() {
   static const int n = [] {
     int dev = 0, v = 0;
@@ -719,35 +305,66 @@ int compute_units() {
   return n;
 }
 
-// Cost of a tile-kernel launch of `tiles` tiles split S ways in K: rounds of
-// workgroups over the compute units (one resident per unit: the kernel takes
-// the whole register file) times the stages per workgroup, plus the split
-// partials' traffic (written, then read once by the consumer) in stage-times:
-// one 256x256x64 stage is ~1.2 us at the power-capped MFMA clock, in which
-// HBM moves ~6 MB.
-static double tile_cost(long tiles, int T, int S, long M, long N) {
-  const long cu = compute_units();
-  const long rounds = (tiles * S + cu - 1) / cu;
-  return (double)rounds * ((T + S - 1) / S) + (S > 1 ? (double)S * M * N * 8.0 / 6.0e6 : 0.0);
+// The tile kernel's shapes. `start` and `stage` are microseconds of one
+// workgroup alone on its compute unit: prologue + epilogue, and one 64-k
+// stage. Least-squares fits over the 8B and 70B layers' GEMMs at 80 to 2080
+// rows and 1 to 4 K splits, weights cold in every cache (rms error 7-17%).
+// Per output element a larger tile is cheaper (256x256: 1.23 us per stage for
+// four 128x128 tiles' work at 0.46 each) but fills fewer compute units.
+struct TileCfg {
+  int qm, qn;  // 64 qm x 64 qn outputs per workgroup
+  float start, stage;
+};
+constexpr TileCfg kTileCfgs[] = {
+    {4, 4, 13.6f, 1.226f}, {3, 4, 9.7f, 1.116f}, {2, 4, 9.5f, 0.709f}, {4, 2, 9.8f, 0.655f},
+    {3, 2, 6.9f, 0.568f},  {2, 2, 6.4f, 0.462f}, {2, 1, 6.0f, 0.330f}, {1, 1, 4.0f, 0.260f},
+};
+constexpr int kTileCfgCount = sizeof(kTileCfgs) / sizeof(kTileCfgs[0]);
+
+// Cost in microseconds of a tile-kernel launch: rounds of workgroups over the
+// compute units (one resident per unit), the weight stream (5 TB/s) that the
+// rounds cannot beat and only partly hide, and the split partials (fp32,
+// written, then read by the consumer, ~6 TB/s). M counts in whole 64-row
+// blocks, so that the choice is constant between multiples of 64.
+static double tile_cost(const TileCfg& t, int M, int N, int K, int S) {
+  const long cu = compute_units(), rows = (M + 63) / 64 * 64;
+  const long wgs = (long)((M + 64 * t.qm - 1) / (64 * t.qm)) * (N / (64 * t.qn)) * S;
+  const int T = K / tile::BK;
+  const double work = (double)((wgs + cu - 1) / cu) * (t.start + t.stage * ((T + S - 1) / S));
+  const double stream = (double)N * K * 2.0 / 5.0e6;
+  return std::max(work, stream) + 0.3 * std::min(work, stream) + (S > 1 ? (double)S * rows * N * 8.0 / 6.0e6 : 0.0);
 }
 
-int gemm_tile_splits(int M, int N, int K) {
-  using namespace tile;
-  if (M <= skinny::MAXM || N % BN || K % BK) return 1;
-  const long tiles = (long)((M + BM - 1) / BM) * (N / BN);
-  const int T = K / BK;
-  int best = 1;
-  double best_cost = tile_cost(tiles, T, 1, M, N);
-  for (int S = 2; S <= 4 && T / S >= 16; ++S) {
-    const double c = tile_cost(tiles, T, S, M, N);
-    if (c < best_cost) best = S, best_cost = c;
+// The cheapest tile shape and, up to max_splits, K splits. SwiGLU pairs a
+// gate and an up block within a wave, so its tiles are at least 128 wide. At
+// most 4 splits of at least 16 stages each, and no more of them than fill one
+// round of 256x256 tiles (two above 2048 rows, where an unsplit launch ends in
+// a nearly empty round: down at 2257 rows 295 us unsplit, 287 with its reduce
+// in two splits); that bounds the partials at 256 KiB per tile and split. The
+// outputs of an unsplit launch do not depend on the tile shape: each is one
+// chain of the same MFMAs over K.
+TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu) {
+  TilePlan best{0, 1};
+  if (M <= skinny::MAXM || N % 256 || K % tile::BK) return best;
+  const long tiles256 = (long)((M + 255) / 256) * (N / 256);
+  const int T = K / tile::BK;
+  double best_cost = 0;
+  for (int S = 1; S <= std::min(max_splits, 4); ++S) {
+    if (S > 1 && (T / S < 16 || tiles256 * S > (M > 2048 ? 2 : 1) * compute_units())) break;
+    for (int i = 0; i < kTileCfgCount; ++i) {
+      if (swiglu && kTileCfgs[i].qn % 2) continue;
+      const double c = tile_cost(kTileCfgs[i], M, N, K, S);
+      if ((S == 1 && i == 0) || c < best_cost) best = TilePlan{i, S}, best_cost = c;
+    }
   }
   return best;
 }
 
+int gemm_tile_splits(int M, int N, int K) { return gemm_tile_plan(M, N, K, 4, false).s; }
+
 size_t gemm_tile_partials_bound(int max_rows, int N, int K) {
   size_t b = 0;
-  for (int m = tile::BM;; m += tile::BM) {
+  for (int m = 64;; m += 64) {
     const int mm = std::min(m, max_rows);
     const int S = gemm_tile_splits(mm, N, K);
     if (S > 1) b = std::max(b, (size_t)S * mm * N * sizeof(float));
@@ -756,9 +373,61 @@ size_t gemm_tile_partials_bound(int max_rows, int N, int K) {
   return b;
 }
 
+// Tile rows walked per group (see the kernel). Few rows (up to ~2300): groups
+// of equal size of at most ~1280 rows, so that the workgroups sharing a
+// weight column run together and no short group trails; more rows: 8 tile
+// rows of 256 on wide outputs (more W reuse per XCD), 4 on narrow ones.
+static int tile_group(int M, int N, int qm) {
+  const int tiles_m = (M + 64 * qm - 1) / (64 * qm);
+  if (M <= 2304) {
+    const int groups = (tiles_m * 64 * qm + 1279) / 1280;
+    return (tiles_m + groups - 1) / groups;
+  }
+  return std::max(1, (N / 256 >= 64 ? 2048 : 1024) / (64 * qm));
+}
+
+// The layer's launches take any shape; the remaining type combinations
+// (single-op calls) run 256x256 tiles only.
+template <int EPI, typename TR, typename TC>
+constexpr bool kTileAllShapes = (EPI == 0 && std::is_same<TR, float>::value) ||
+                                (EPI == 1 && !std::is_same<TR, TC>::value) ||
+                                (EPI == 2 && std::is_same<TC, bf16_t>::value);
+
+#define PS_TILE_EXTERN(QM, QN, NS, EPI, TR, TC)                                                                     \
+  extern template int launch_tile_g<QM, QN, NS, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
+                                                             void*, hipStream_t, int, int);
+PS_TILE_INSTANCES(PS_TILE_EXTERN)
+#undef PS_TILE_EXTERN
+
+template <int EPI, typename TR, typename TC>
+static int launch_tile(int M, int N, int K, TilePlan pl, const void* A, const void* W, const void* R, void* C,
+                       hipStream_t st) {
+  if (!kTileAllShapes<EPI, TR, TC>) pl.cfg = 0;
+  const int group = tile_group(M, N, kTileCfgs[pl.cfg].qm);
+#define PS_TILE_GO(QM, QN, NS) launch_tile_g<QM, QN, NS, EPI, TR, TC>(M, N, K, A, W, R, C, st, pl.s, group)
+  if constexpr (kTileAllShapes<EPI, TR, TC>) {
+    switch (pl.cfg) {
+      case 1: return PS_TILE_GO(3, 4, 2);
+      case 2: return PS_TILE_GO(2, 4, 3);
+      case 3: return PS_TILE_GO(4, 2, 3);
+      case 4: return PS_TILE_GO(3, 2, 3);
+      case 5: return PS_TILE_GO(2, 2, 4);
+      default: break;
+    }
+    if constexpr (EPI != 2) {
+      if (pl.cfg == 6) return PS_TILE_GO(2, 1, 6);
+      if (pl.cfg == 7) return PS_TILE_GO(1, 1, 5);
+    }
+  }
+  return PS_TILE_GO(4, 4, 2);
+#undef PS_TILE_GO
+}
+
 int launch_gemm_tile_split(int M, int N, int K, int S, const void* A, const void* W, float* part, hipStream_t st) {
-  if (M <= 0 || S < 1 || N % tile::BN || K % tile::BK || K / tile::BK < S) return -1;
-  return launch_tile<0, float, float>(M, N, K, A, W, nullptr, part, st, S);
+  if (M <= 0 || S < 1 || N % 256 || K % tile::BK || K / tile::BK < S) return -1;
+  TilePlan pl = gemm_tile_plan(M, N, K, 4, false);
+  if (pl.s != S) return -1;
+  return launch_tile<0, float, float>(M, N, K, pl, A, W, nullptr, part, st);
 }
 
 template <int EPI, typename TR, typename TC>
@@ -943,7 +612,8 @@ int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, con
   }
   if (N % 256 != 0) return -1;
 #define TILE_CASE(E, TR_, TC_, rd, cd) \
-  if (epi == E && r_dt == rd && c_dt == cd) return launch_tile<E, TR_, TC_>(M, N, K, A, W, R, C, st);
+  if (epi == E && r_dt == rd && c_dt == cd)  \
+    return launch_tile<E, TR_, TC_>(M, N, K, gemm_tile_plan(M, N, K, 1, E == 2), A, W, R, C, st);
   TILE_CASE(0, float, bf16_t, 0, 1)
   TILE_CASE(0, float, bf16_t, 1, 1)
   TILE_CASE(0, float, float, 0, 0)

@@ -56,6 +56,12 @@ struct SkinnyPlan {
 };
 SkinnyPlan gemm_skinny_plan(int M, int N, int K);
 int gemm_check(int dtype, int epi, int M, int N, int K);
+struct TilePlan {
+  int cfg;  // tile shape, an index into the tile GEMM's table
+  int s;    // K splits
+};
+// Tile shape and K splits (up to max_splits) of a tile-path GEMM (M > 64).
+TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu);
 // K splits (1..4) for a tile-path GEMM (M > 64) whose fp32 partials a fused
 // consumer sums: chosen to cut the launch's rounds over the compute units,
 // weighed against the partials' traffic. 1 for the skinny path.

@@ -105,6 +105,31 @@ def test_prefill_5x416_three_way_k_split(layer8b):
         normwise_ok(got[(b + 1) * T - 1], r, f"seq {b} row {T - 1}")
 
 
+@pytest.mark.parametrize("rows", [66, 129, 200, 450, 577, 700, 1100, 1300])
+def test_prefill_row_counts_between_decode_and_full_batches(layer8b, rows):
+    """One prompt of each length takes another pair of tile shape and K split
+    in the O and down GEMMs: O 2 and 4 ways up to 768 rows, down 4 ways at 66
+    to 450 rows, 3 at 577 and 1100, 2 at 700, none at 1300. The split sums sit
+    in the fused residual + norm and the reduce kernel. Rows around each
+    64-row and tile edge and the last row are compared."""
+    wl, sh = layer8b["wl"], layer8b["wl"].shape
+    pool = H.Pool(sh, rows // 16 + 9, 1, rows // 16 + 1, seed=gen.page_order_seed(wl))
+    layer = B.Layer(pool.cfg)
+    s = pool.kv.open()
+    pool.kv.alloc(s, rows)
+    ws = H.workspace(B.Layer.workspace_bytes(pool.cfg, rows, 1, rows // 16 + 1))
+    x = gen.prefill_input(wl, rows)
+    out = H.empty((rows, sh.hidden), "bf16")
+    layer.prefill(layer8b["dev"].w, pool.kv, 0, [s], [rows], H.to_dev(x, "bf16"), out, ws)
+    sync()
+    got = H.to_f64(out)
+    assert np.all(np.isfinite(got))
+    sample = sorted({r for e in (64, 128, 192, 256, 512, 1024) for r in (e - 1, e) if r < rows} | {0, rows - 1})
+    ref = O.layer_rows(layer8b["wf"], sh, gen.widen(x, "bf16"), sample)
+    for r, want in zip(sample, ref):
+        normwise_ok(got[r], want, f"{rows} rows, row {r}")
+
+
 def _decode_fullsize(layer8b, wl, sample, phase, mixed=False):
     sh = wl.shape
     ctx = [int(c) for c in gen.context_lengths(wl)]

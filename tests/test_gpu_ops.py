@@ -121,6 +121,50 @@ def test_gemm_swiglu(M, F, K):
     H.assert_close_elementwise(H.to_f64(C), ref, 1e-3, 2 ** -7, "swiglu")
 
 
+# row counts and widths that each take another workgroup tile: 256x256, 192x256, 128x256, 256x128 (from 6 stages),
+# 192x128, 128x128, 128x64, 64x64 (128x128 with SwiGLU for the last two), with a partial last tile row in each
+@pytest.mark.parametrize("M,N", [(389, 28672), (257, 28672), (577, 12288), (389, 12288), (257, 12288), (257, 6144),
+                                 (129, 6144), (65, 256)])
+# 64-k stages: fewer than the LDS ring holds, as many, one more, and the lengths around the end of its unrolled loop
+@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 6, 7, 9, 11, 12, 13])
+def test_gemm_every_tile_shape_and_ring_remainder(M, N, stages):
+    K = 64 * stages
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + stages)
+    a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+    wt = torch.empty(N * K, dtype=torch.bfloat16, device="cuda")
+    B.op_tile_weight(B.PS_BF16, N, K, w, wt)
+    ref = a.double() @ w.double().T
+    # fp32 accumulation: 2 K 2^-24 sum |a w| (as gemm_bound), plus half an output ulp
+    absb = (a.double().abs() @ w.double().abs().T) * (2 * K * 2.0 ** -24)
+
+    def ok(got, want, extra=0.0, rel=0.0):
+        return bool(((got.double() - want).abs() <= absb + extra + rel * want.abs()).all())
+
+    c32 = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    B.op_gemm(B.PS_BF16, 0, B.PS_F32, B.PS_EPI_STORE, M, N, K, a, wt, None, c32)
+    assert ok(c32, ref), "store fp32"
+    c16 = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    B.op_gemm(B.PS_BF16, 0, B.PS_BF16, B.PS_EPI_STORE, M, N, K, a, wt, None, c16)
+    assert torch.equal(c16.view(torch.int16), c32.to(torch.bfloat16).view(torch.int16)), "store bf16"
+    r32 = torch.randn((M, N), generator=g, device="cuda")
+    B.op_gemm(B.PS_BF16, B.PS_F32, B.PS_BF16, B.PS_EPI_RESIDUAL, M, N, K, a, wt, r32, c16)
+    assert torch.equal(c16.view(torch.int16), (c32 + r32).to(torch.bfloat16).view(torch.int16)), "residual fp32"
+    r16 = r32.to(torch.bfloat16)
+    h = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    B.op_gemm(B.PS_BF16, B.PS_BF16, B.PS_F32, B.PS_EPI_RESIDUAL, M, N, K, a, wt, r16, h)
+    assert torch.equal(h, c32 + r16.float()), "residual bf16"
+    m = torch.empty((M, N // 2), dtype=torch.bfloat16, device="cuda")
+    B.op_gemm(B.PS_BF16, 0, B.PS_BF16, B.PS_EPI_SWIGLU, M, N, K, a, wt, None, m)
+    gu = ref.view(M, N // 64, 2, 32)
+    want = (torch.nn.functional.silu(gu[:, :, 0]) * gu[:, :, 1]).reshape(M, N // 2)
+    assert bool(((m.double() - want).abs() <= 1e-3 + 2 ** -7 * want.abs()).all()), "swiglu"
+    # every output is one chain of products over K, whatever tile it falls in
+    c65 = torch.empty((65, N), dtype=torch.float32, device="cuda")
+    B.op_gemm(B.PS_BF16, 0, B.PS_F32, B.PS_EPI_STORE, 65, N, K, a[M - 65:].contiguous(), wt, None, c65)
+    assert torch.equal(c65, c32[M - 65:]), "the same rows in another tile shape"
+
+
 @pytest.mark.parametrize("epi,N,K", [(0, 128, 256), (1, 128, 256), (2, 128, 256), (0, 100, 70), (1, 70, 130)])
 @pytest.mark.parametrize("M", [512, 4, 70])
 def test_gemm_f32(epi, N, K, M):
