@@ -307,17 +307,18 @@ int compute_units() {
 
 // The tile kernel's shapes. `start` and `stage` are microseconds of one
 // workgroup alone on its compute unit: prologue + epilogue, and one 64-k
-// stage. Least-squares fits over the 8B and 70B layers' GEMMs at 80 to 2080
-// rows and 1 to 4 K splits, weights cold in every cache (rms error 7-17%).
-// Per output element a larger tile is cheaper (256x256: 1.23 us per stage for
-// four 128x128 tiles' work at 0.46 each) but fills fewer compute units.
+// stage. Least-squares fits over the 8B and 70B layers' GEMMs at 80 to 4096
+// rows and 1 to 4 K splits, weights cold in every cache (rms error 7-16%; the
+// shape and splits chosen are within 1% of the best measured on average, 14%
+// at worst). Per output element a larger tile is cheaper (256x256: 1.26 us per
+// stage for four 128x128 tiles' work at 0.47 each) but fills fewer compute units.
 struct TileCfg {
   int qm, qn;  // 64 qm x 64 qn outputs per workgroup
   float start, stage;
 };
 constexpr TileCfg kTileCfgs[] = {
-    {4, 4, 13.6f, 1.226f}, {3, 4, 9.7f, 1.116f}, {2, 4, 9.5f, 0.709f}, {4, 2, 9.8f, 0.655f},
-    {3, 2, 6.9f, 0.568f},  {2, 2, 6.4f, 0.462f}, {2, 1, 6.0f, 0.330f}, {1, 1, 4.0f, 0.260f},
+    {4, 4, 13.7f, 1.260f}, {3, 4, 10.7f, 1.127f}, {2, 4, 10.3f, 0.735f}, {4, 2, 10.6f, 0.715f},
+    {3, 2, 7.6f, 0.571f},  {2, 2, 7.4f, 0.466f},  {2, 1, 6.0f, 0.326f},  {1, 1, 4.0f, 0.250f},
 };
 constexpr int kTileCfgCount = sizeof(kTileCfgs) / sizeof(kTileCfgs[0]);
 

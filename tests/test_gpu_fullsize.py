@@ -108,10 +108,10 @@ def test_prefill_5x416_three_way_k_split(layer8b):
 @pytest.mark.parametrize("rows", [66, 129, 200, 450, 577, 700, 1100, 1300])
 def test_prefill_row_counts_between_decode_and_full_batches(layer8b, rows):
     """One prompt of each length takes another pair of tile shape and K split
-    in the O and down GEMMs: O 2 and 4 ways up to 768 rows, down 4 ways at 66
-    to 450 rows, 3 at 577 and 1100, 2 at 700, none at 1300. The split sums sit
-    in the fused residual + norm and the reduce kernel. Rows around each
-    64-row and tile edge and the last row are compared."""
+    in the O and down GEMMs: O two ways at 66 to 200, 577 and 700 rows; down
+    four ways up to 450 rows, three at 577 and 1100, two at 700, none at 1300.
+    The split sums sit in the fused residual + norm and the reduce kernel.
+    Rows around each 64-row and tile edge and the last row are compared."""
     wl, sh = layer8b["wl"], layer8b["wl"].shape
     pool = H.Pool(sh, rows // 16 + 9, 1, rows // 16 + 1, seed=gen.page_order_seed(wl))
     layer = B.Layer(pool.cfg)

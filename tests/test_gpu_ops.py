@@ -121,12 +121,14 @@ def test_gemm_swiglu(M, F, K):
     H.assert_close_elementwise(H.to_f64(C), ref, 1e-3, 2 ** -7, "swiglu")
 
 
-# row counts and widths that each take another workgroup tile: 256x256, 192x256, 128x256, 256x128 (from 6 stages),
-# 192x128, 128x128, 128x64, 64x64 (128x128 with SwiGLU for the last two), with a partial last tile row in each
-@pytest.mark.parametrize("M,N", [(389, 28672), (257, 28672), (577, 12288), (389, 12288), (257, 12288), (257, 6144),
-                                 (129, 6144), (65, 256)])
+# row counts and widths that each take another workgroup tile: 256x256, 192x256, 128x256, 192x128, 128x128, 128x64,
+# 64x64 (128x128 with SwiGLU for the last two) and, from 17 stages, 256x128, with a partial last tile row in each
+TILE_SHAPES = [(389, 28672), (257, 28672), (577, 12288), (257, 12288), (257, 6144), (129, 6144), (65, 256)]
+
+
 # 64-k stages: fewer than the LDS ring holds, as many, one more, and the lengths around the end of its unrolled loop
-@pytest.mark.parametrize("stages", [1, 2, 3, 4, 5, 6, 7, 9, 11, 12, 13])
+@pytest.mark.parametrize("M,N,stages", [(m, n, t) for m, n in TILE_SHAPES for t in (1, 2, 3, 4, 5, 6, 7, 9, 11, 12, 13)] +
+                         [(200, 28672, t) for t in (18, 19, 20)])
 def test_gemm_every_tile_shape_and_ring_remainder(M, N, stages):
     K = 64 * stages
     g = torch.Generator(device="cuda").manual_seed(M * 1000 + stages)
