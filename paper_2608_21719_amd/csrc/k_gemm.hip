@@ -12,7 +12,7 @@
 //    staged in LDS and shared by the workgroup's four waves; K may be split
 //    across workgroups, fp32 partials then reduced in split order by
 //    gemm_reduce_kernel. HBM-bound (AI = M FLOP/byte).
-//  * gemm_f32_kernel: fp32 layers, 64x64 register-blocked vector FMA.
+//  * gemm_f32_kernel: fp32 layers, fp32 MFMA straight from global memory.
 //
 // Epilogues: store, residual add (C = R + A W^T) and SwiGLU (W rows
 // interleaved gate/up in blocks of 32; C[:, j] = silu(gate_j) * up_j).
@@ -217,79 +217,159 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 }
 
 // ======================================================================= f32
-template <int EPI, typename TR, typename TC>
+// fp32 layers on v_mfma_f32_16x16x4_f32 (fp32 products and sums; twice the
+// vector rate without packed instructions). A wave holds RB x CB blocks of 16
+// rows x 16 columns and reads its operands straight from global memory: in a
+// 16-k step lane (h, r) loads k 4h .. 4h+3 of row r as one 16-byte access, and
+// MFMA j takes element j of every lane, i.e. k j, 4+j, 8+j, 12+j - the same
+// four for A and W, so any such order is a correct product. The step's rows
+// are 64-byte segments; the next 64-k tile's loads are issued before this
+// tile's MFMAs.
+//
+// These launches are short (the tiny layer: 0.1 to 4 MFLOP per wave), so what
+// bounds them is the chain load - multiply - store and the number of
+// workgroups in flight, not arithmetic. Two arrangements of a workgroup's four
+// waves:
+//  * KSPLIT: all four on the same 16 RB x 16 CB outputs, each over a quarter
+//    of K's 64-wide tiles; partial sums meet in LDS and are added in wave
+//    order. Many small tiles, a quarter of the chain each.
+//  * else: 2 x 2 waves on 32 RB x 32 CB outputs, the whole K each: operands
+//    are read once per 64 x 64 outputs, for launches that fill the chip.
+// Measured (us, one launch): 4 x 512 x 256 (M, N, K) 33 -> 7.5 and
+// 4 x 256 x 1024 124 -> 7.7 (both now a launch's own cost), 100 x 4096 x 4096
+// 650 -> 73, 4096^3 2824 -> 1088 (126 TFLOP/s; torch 145), against 64 x 64
+// LDS tiles on the vector ALU; the error against 64 bits is the same or half.
+// SwiGLU: a wave's column block c comes with the matching up block (32 rows
+// of W further on), so gate and up of one output sit in one lane.
+// VEC: A rows can be read 16 bytes at a time (K a multiple of 4).
+namespace f32g {
+constexpr int NT = 256;
+}
+template <int RB, int CB, bool KSPLIT, bool VEC, int EPI, typename TR, typename TC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        const TR* __restrict__ R, TC* __restrict__ C, int M, int N,
                                                        int K) {
-  __shared__ float sA[16][65], sW[16][65];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-      const int r = e >> 4, kk = e & 15;
-      const int k = k0 + kk;
-      sA[kk][r] = (m0 + r < M && k < K) ? A[(long)(m0 + r) * K + k] : 0.f;
-      sW[kk][r] = (n0 + r < N && k < K) ? W[tiled_index(n0 + r, k, K)] : 0.f;
-    }
-    __syncthreads();
+  constexpr int WB = EPI == 2 ? 2 * CB : CB;  // W blocks per wave
+  constexpr int MW = KSPLIT ? 1 : 2;          // waves along each side of the workgroup tile
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int h = lane >> 4, r16 = lane & 15;
+  const int m0 = (blockIdx.y * MW + (KSPLIT ? 0 : wave >> 1)) * 16 * RB;
+  const int c0 = (blockIdx.x * MW + (KSPLIT ? 0 : wave & 1)) * 16 * CB;  // output column
+  const int kt = (K + kWTile - 1) / kWTile;
+  const int t0 = KSPLIT ? wave * kt / 4 : 0, t1 = KSPLIT ? (wave + 1) * kt / 4 : kt;
+  // W row of block b at this lane's r16 (rows past N read row 0 of the tile
+  // grid's last block, results unused)
+  const int n_pad = (N + kWTile - 1) / kWTile * kWTile;
+  const float* wp[WB];
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sA[kk][ty * 4 + i];
-        w[i] = sW[kk][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= M) continue;
+  for (int b = 0; b < WB; ++b) {
+    int n;
     if constexpr (EPI == 2) {
-      continue;  // handled below through LDS
+      const int c = c0 + (b >> 1) * 16;  // output columns 32 i .. come from W rows 64 i .. (gate) and 64 i + 32 .. (up)
+      n = c / kGateUpBlock * (2 * kGateUpBlock) + c % kGateUpBlock + (b & 1) * kGateUpBlock + r16;
     } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = n0 + tx * 4 + j;
-        if (col < N) {
-          float v = acc[i][j];
-          if constexpr (EPI == 1) v += ld_elt<TR>(R, (long)row * N + col);
-          st_elt<TC>(C, (long)row * N + col, v);
-        }
-      }
+      n = c0 + b * 16 + r16;
     }
+    n = min(n, n_pad - 1);
+    wp[b] = W + ((long)(n / kWTile) * kt) * kWTileElts + (n % kWTile) * kWTile + 4 * h;
   }
-  if constexpr (EPI == 2) {
-    // SwiGLU: exchange the up half through LDS (reuse sA as [64][65])
-    __shared__ float sUp[64][33];
+  const float* ap[RB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < RB; ++i) ap[i] = A + (long)min(m0 + 16 * i + r16, M - 1) * K + 4 * h;
+  f32x4_t acc[RB][WB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int cl = tx * 4 + j;
-        if (cl >= kGateUpBlock) sUp[ty * 4 + i][cl - kGateUpBlock] = acc[i][j];
-      }
-    __syncthreads();
-    const int ldc = N / 2;
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = m0 + ty * 4 + i;
+    for (int b = 0; b < WB; ++b) acc[i][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  struct Tile {
+    float4 a[4][RB], w[4][WB];
+  };
+  // the four 16-k steps of 64-k tile t; A past K is zero (W is padded)
+  auto load = [&](int t, Tile& x) __attribute__((always_inline)) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int cl = tx * 4 + j;
-        if (cl < kGateUpBlock && row < M) {
-          const int col = n0 / 2 + cl;
-          st_elt<TC>(C, (long)row * ldc + col, silu_f(acc[i][j]) * sUp[ty * 4 + i][cl]);
+    for (int s = 0; s < 4; ++s) {
+      const int k = t * kWTile + 16 * s;
+#pragma unroll
+      for (int b = 0; b < WB; ++b) x.w[s][b] = *(const float4*)(wp[b] + (long)t * kWTileElts + 16 * s);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const int ke = k + 4 * h;
+        if constexpr (VEC) {
+          x.a[s][i] = ke < K ? *(const float4*)(ap[i] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+          x.a[s][i] = make_float4(ke < K ? ap[i][k] : 0.f, ke + 1 < K ? ap[i][k + 1] : 0.f,
+                                  ke + 2 < K ? ap[i][k + 2] : 0.f, ke + 3 < K ? ap[i][k + 3] : 0.f);
         }
       }
     }
+  };
+  auto mul = [&](const Tile& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      auto step = [&](auto pick) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int b = 0; b < WB; ++b)
+            acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(pick(x.a[s][i]), pick(x.w[s][b]), acc[i][b], 0, 0, 0);
+      };
+      step([](const float4& v) { return v.x; });
+      step([](const float4& v) { return v.y; });
+      step([](const float4& v) { return v.z; });
+      step([](const float4& v) { return v.w; });
+    }
+  };
+  Tile x0, x1;
+  int t = t0;
+  if (t < t1) load(t, x0);
+  for (; t + 1 < t1; t += 2) {
+    load(t + 1, x1);
+    mul(x0);
+    if (t + 2 < t1) load(t + 2, x0);
+    mul(x1);
+  }
+  if (t < t1) mul(x0);
+
+  // acc[i][b][e] is row m0 + 16 i + 4 h + e, column r16 of block b
+  auto store = [&](int i, int cb, int e, float g, float u) __attribute__((always_inline)) {
+    const int row = m0 + 16 * i + 4 * h + e, col = c0 + 16 * cb + r16;
+    const int ldc = EPI == 2 ? N / 2 : N;
+    if (row >= M || col >= ldc) return;
+    const long idx = (long)row * ldc + col;
+    float v = g;
+    if constexpr (EPI == 1) v += ld_elt<TR>(R, idx);
+    if constexpr (EPI == 2) v = silu_f(g) * u;
+    st_elt<TC>(C, idx, v);
+  };
+  if constexpr (KSPLIT) {
+    __shared__ f32x4_t part[4][RB * WB][64];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int b = 0; b < WB; ++b) part[wave][i * WB + b][lane] = acc[i][b];
+    __syncthreads();
+    // wave w finishes output block w, w + 4, ...
+    constexpr int PB = EPI == 2 ? 2 : 1;
+    for (int o = wave; o < RB * CB; o += 4) {
+      f32x4_t sum[PB];
+#pragma unroll
+      for (int p = 0; p < PB; ++p) {
+        sum[p] = part[0][o * PB + p][lane];
+        for (int w = 1; w < 4; ++w) sum[p] += part[w][o * PB + p][lane];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) store(o / CB, o % CB, e, sum[0][e], sum[PB - 1][e]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if constexpr (EPI == 2) store(i, cb, e, acc[i][2 * cb][e], acc[i][2 * cb + 1][e]);
+          else store(i, cb, e, acc[i][cb][e], 0.f);
+        }
   }
 }
 
@@ -562,12 +642,31 @@ static int launch_skinny(int M, int N, int K, const void* A, const void* W, floa
   return launch_skinny_plan<EPI, TR, TC>(M, N, K, gemm_skinny_plan(M, N, K), A, W, part, R, C, st);
 }
 
+template <int RB, int CB, bool KSPLIT, int EPI, typename TR, typename TC>
+static int launch_f32_shape(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st) {
+  constexpr int MW = KSPLIT ? 1 : 2;
+  const int cols = EPI == 2 ? N / 2 : N;
+  dim3 grid((cols + 16 * CB * MW - 1) / (16 * CB * MW), (M + 16 * RB * MW - 1) / (16 * RB * MW));
+  auto go = [&](auto vec) {
+    hipLaunchKernelGGL((gemm_f32_kernel<RB, CB, KSPLIT, decltype(vec)::value, EPI, TR, TC>), grid, dim3(f32g::NT), 0, st,
+                       (const float*)A, (const float*)W, (const TR*)R, (TC*)C, M, N, K);
+  };
+  if (K % 4 == 0) go(std::true_type{});
+  else go(std::false_type{});
+  return 0;
+}
+
 template <int EPI, typename TR, typename TC>
 static int launch_f32(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st) {
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, TR, TC>), grid, dim3(256), 0, st, (const float*)A, (const float*)W,
-                     (const TR*)R, (TC*)C, M, N, K);
-  return 0;
+  // 128 x 128 tiles (64 x 64 per wave) where they reach half the compute
+  // units (1024 x 1024 x 1024 in 32 x 32 tiles: 40 us against 64 tiles of
+  // 128 x 128 that leave three quarters idle); else K split over the waves,
+  // 16 rows at a time for decode-sized M.
+  const int cols = EPI == 2 ? N / 2 : N;
+  const long tiles = (long)((M + 127) / 128) * ((cols + (EPI == 2 ? 63 : 127)) / (EPI == 2 ? 64 : 128));
+  if (tiles >= compute_units() / 2) return launch_f32_shape<4, EPI == 2 ? 2 : 4, false, EPI, TR, TC>(M, N, K, A, W, R, C, st);
+  if (M <= 16) return launch_f32_shape<1, 1, true, EPI, TR, TC>(M, N, K, A, W, R, C, st);
+  return launch_f32_shape<2, EPI == 2 ? 1 : 2, true, EPI, TR, TC>(M, N, K, A, W, R, C, st);
 }
 
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K) {

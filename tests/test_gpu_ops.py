@@ -186,6 +186,32 @@ def test_gemm_f32(epi, N, K, M):
     H.assert_close_elementwise(H.to_f64(C), ref, 1e-5, 1e-5, "gemm f32")
 
 
+# the three fp32 arrangements (16 rows, 32 x 32 with K split over waves, 128 x 128) around their edges, with rows that
+# can and cannot be read 16 bytes at a time
+@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (16, 192, 324), (17, 192, 61), (33, 1000, 515), (130, 64, 1028),
+                                   (1025, 2112, 67), (2050, 1088, 260)])
+def test_gemm_f32_arrangements(M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a = torch.randn((M, K), generator=g, device="cuda")
+    w = torch.randn((N, K), generator=g, device="cuda") * 0.05
+    wt = torch.empty(B.tiled_weight_elems(N, K), device="cuda")
+    B.op_tile_weight(B.PS_F32, N, K, w, wt)
+    r = torch.randn((M, N), generator=g, device="cuda")
+    ref = a.double() @ w.double().T
+    bound = (a.double().abs() @ w.double().abs().T) * (2 * K * 2.0 ** -24) + 2.0 ** -23 * (ref.abs() + r.double().abs())
+    c = torch.empty((M, N), device="cuda")
+    B.op_gemm(B.PS_F32, 0, B.PS_F32, B.PS_EPI_STORE, M, N, K, a, wt, None, c)
+    assert bool(((c.double() - ref).abs() <= bound).all()), "store"
+    B.op_gemm(B.PS_F32, B.PS_F32, B.PS_F32, B.PS_EPI_RESIDUAL, M, N, K, a, wt, r, c)
+    assert bool(((c.double() - ref - r.double()).abs() <= bound).all()), "residual"
+    if N % 64 == 0:
+        m = torch.empty((M, N // 2), device="cuda")
+        B.op_gemm(B.PS_F32, 0, B.PS_F32, B.PS_EPI_SWIGLU, M, N, K, a, wt, None, m)
+        gu = ref.view(M, N // 64, 2, 32)
+        want = (torch.nn.functional.silu(gu[:, :, 0]) * gu[:, :, 1]).reshape(M, N // 2)
+        assert bool(((m.double() - want).abs() <= 1e-5 + 1e-5 * want.abs()).all()), "swiglu"
+
+
 @pytest.mark.parametrize("dt,N,K", [("bf16", 192, 320), ("bf16", 100, 70), ("f32", 65, 129), ("f32", 1, 1)])
 def test_op_tile_weight_matches_host_tiling(dt, N, K):
     """Device tiling is bit-identical to the host helper, padding included."""
@@ -610,4 +636,28 @@ def test_attention_f32(hist, new):
         ref = O.attention(q[r0:r0 + n].astype(np.float64), Ks[b].astype(np.float64), Vs[b].astype(np.float64),
                           np.arange(L, L + n))
         H.assert_close_elementwise(got[r0:r0 + n], ref, 1e-5, 1e-5, "attn f32")
+        r0 += n
+
+
+# 16-wave workgroups (at most 256 row-head pairs) past 1024 keys, 4-wave ones past 256; head_dim 128, 64 and sizes whose
+# rows are not 16-byte multiples; groups the MFMA kernels do not take; stale pool slots hold NaN
+@pytest.mark.parametrize("dtype,n_q,n_kv,hd,hist,new", [
+    ("f32", 4, 2, 64, [1500, 0, 63], [1, 1, 1]), ("f32", 4, 4, 128, [64, 127, 1023], [1, 1, 1]),
+    ("f32", 8, 2, 64, [0, 300], [70, 33]), ("f32", 6, 3, 6, [5, 130], [3, 60]),
+    ("bf16", 6, 2, 64, [1200, 15], [2, 5]), ("bf16", 3, 1, 128, [400, 16], [60, 40]), ("bf16", 5, 5, 10, [70], [90])])
+def test_generic_attention_shapes(dtype, n_q, n_kv, hd, hist, new):
+    shape = LayerShape(n_q * hd, n_q, n_kv, hd, 64, 1e-5, 10000.0, dtype)
+    P = make_pool(shape, 256, 4, 128, seed=9)
+    seqs, Ks, Vs = fill_kv(P, hist, new, dtype, 900)
+    rows = sum(new)
+    q = rnd((rows, n_q, hd), dtype, 64, 2.0)
+    o = H.empty((rows, n_q * hd), dtype)
+    B.op_attention(P.kv, 0, seqs, new, H.to_dev(q, dtype), o, H.workspace(1 << 20))
+    sync()
+    got, r0 = H.to_f64(o).reshape(rows, n_q, hd), 0
+    atol, rtol = (H.BF16_TOL_ABS, H.BF16_TOL_REL) if dtype == "bf16" else (1e-5, 1e-5)
+    for b, (L, n) in enumerate(zip(hist, new)):
+        ref = O.attention(gen.widen(q[r0:r0 + n], dtype), gen.widen(Ks[b], dtype), gen.widen(Vs[b], dtype),
+                          np.arange(L, L + n))
+        H.assert_close_elementwise(got[r0:r0 + n], ref, atol, rtol, f"generic attention b={b}")
         r0 += n
