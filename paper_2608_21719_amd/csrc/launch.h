@@ -112,9 +112,6 @@ __device__ inline void upload_block(const UploadJob& j, int b) {
 bool make_upload_job(const void* host_dev_ptr, void* dst, size_t bytes, uint32_t* done, uint32_t tag, UploadJob* j);
 // Enqueues the job as its own kernel.
 int launch_upload(const UploadJob& j, hipStream_t st);
-// True when launch_rmsnorm for these types runs the kernel that can carry an
-// upload job in leading workgroups of its own grid.
-bool rmsnorm_carries_upload(int x_dt, int g_dt, int y_dt, int d);
 int launch_embed(int rows, int d, int vocab, const void* table, const int32_t* tokens, void* x, hipStream_t st);
 int launch_gather_rows(int n, int d, const void* src, const int32_t* rows, void* dst, hipStream_t st);
 int launch_argmax(int rows, int vocab, const float* logits, int32_t* next, hipStream_t st);
