@@ -255,7 +255,8 @@ __device__ __forceinline__ int find_seq_wave(const SeqInfo* __restrict__ si, int
 // ---------------------------------------------------------------- RoPE + KV
 // One row per workgroup: rotate the row's q and k heads (rotate-half, angle
 // pos * inv_freq[j] evaluated in fp64), write q to q_out and k, v into the
-// row's page slot. bf16 rows move four pairs per thread with 8-byte accesses.
+// row's page slot. bf16 rows move four pairs per thread with 8-byte accesses;
+// up to 1536 rows (above, rope_kvwrite_rows_kernel takes 16 at a time).
 // PART (bf16, decode): the QKV row is not materialised; it is the sum of the
 // GEMM's S split-K partials (fp32 [S][rows][n_q + 2 n_kv][hd]) in split order,
 // rounded to bf16, exactly what the separate reduce kernel would have stored.
@@ -494,7 +495,11 @@ int launch_rope_kvwrite(int dt, int rows, const void* qkv, void* q_out, void* po
     return -1;
   }
   const size_t v_lds = (size_t)kRopeRows * n_kv * hd * sizeof(bf16_t);
-  if (dt == 1 && hd % 16 == 0 && v_lds <= 64 * 1024) {
+  // 16 rows per workgroup only from 1537 rows: below that its workgroups
+  // leave compute units idle (8B shape, us, one row / 16 rows: 256 decode rows
+  // 6.8 / 18.0, one prompt of 389 7.4 / 10.2, 3 x 373 11.6 / 17.7, 4 x 512
+  // 16.1 / 12.2, 8 x 389 23.7 / 22.0)
+  if (dt == 1 && rows > 1536 && hd % 16 == 0 && v_lds <= 64 * 1024) {
     static const hipError_t attr = hipFuncSetAttribute((const void*)rope_kvwrite_rows_kernel,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
     if (attr != hipSuccess) return -1;

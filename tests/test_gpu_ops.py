@@ -369,6 +369,43 @@ def test_rope_kvwrite(dtype, shape):
         r0 += n
 
 
+@pytest.mark.parametrize("shape", [S8, S70], ids=["8B", "70B"])
+def test_rope_kvwrite_large_batch_equals_per_sequence_calls_bit_for_bit(shape):
+    """More than 1536 rows take 16 rows per workgroup (groups that fill a page,
+    groups that straddle sequences or pages, a partial last group); each
+    sequence alone takes one row per workgroup. Same bits either way."""
+    hist, new = [0, 5, 300, 32, 0], [7, 16, 41, 900, 805]
+    rows = sum(new)
+    qkv = H.to_dev(rnd((rows, (shape.n_q + 2 * shape.n_kv) * shape.head_dim), "bf16", 43), "bf16")
+    ws, res = H.workspace(1 << 22), []
+    for together in (True, False):
+        P = H.Pool(shape, 200, 5, 64, seed=6)
+        seqs = [P.kv.open() for _ in hist]
+        for s, L, n in zip(seqs, hist, new):
+            P.kv.alloc(s, L + n)
+            if L:
+                z = torch.zeros((L, shape.n_kv, shape.head_dim), dtype=torch.bfloat16, device="cuda")
+                P.kv.append(0, [s], [L], z, z, ws)
+                P.kv.commit([s], [L])
+        q = H.empty((rows, shape.d_q), "bf16")
+        if together:
+            B.op_rope_kvwrite(P.kv, 0, seqs, new, qkv, q, ws)
+        else:
+            r0 = 0
+            for s, n in zip(seqs, new):
+                B.op_rope_kvwrite(P.kv, 0, [s], [n], qkv[r0:r0 + n], q[r0:r0 + n], ws)
+                r0 += n
+        P.kv.commit(seqs, new)
+        out = [q]
+        for s, L, n in zip(seqs, hist, new):
+            out += [H.empty((L + n, shape.n_kv, shape.head_dim), "bf16") for _ in range(2)]
+            P.kv.gather(0, s, out[-2], out[-1], ws)
+        sync()
+        res.append(out)
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(H.bits(a), H.bits(b))
+
+
 # ------------------------------------------------------------------ attention
 def fill_kv(P, lens_hist, n_new, dtype, seed, ones_v=False):
     """Open sequences, write history (committed) and new rows (uncommitted)."""
