@@ -569,6 +569,98 @@ std::vector<PrefillItem> plan_prefill(const std::vector<SeqInfo>& si, size_t cou
   return it;
 }
 
+// The same work with long key walks split over workgroups, for launches whose
+// query tiles do not fill the chip's workgroup slots (three per compute unit):
+// a few rows behind long cached prefixes, where a launch lasts as long as one
+// workgroup's serial walk. Empty `items`: not worth it.
+struct PrefillSplit {
+  std::vector<PrefillSplitItem> items;
+  std::vector<PrefillMerge> merges;
+  int32_t n_parts = 0;
+};
+
+// `groups`: workgroups per query tile (4 query heads each); `max_parts`: room
+// for partial results. For one, two and three workgroups per compute unit, the
+// shortest split length (at least 24 key tiles) whose items fit that many and
+// whose parts fit the room; the cheapest of them and the whole walk is taken,
+// each tile's walk cut into near-equal ranges. Costs in us, measured: a key
+// tile of a workgroup's walk takes 0.65, 0.95 and 1.5 with one, two and three
+// workgroups on a compute unit; the merge is a launch (8) and its partials'
+// traffic. Whole walk -> split and merged, 8B shape: 64 rows behind 16000
+// tokens 324 -> 51 us, 512 behind 4000 96 -> 64, three of 300 to 512 behind
+// 6000 to 12000 306 -> 199; 1024 behind 2000 stays whole (68; cut to fill three
+// workgroups per unit it took 72).
+PrefillSplit plan_prefill_split(const std::vector<SeqInfo>& si, size_t count, int groups, int n_q, int max_parts) {
+  PrefillSplit P;
+  const int qt = fa_query_tile(), kt = fa_key_tile();
+  struct Tile {
+    int32_t b, q0, tiles;
+  };
+  std::vector<Tile> t;
+  const int slots = 3 * compute_units() / std::max(1, groups);
+  for (size_t b = 0; b < count; ++b)
+    for (int32_t q0 = 0; q0 < si[b].n_new; q0 += qt) {
+      if ((int)t.size() >= slots) return P;
+      const int32_t keys = si[b].kv_before + std::min(q0 + qt, si[b].n_new);
+      t.push_back(Tile{(int32_t)b, q0, (keys + kt - 1) / kt});
+    }
+  int longest = 0;
+  for (const Tile& x : t) longest = std::max(longest, x.tiles);
+  constexpr int kMinTiles = 24;
+  if (longest < 2 * kMinTiles) return P;
+  auto count_items = [&](int len, int* parts) {
+    int n = 0;
+    *parts = 0;
+    for (const Tile& x : t) {
+      const int k = (x.tiles + len - 1) / len;
+      n += k;
+      if (k > 1) *parts += k;
+    }
+    return n;
+  };
+  auto per_tile = [&](int items) {
+    const double r = (double)items * groups / compute_units();
+    return r <= 1 ? 0.65 : r <= 2 ? 0.65 + 0.3 * (r - 1) : 0.95 + 0.55 * (r - 2);
+  };
+  const double whole = longest * per_tile((int)t.size());
+  double best = 0.9 * whole;  // a split has to promise a tenth
+  int len = 0;
+  for (int r = 1; r <= 3; ++r) {
+    const int room = r * compute_units() / std::max(1, groups);
+    if ((int)t.size() > room) continue;
+    int lo = kMinTiles - 1, hi = longest, parts = 0;  // the counts fall as the length grows; `longest` fits
+    while (lo + 1 < hi) {
+      const int mid = (lo + hi) / 2;
+      if (count_items(mid, &parts) <= room && parts <= max_parts) hi = mid;
+      else lo = mid;
+    }
+    const int n = count_items(hi, &parts);
+    const double cost = hi * per_tile(n) + 8.0 + parts * (double)qt * n_q * 128 * 8.0 / 4.0e6;
+    if (parts > 0 && cost < best) best = cost, len = hi;
+  }
+  if (len == 0) return P;
+  for (const Tile& x : t) {
+    const int k = (x.tiles + len - 1) / len;
+    if (k == 1) {
+      P.items.push_back(PrefillSplitItem{x.b, x.q0, 0, x.tiles, -1});
+      continue;
+    }
+    P.merges.push_back(PrefillMerge{si[x.b].row_start + x.q0, std::min(qt, si[x.b].n_new - x.q0), P.n_parts, k});
+    for (int i = 0; i < k; ++i)
+      P.items.push_back(PrefillSplitItem{x.b, x.q0, (int32_t)((long)i * x.tiles / k), (int32_t)((long)(i + 1) * x.tiles / k),
+                                         P.n_parts + i});
+    P.n_parts += k;
+  }
+  std::stable_sort(P.items.begin(), P.items.end(), [](const PrefillSplitItem& a, const PrefillSplitItem& c) {
+    return a.kt_end - a.kt_begin > c.kt_end - c.kt_begin;
+  });
+  return P;
+}
+
+// Bytes of one part: O, and its bases and sums.
+size_t fa_part_bytes(int n_q) { return (size_t)fa_query_tile() * n_q * 128 * sizeof(float); }
+size_t fa_part_ml_bytes(int n_q) { return (size_t)fa_query_tile() * n_q * 2 * sizeof(float); }
+
 bool use_mfma_attn(const ps_layer_cfg& c) { return c.dtype == PS_BF16 && c.head_dim == 128; }
 int group_of(const ps_layer_cfg& c) { return c.n_q_heads / c.n_kv_heads; }
 bool fa_ok(const ps_layer_cfg& c) { return use_mfma_attn(c) && group_of(c) % 4 == 0 && group_of(c) <= 64; }
@@ -644,6 +736,8 @@ size_t meta_bound(const ps_layer_cfg& c, int32_t max_rows, int32_t max_seqs, int
   const size_t parts = (size_t)max_seqs * ((max_pages + 7) / 8);
   b += align_up(sizeof(DecodeItem) * parts, 256) + 2 * align_up(4ull * max_seqs, 256);
   b += align_up(sizeof(PrefillItem) * ((size_t)max_rows / 32 + max_seqs), 256);
+  // split prefill items: at most one per workgroup slot
+  if (fa_ok(c)) b += 2 * align_up(sizeof(PrefillSplitItem) * 3 * compute_units(), 256);
   return b + 256;
 }
 
@@ -942,15 +1036,35 @@ struct LayerPlan {
   bool fa = false, dec_mfma = false;
   size_t o_si = 0, o_bt = 0, o_fr = 0, o_pi = 0, o_di = 0, o_pb = 0, o_pc = 0;
   int n_pitems = 0, n_ditems = 0;
+  int n_merges = 0;  // > 0: the prefill items are split ones
+  size_t o_mg = 0;
   int32_t n_parts = 0;
   int32_t n_seqs = 0;
   Meta mt;
   WsLayout wl;
 };
 
+// Room for split prefill attention's partial results in a layer call, all of
+// it idle while attention runs: the chunk rows of h and m, which nothing holds
+// yet, and the caller stream's GEMM partials, whose last reader was RoPE, take
+// the parts' O; the chunk rows of xn, read by the QKV GEMM before, their bases
+// and sums.
+struct FaRoom {
+  int end[2];  // slots in h, in h and m
+  int parts;
+};
+FaRoom fa_layer_parts(const ps_layer_cfg& c, int32_t chunk_rows, int32_t rows) {
+  const size_t part = fa_part_bytes(c.n_q_heads);
+  const WsLayout wl = layout(c, 0, rows, 0);
+  const size_t h = (size_t)chunk_rows * c.hidden * 4 / part, m = (size_t)chunk_rows * c.ffn * 2 / part;
+  const size_t g = (wl.gemm_b - wl.gemm) / part;
+  const size_t ml = (size_t)chunk_rows * c.hidden * 2 / fa_part_ml_bytes(c.n_q_heads);
+  return FaRoom{{(int)h, (int)(h + m)}, (int)std::min(h + m + g, ml)};
+}
+
 ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int32_t n_chunk,
                      const int32_t* chunk_seqs, const int32_t* chunk_tok, int32_t n_dec, const int32_t* dec_seqs,
-                     LayerPlan& P) {
+                     bool may_split, LayerPlan& P) {
   if (phase < PS_PHASE_PREFILL || phase > PS_PHASE_ANSWER) return fail(PS_E_INVALID, "bad phase");
   CallSeqs cs;
   if (ps_status rc = plan_seqs(kv, n_chunk, chunk_seqs, chunk_tok, -1, cs)) return rc;
@@ -975,9 +1089,20 @@ ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int3
   P.fa = fa_ok(c) && n_chunk > 0;
   P.dec_mfma = dec_ok(c) && n_dec > 0;
   if (P.fa) {
-    std::vector<PrefillItem> pitems = plan_prefill(cs.si, n_chunk);
-    P.n_pitems = (int)pitems.size();
-    P.o_pi = P.mt.add(pitems.data(), pitems.size() * sizeof(PrefillItem));
+    PrefillSplit sp;
+    if (may_split)
+      sp = plan_prefill_split(cs.si, n_chunk, c.n_kv_heads * (group_of(c) / 4), c.n_q_heads,
+                              fa_layer_parts(c, P.chunk_rows, P.rows).parts);
+    if (!sp.items.empty()) {
+      P.n_pitems = (int)sp.items.size();
+      P.n_merges = (int)sp.merges.size();
+      P.o_pi = P.mt.add(sp.items.data(), sp.items.size() * sizeof(PrefillSplitItem));
+      P.o_mg = P.mt.add(sp.merges.data(), sp.merges.size() * sizeof(PrefillMerge));
+    } else {
+      std::vector<PrefillItem> pitems = plan_prefill(cs.si, n_chunk);
+      P.n_pitems = (int)pitems.size();
+      P.o_pi = P.mt.add(pitems.data(), pitems.size() * sizeof(PrefillItem));
+    }
   }
   if (P.dec_mfma) {
     DecodePlan dp = plan_decode(cs.si, n_chunk, choose_split_pages(cs.si, n_chunk, c.n_kv_heads, phase));
@@ -1087,7 +1212,12 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
     }
   };
   auto prefill_attn = [&](hipStream_t s) {
-    if (P.fa)
+    if (P.fa && P.n_merges > 0) {
+      const FaRoom room = fa_layer_parts(c, P.chunk_rows, P.rows);
+      bad |= launch_fa_prefill_split(G, P.n_pitems, P.n_merges, c.n_kv_heads, qr, pool, si, bt,
+                                     (const PrefillSplitItem*)(W + P.o_pi), (const PrefillMerge*)(W + P.o_mg),
+                                     FaPartials{{(float*)h, (float*)m, (float*)gws}, {room.end[0], room.end[1]}, (float*)xn}, o, scale_log2, s);
+    } else if (P.fa)
       bad |= launch_fa_prefill(G, P.n_pitems, c.n_kv_heads, qr, pool, si, bt, (const PrefillItem*)(W + P.o_pi), o,
                                scale_log2, s);
     else
@@ -1181,11 +1311,16 @@ ps_status run_layer(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, 
     return fail(PS_E_INVALID, "layer and KV pool configurations differ");
   if (ps_status rc = check_layer(kv, layer)) return rc;
   LayerPlan P;
-  if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, P)) return rc;
+  if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
   if (P.rows == 0) return PS_OK;
   if (!x_in || !x_out) return fail(PS_E_INVALID, "null activation pointer");
   if (ps_status rc = check_aligned({x_in, x_out})) return rc;
   P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+  if (P.n_merges > 0 && ws_bytes < P.wl.total) {  // no room for the longer work list: the unsplit walk
+    P = LayerPlan{};
+    if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
+    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+  }
   if (ps_status rc = check_ws(ws, ws_bytes, P.wl.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
   AuxStream* aux = nullptr;
@@ -1234,7 +1369,7 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
   if (!same_cfg(c, kv->cfg)) return fail(PS_E_INVALID, "model and KV pool configurations differ");
   if (kv->n_layers < M->n_layers) return fail(PS_E_INVALID, "KV pool has fewer layers than the model");
   LayerPlan P;
-  if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, P)) return rc;
+  if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
   if (P.rows == 0) return PS_OK;
   if (!tokens || !next) return fail(PS_E_INVALID, "null token pointer");
   if (ps_status rc = check_aligned({logits_out})) return rc;
@@ -1251,9 +1386,16 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
     }
     for (int i = 0; i < n_dec; ++i) last[n_chunk + i] = r + i;
   }
-  const size_t o_last = P.mt.add(last.data(), last.size() * 4);
+  size_t o_last = P.mt.add(last.data(), last.size() * 4);
   P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
-  const ModelWs mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out);
+  ModelWs mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out);
+  if (P.n_merges > 0 && ws_bytes < mw.total) {  // no room for the longer work list: the unsplit walk
+    P = LayerPlan{};
+    if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
+    o_last = P.mt.add(last.data(), last.size() * 4);
+    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+    mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out);
+  }
   if (ps_status rc = check_ws(ws, ws_bytes, mw.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (ps_status rc = upload_meta(kv, P.mt, ws, st)) return rc;
@@ -1503,10 +1645,25 @@ extern "C" ps_status ps_op_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, c
   const size_t o_bt = mt.add(cs.bt.data(), cs.bt.size() * 4);
   const bool fa = fa_ok(c);
   std::vector<PrefillItem> pitems;
-  size_t o_pi = 0;
+  PrefillSplit sp;
+  size_t o_pi = 0, o_mg = 0, off_po = 0, off_ml = 0;
   if (fa) {
-    pitems = plan_prefill(cs.si, cs.si.size());
-    o_pi = mt.add(pitems.data(), pitems.size() * sizeof(PrefillItem));
+    // split where the workspace has room for the partial results behind the metadata
+    const size_t part = fa_part_bytes(c.n_q_heads), ml = fa_part_ml_bytes(c.n_q_heads);
+    const size_t fixed = mt.size() + 2 * align_up(sizeof(PrefillSplitItem) * 3 * compute_units(), 256) + 1024;
+    if (ws_bytes > fixed)
+      sp = plan_prefill_split(cs.si, cs.si.size(), c.n_kv_heads * (group_of(c) / 4), c.n_q_heads,
+                              (int)std::min<size_t>((ws_bytes - fixed) / (part + ml), 1 << 20));
+    if (!sp.items.empty()) {
+      o_pi = mt.add(sp.items.data(), sp.items.size() * sizeof(PrefillSplitItem));
+      o_mg = mt.add(sp.merges.data(), sp.merges.size() * sizeof(PrefillMerge));
+      off_po = mt.size();
+      off_ml = off_po + sp.n_parts * part;
+      if (off_ml + sp.n_parts * ml > ws_bytes) return fail(PS_E_INVALID, "internal error: split attention workspace");
+    } else {
+      pitems = plan_prefill(cs.si, cs.si.size());
+      o_pi = mt.add(pitems.data(), pitems.size() * sizeof(PrefillItem));
+    }
   }
   if (ps_status rc = check_ws(ws, ws_bytes, mt.size())) return rc;
   if (cs.rows == 0) return PS_OK;
@@ -1519,7 +1676,13 @@ extern "C" ps_status ps_op_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, c
   char* W = (char*)ws;
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
   int bad;
-  if (fa)
+  if (fa && !sp.items.empty())
+    bad = launch_fa_prefill_split(group_of(c), (int)sp.items.size(), (int)sp.merges.size(), c.n_kv_heads, q,
+                                  kv->layer_base(layer), (const SeqInfo*)(W + o_si), (const int32_t*)(W + o_bt),
+                                  (const PrefillSplitItem*)(W + o_pi), (const PrefillMerge*)(W + o_mg),
+                                  FaPartials{{(float*)(W + off_po), nullptr, nullptr}, {sp.n_parts, sp.n_parts}, (float*)(W + off_ml)}, o,
+                                  scale_log2, st);
+  else if (fa)
     bad = launch_fa_prefill(group_of(c), (int)pitems.size(), c.n_kv_heads, q, kv->layer_base(layer),
                             (const SeqInfo*)(W + o_si), (const int32_t*)(W + o_bt), (const PrefillItem*)(W + o_pi), o,
                             scale_log2, st);

@@ -77,4 +77,23 @@ struct PrefillItem {
   int32_t q_begin;  // first new row of the tile, relative to the sequence's new rows
 };
 
+// One key range of a query tile whose walk is split over workgroups: key
+// tiles (32 keys) [kt_begin, kt_end). part < 0: the whole walk, output
+// written directly; else the index of its partial result.
+struct PrefillSplitItem {
+  int32_t b;
+  int32_t q_begin;
+  int32_t kt_begin;
+  int32_t kt_end;
+  int32_t part;
+};
+
+// A split query tile's merge: its first output row, rows, first part, parts.
+struct PrefillMerge {
+  int32_t row;
+  int32_t n_rows;
+  int32_t part;
+  int32_t n_parts;
+};
+
 }  // namespace ps

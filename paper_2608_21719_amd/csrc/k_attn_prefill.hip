@@ -69,12 +69,13 @@ __device__ __forceinline__ void fa_barrier() {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void fa_prefill_kernel(const bf16_t* __restrict__ q,
-                                                         const bf16_t* __restrict__ pool,
-                                                         const SeqInfo* __restrict__ si,
-                                                         const int32_t* __restrict__ bt,
-                                                         const PrefillItem* __restrict__ items,
-                                                         bf16_t* __restrict__ o, int n_kv, int G, float scale_log2) {
+// SPLIT: an item is a range of its query tile's key tiles (PrefillSplitItem);
+// parts leave O unnormalised with their base and sum for the merge kernel.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void fa_prefill_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool, const SeqInfo* __restrict__ si,
+    const int32_t* __restrict__ bt, const typename std::conditional<SPLIT, PrefillSplitItem, PrefillItem>::type* __restrict__ items,
+    bf16_t* __restrict__ o, int n_kv, int G, float scale_log2, FaPartials parts) {
   constexpr int NT = 256;
   constexpr int NPG = 2;
   constexpr int kKB = kPageTokens * kHd;  // elements of a page's K block (its V^T block follows)
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
 
   const int hq = G / 4;
   const int kvh = blockIdx.y / hq;
-  const PrefillItem it = items[blockIdx.x];
+  const auto it = items[blockIdx.x];
   const SeqInfo s = si[it.b];
   const int n_q = n_kv * G;
   const int t = threadIdx.x;
@@ -104,7 +105,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
   const int n_keys = qpos0 + qn;
   const int kv_valid = s.kv_before + s.n_new;
   const int32_t* btr = bt + s.bt_off;
-  const int n_tiles = (n_keys + KT - 1) / KT;
+  // key tiles kt0 .. n_tiles - 1; kt0's first key is visible to every row
+  int kt0 = 0, n_tiles = (n_keys + KT - 1) / KT;
+  if constexpr (SPLIT) kt0 = it.kt_begin, n_tiles = it.kt_end;
   const bf16_t* pool_h = pool + (long)kvh * (2L * kKB);
   const long page_stride = (long)n_kv * (2L * kKB);
 
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
   const uint32_t vread = (uint32_t)(c * kPageTokens * 2 + ((g ^ ((c >> 3) & 1)) << 4));  // + page, dim block
 
   // one key tile: K, V hold it; the next tile's fills go to nK, nV
-  int pid_next = n_tiles > 1 ? page_id(KT) : 0;
+  int pid_next = kt0 + 1 < n_tiles ? page_id((kt0 + 1) * KT) : 0;
   // `firstc`: std::true_type for the walk's first tile, which sets the base
   auto tile = [&](int kt, const bf16_t* K, const bf16_t* V, bf16_t* nK, bf16_t* nV, auto firstc) {
     constexpr bool FIRST = decltype(firstc)::value;
@@ -203,8 +206,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     }
     // P = 2^(s scale - mb) against the row's exponent base mb, and this
     // lane's partial row sum of the bf16 P values. The first tile sets the
-    // base from its own row max (key 0 is visible to every query row, so that
-    // max is finite). After it, the sum doubles as the test of the base: past
+    // base from its own row max (its first key is visible to every query row,
+    // so that max is finite). After it, the sum doubles as the test of the base: past
     // 2^32 (or infinite or NaN, where an exponent overflowed) the tile takes
     // the slow path, which takes the row's true max over the tile, rescales O
     // and l to it and redoes the exponentials. While the base stands no max
@@ -266,15 +269,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     }
   };
 
-  issue(0, page_id(0), sK0, sV0);
+  issue(kt0 * KT, page_id(kt0 * KT), sK0, sV0);
   fa_barrier();
-  if (KT > kv_valid) {
-    zero_tail(0, sV0);
+  if ((kt0 + 1) * KT > kv_valid) {
+    zero_tail(kt0 * KT, sV0);
     fa_barrier();
   }
-  // tile t sits in slot t & 1; the first tile is peeled (it sets the base)
-  tile(0, sK0, sV0, sK1, sV1, std::true_type{});
-  for (int kt = 1; kt < n_tiles; kt += 2) {
+  // tile kt0 + t sits in slot t & 1; the first tile is peeled (it sets the base)
+  tile(kt0, sK0, sV0, sK1, sV1, std::true_type{});
+  for (int kt = kt0 + 1; kt < n_tiles; kt += 2) {
     tile(kt, sK1, sV1, sK0, sV0, std::false_type{});
     if (kt + 1 < n_tiles) tile(kt + 1, sK0, sV0, sK1, sV1, std::false_type{});
   }
@@ -282,6 +285,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
   {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
     const float l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);  // lower half's part + upper half's
+    if constexpr (SPLIT) {
+      if (it.part >= 0) {
+        const long head_tile = (long)n_q * kQT * kHd;  // floats per part
+        float* po = parts.part(it.part, head_tile) + ((long)head * kQT + c) * kHd;
+        if (c < qn) {
+#pragma unroll
+          for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb)
+              *(float4*)(po + 32 * db + 8 * rb + 4 * g) =
+                  make_float4(oacc[db][4 * rb], oacc[db][4 * rb + 1], oacc[db][4 * rb + 2], oacc[db][4 * rb + 3]);
+          if (g == 0) *(float2*)(parts.ml + (((long)it.part * n_q + head) * kQT + c) * 2) = make_float2(mb, l);
+        }
+        return;
+      }
+    }
     if (c < qn) {
       const float inv = 1.f / l;
       bf16_t* op = o + ((long)(s.row_start + it.q_begin + c) * n_q + head) * kHd;
@@ -298,15 +317,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
   }
 }
 
+// o[row, head, :] = sum_p O_p 2^(m_p - M) / sum_p l_p 2^(m_p - M), parts of one
+// query tile in key order. A wave per head, two dimensions per lane. The pass
+// is bound by the partials' traffic (16 KiB per row and part at 32 heads).
+__global__ __launch_bounds__(256) void fa_merge_kernel(const PrefillMerge* __restrict__ merges, FaPartials parts,
+                                                       bf16_t* __restrict__ o, int n_q) {
+  const PrefillMerge mg = merges[blockIdx.x / kQT];
+  const int c = blockIdx.x % kQT;
+  const int head = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (c >= mg.n_rows) return;
+  const long head_tile = (long)n_q * kQT * kHd;
+  const float* ml = parts.ml + (((long)mg.part * n_q + head) * kQT + c) * 2;
+  const long ml_step = (long)n_q * kQT * 2;
+  float M = -INFINITY;
+  for (int p = 0; p < mg.n_parts; ++p) M = fmaxf(M, ml[p * ml_step]);
+  float x = 0.f, y = 0.f, L = 0.f;
+  for (int p = 0; p < mg.n_parts; ++p) {
+    const float* po = parts.part(mg.part + p, head_tile) + ((long)head * kQT + c) * kHd;
+    const float2 v = *(const float2*)(po + 2 * lane);
+    const float f = exp2f(ml[p * ml_step] - M);
+    x += v.x * f;
+    y += v.y * f;
+    L += ml[p * ml_step + 1] * f;
+  }
+  *(uint32_t*)(o + ((long)(mg.row + c) * n_q + head) * kHd + 2 * lane) = pack_bf2(x / L, y / L);
+}
+
 int fa_query_tile() { return kQT; }
+int fa_key_tile() { return KT; }
 
 int launch_fa_prefill(int G, int n_items, int n_kv, const void* q, const void* pool_layer, const SeqInfo* si,
                       const int32_t* bt, const PrefillItem* items, void* o, float scale_log2, hipStream_t st) {
   if (n_items == 0) return 0;
   if (G % 4 != 0) return -1;
   dim3 grid(n_items, n_kv * (G / 4));
-  hipLaunchKernelGGL(fa_prefill_kernel, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, bt,
-                     items, (bf16_t*)o, n_kv, G, scale_log2);
+  hipLaunchKernelGGL(fa_prefill_kernel<false>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si,
+                     bt, items, (bf16_t*)o, n_kv, G, scale_log2, FaPartials{});
+  return 0;
+}
+
+int launch_fa_prefill_split(int G, int n_items, int n_merges, int n_kv, const void* q, const void* pool_layer,
+                            const SeqInfo* si, const int32_t* bt, const PrefillSplitItem* items,
+                            const PrefillMerge* merges, FaPartials part, void* o, float scale_log2, hipStream_t st) {
+  if (n_items == 0) return 0;
+  if (G % 4 != 0) return -1;
+  hipLaunchKernelGGL(fa_prefill_kernel<true>, dim3(n_items, n_kv * (G / 4)), dim3(256), 0, st, (const bf16_t*)q,
+                     (const bf16_t*)pool_layer, si, bt, items, (bf16_t*)o, n_kv, G, scale_log2, part);
+  if (n_merges > 0)
+    hipLaunchKernelGGL(fa_merge_kernel, dim3(n_merges * kQT, n_kv * (G / 4)), dim3(256), 0, st, merges, part, (bf16_t*)o,
+                       n_kv * G);
   return 0;
 }
 

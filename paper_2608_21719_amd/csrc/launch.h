@@ -41,6 +41,25 @@ int launch_attn_generic(int dt, int row0, int rows, int n_seqs, int n_q, int n_k
                         hipStream_t st);
 int compute_units();  // of the current device (256 if the query fails)
 int fa_query_tile();  // query rows per prefill work item
+// Where the partial results of split query tiles go: part p's O (fp32,
+// [n_q][32 rows][128]) in slot p of o[0] for p < end[0], in slot p - end[0] of
+// o[1] for p < end[1], else in slot p - end[1] of o[2]; bases and sums (fp32
+// [part][n_q][32][2]) in ml.
+struct FaPartials {
+  float* o[3];
+  int end[2];
+  float* ml;
+  __device__ float* part(int p, long part_floats) const {
+    if (p < end[0]) return o[0] + p * part_floats;
+    if (p < end[1]) return o[1] + (p - end[0]) * part_floats;
+    return o[2] + (p - end[1]) * part_floats;
+  }
+};
+int fa_key_tile();  // keys per tile of a prefill walk
+// launch_fa_prefill over split items, then the merge of the split tiles.
+int launch_fa_prefill_split(int G, int n_items, int n_merges, int n_kv, const void* q, const void* pool_layer,
+                            const SeqInfo* si, const int32_t* bt, const PrefillSplitItem* items,
+                            const PrefillMerge* merges, FaPartials part, void* o, float scale_log2, hipStream_t st);
 int launch_fa_prefill(int G, int n_items, int n_kv, const void* q, const void* pool_layer, const SeqInfo* si,
                       const int32_t* bt, const PrefillItem* items, void* o, float scale_log2, hipStream_t st);
 

@@ -383,3 +383,53 @@ def test_admitted_mixed_batch_matches_oracle():
     for s, n in zip(first + new, (1, 1, 64, 48)):
         sched.finish(s, n)
     assert sched.running() == 0 and h.kv.free_pages() == 200
+
+
+def test_8b_chunk_behind_long_prefix_split_walks(h8):
+    """80 rows behind 3000 cached tokens: the key walks are split, their partial
+    results in the call's own workspace (idle rows of h, m, xn and the GEMM
+    partials). Alone, and as the chunk of a forked mixed step beside decode
+    rows (the same bits); the workspace a call without the split needs is
+    still accepted and takes the whole walk. All against the oracle."""
+    sh, g = h8.shape, torch.Generator(device="cuda").manual_seed(81)
+    pre, n, decs = 3000, 80, [700, 90, 1500]
+    hist = [pre] + decs
+    kvh = [tuple(torch.randn((L, sh.n_kv, sh.head_dim), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+           for L in hist]
+    pools, seqs = [H.Pool(sh, 360, 4, 200, seed=31 + i) for i in range(3)], []
+    nbytes = B.Layer.workspace_bytes(pools[0].cfg, n + len(decs), 4, 200)
+    ws = H.workspace(nbytes)
+    for p in pools:
+        seqs.append([p.kv.open() for _ in hist])
+        for s, L, (k, v) in zip(seqs[-1], hist, kvh):
+            p.kv.alloc(s, L + n)
+            p.kv.append(0, [s], [L], k, v, ws)
+            p.kv.commit([s], [L])
+    xb = gen.mixed_input(h8.wl, n + len(decs))
+    x = H.to_dev(xb, "bf16")
+    out_m, out_p, out_w = (H.empty((r, sh.hidden), "bf16") for r in (n + len(decs), n, n))
+    h8.layer.mixed_step(h8.dev.w, pools[0].kv, 0, seqs[0][:1], [n], seqs[0][1:], x, out_m, ws)
+    h8.layer.prefill(h8.dev.w, pools[1].kv, 0, seqs[1][:1], [n], x[:n].contiguous(), out_p, ws)
+    sync()
+    assert torch.equal(out_m[:n].view(torch.int16), out_p.view(torch.int16)), "chunk rows differ from the plain prefill"
+    # the smallest workspace the call accepts has no room for the split's longer work list
+    lo, hi = 1, nbytes
+    while lo < hi:
+        mid = (lo + hi) // 2
+        try:
+            h8.layer.prefill(h8.dev.w, pools[2].kv, 0, seqs[2][:1], [n], x[:n].contiguous(), out_w, ws[:mid])
+            hi = mid
+        except B.PsError:
+            lo = mid + 1
+    h8.layer.prefill(h8.dev.w, pools[2].kv, 0, seqs[2][:1], [n], x[:n].contiguous(), out_w, ws[:hi])
+    sync()
+    assert not torch.equal(out_w, out_p), "the smallest workspace was expected to take the whole walk"
+    xf = gen.widen(xb, "bf16")
+    rows = [0, 31, 32, 63, 64, 79]
+    hk, hv = (H.to_f64(t) for t in kvh[0])
+    ref = O.layer_rows(h8.wf, sh, xf[:n], rows, hk, hv)
+    for name, out in (("split", out_p), ("whole", out_w)):
+        check(H.to_f64(out)[rows], ref, "bf16", f"chunk rows, {name} walk")
+    for i, (k, v) in enumerate(kvh[1:]):
+        ref = O.layer_rows(h8.wf, sh, xf[n + i:n + i + 1], [0], H.to_f64(k), H.to_f64(v))
+        check(H.to_f64(out_m)[n + i:n + i + 1], ref, "bf16", f"decode row {i}")

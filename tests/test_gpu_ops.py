@@ -698,3 +698,38 @@ def test_generic_attention_shapes(dtype, n_q, n_kv, hd, hist, new):
                           np.arange(L, L + n))
         H.assert_close_elementwise(got[r0:r0 + n], ref, atol, rtol, f"generic attention b={b}")
         r0 += n
+
+
+# few query tiles behind long prefixes: key walks split over workgroups (cut at tiles every row sees), with a partial
+# last query tile, a short walk left whole beside them, and a row whose keys end inside a page
+SPLIT_PRE = {"long": ([6000, 9001, 0, 2500], [33, 100, 40, 1]), "one": ([3000], [64]), "diagonal": ([1700], [900])}
+
+
+@pytest.mark.parametrize("shape", [S8, S70], ids=["G4", "G8"])
+@pytest.mark.parametrize("case", list(SPLIT_PRE))
+@pytest.mark.parametrize("room", [1 << 28, 6 << 20, 1 << 17], ids=["roomy", "few-parts", "unsplit"])
+def test_prefill_attention_split_key_walks(shape, case, room):
+    hist, new = SPLIT_PRE[case]
+    P = make_pool(shape, 1200, 4, 600, seed=22)
+    seqs, Ks, Vs = fill_kv(P, hist, new, "bf16", 740)
+    rows = sum(new)
+    q = rnd((rows, shape.n_q, shape.head_dim), "bf16", 65, 2.0)
+    o = H.empty((rows, shape.d_q), "bf16")
+    B.op_attention(P.kv, 0, seqs, new, H.to_dev(q, "bf16"), o, H.workspace(room))
+    sync()
+    got, qf, r0 = H.to_f64(o).reshape(rows, shape.n_q, shape.head_dim), gen.widen(q, "bf16"), 0
+    for b, (L, n) in enumerate(zip(hist, new)):
+        pick = sorted({0, n // 2, n - 1, min(31, n - 1), min(32, n - 1)})
+        ref = O.attention(qf[r0:r0 + n][pick], gen.widen(Ks[b], "bf16"), gen.widen(Vs[b], "bf16"), L + np.array(pick))
+        H.assert_close_elementwise(got[r0:r0 + n][pick], ref, H.BF16_TOL_ABS, H.BF16_TOL_REL, f"{case} b={b}")
+        r0 += n
+
+
+def test_prefill_attention_split_ones_v_gives_exactly_one():
+    P = make_pool(S8, 700, 2, 600, seed=23)
+    seqs, _, _ = fill_kv(P, [6000, 3333], [70, 5], "bf16", 760, ones_v=True)
+    q = rnd((75, S8.n_q, S8.head_dim), "bf16", 66, 3.0)
+    o = H.empty((75, S8.d_q), "bf16")
+    B.op_attention(P.kv, 0, seqs, [70, 5], H.to_dev(q, "bf16"), o, H.workspace(1 << 27))
+    sync()
+    assert np.all(H.to_f64(o) == 1.0)
