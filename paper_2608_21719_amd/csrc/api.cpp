@@ -1166,8 +1166,9 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   // O projection + residual -> h (fp32), then the FFN RMSNorm -> xn, over
   // `n` rows from row r0. Split-K partials (a decode-sized skinny plan, or a
   // tile launch that would leave compute units idle) are summed by the norm
-  // kernel, which also adds the residual and stores h.
-  auto o_proj = [&](int r0, int n, void* ws, size_t ws_bytes, hipStream_t s) {
+  // kernel, which also adds the residual and stores h. `own_cu`: the norm runs
+  // on compute units of its own (see launch_rmsnorm_own_cu).
+  auto o_proj = [&](int r0, int n, void* ws, size_t ws_bytes, hipStream_t s, bool own_cu = false) {
     if (n == 0) return;
     const char* a = o + (size_t)r0 * dq * eb;
     const char* res = (const char*)x_in + (size_t)r0 * d * eb;
@@ -1189,7 +1190,9 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
       bad |= launch_gemm(dt, dt, PS_F32, PS_EPI_RESIDUAL, n, d, dq, a, w->w_o, res, hr, ws, ws_bytes, s);
     }
     if (S > 1)
-      bad |= launch_split_residual_rmsnorm(n, d, S, (const float*)ws, res, hr, w->ffn_norm, c.rms_eps, y, s);
+      bad |= launch_split_residual_rmsnorm(n, d, S, (const float*)ws, res, hr, w->ffn_norm, c.rms_eps, y, s, own_cu);
+    else if (own_cu)
+      bad |= launch_rmsnorm_own_cu(n, d, hr, w->ffn_norm, c.rms_eps, y, s);
     else
       bad |= launch_rmsnorm(PS_F32, dt, dt, n, d, hr, w->ffn_norm, c.rms_eps, y, s);
   };
@@ -1285,7 +1288,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   swiglu(cr, P.n_dec, gws_b, gws_b_bytes, sb);
   down_proj(cr, P.n_dec, gws_b, gws_b_bytes, sb);
   prefill_attn(st);
-  o_proj(0, cr, gws, gws_bytes, st);
+  o_proj(0, cr, gws, gws_bytes, st, true);
   swiglu(0, cr, gws, gws_bytes, st);
   down_proj(0, cr, gws, gws_bytes, st);
   link(sb, st, 1);  // joined: the call's work is on the caller's stream again

@@ -41,10 +41,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const TX* __restrict__ x, 
 
 // Second half of the vectorised RMSNorm, shared by the kernels that hold a
 // row in registers (v[c][e] = element (c * 256 + threadIdx.x) * 8 + e):
-// sum of squares in that order, wave then workgroup reduction, bf16 output.
-template <int VPT>
+// sum of squares in that order, wave then row reduction, bf16 output. YB rows
+// per workgroup (256 threads each, threadIdx.y); `live`: the row exists.
+template <int VPT, int YB = 1>
 __device__ __forceinline__ void rmsnorm_row_out(const float (&v)[VPT][8], const bf16_t* __restrict__ g,
-                                                bf16_t* __restrict__ yr, int d, float eps) {
+                                                bf16_t* __restrict__ yr, int d, float eps, bool live = true) {
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < VPT; ++c) {
@@ -55,7 +56,8 @@ __device__ __forceinline__ void rmsnorm_row_out(const float (&v)[VPT][8], const 
     }
   }
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-  __shared__ float red[4];
+  __shared__ float reds[YB][4];
+  float* red = reds[YB > 1 ? threadIdx.y : 0];
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
   float tot = red[0] + red[1] + red[2] + red[3];
@@ -63,7 +65,7 @@ __device__ __forceinline__ void rmsnorm_row_out(const float (&v)[VPT][8], const 
 #pragma unroll
   for (int c = 0; c < VPT; ++c) {
     int i = (c * 256 + threadIdx.x) * 8;
-    if (i < d) {
+    if (live && i < d) {
       uint4 gw = *(const uint4*)(g + i);
       uint32_t gs[4] = {gw.x, gw.y, gw.z, gw.w};
       uint32_t o[4];
@@ -78,19 +80,22 @@ __device__ __forceinline__ void rmsnorm_row_out(const float (&v)[VPT][8], const 
 // Vectorised bf16 -> bf16 variant: 8 elements per 16-byte access, the row
 // kept in registers between the two passes (d <= 256 * 8 * VPT).
 // up as in rmsnorm_kernel.
-template <typename TX, int VPT>
-__global__ __launch_bounds__(256) void rmsnorm_vec_kernel(const TX* __restrict__ x, const bf16_t* __restrict__ g,
-                                                          bf16_t* __restrict__ y, int d, float eps, UploadJob up) {
-  if ((int)blockIdx.x < up.blocks) {
+// YB > 1: YB rows per workgroup, no upload.
+template <typename TX, int VPT, int YB = 1>
+__global__ __launch_bounds__(256 * YB) void rmsnorm_vec_kernel(const TX* __restrict__ x, const bf16_t* __restrict__ g,
+                                                               bf16_t* __restrict__ y, int rows, int d, float eps,
+                                                               UploadJob up) {
+  if (YB == 1 && (int)blockIdx.x < up.blocks) {
     upload_block(up, blockIdx.x);
     return;
   }
-  const long row = blockIdx.x - up.blocks;
+  const long row = YB == 1 ? (long)blockIdx.x - up.blocks : (long)blockIdx.x * YB + threadIdx.y;
+  const bool live = YB == 1 || row < rows;
   float v[VPT][8];
 #pragma unroll
   for (int c = 0; c < VPT; ++c) {
     int i = (c * 256 + threadIdx.x) * 8;
-    if (i < d) {
+    if (live && i < d) {
       if constexpr (sizeof(TX) == 2) {
         uint4 w = *(const uint4*)(x + row * d + i);
         uint32_t ws[4] = {w.x, w.y, w.z, w.w};
@@ -107,20 +112,22 @@ __global__ __launch_bounds__(256) void rmsnorm_vec_kernel(const TX* __restrict__
       }
     }
   }
-  rmsnorm_row_out<VPT>(v, g, y + row * d, d, eps);
+  rmsnorm_row_out<VPT, YB>(v, g, y + row * d, d, eps, live);
 }
 
 // Decode-sized O projection fused with its consumer: h = sum of the split-K
 // partials of o W^T, in split order, + the residual x (bf16), stored fp32;
 // then hn = RMSNorm(h) * g from the same registers. The sum and the norm
 // are those of the separate reduce and RMSNorm kernels, bit for bit.
-template <int VPT, int S>
-__global__ __launch_bounds__(256) void split_residual_rmsnorm_kernel(const float* __restrict__ part, long mn,
+// YB rows per workgroup.
+template <int VPT, int S, int YB = 1>
+__global__ __launch_bounds__(256 * YB) void split_residual_rmsnorm_kernel(const float* __restrict__ part, int rows, long mn,
                                                                      const bf16_t* __restrict__ res,
                                                                      float* __restrict__ h,
                                                                      const bf16_t* __restrict__ g,
                                                                      bf16_t* __restrict__ y, int d, float eps) {
-  const long row = blockIdx.x;
+  const long row = YB == 1 ? (long)blockIdx.x : (long)blockIdx.x * YB + threadIdx.y;
+  const bool live = YB == 1 || row < rows;
   float v[VPT][8];
   // every partial and residual load of the row is issued before the sums
   // (S is a compile-time count): one round of memory latency, not S x VPT
@@ -129,7 +136,7 @@ __global__ __launch_bounds__(256) void split_residual_rmsnorm_kernel(const float
 #pragma unroll
   for (int c = 0; c < VPT; ++c) {
     const int i = (c * 256 + threadIdx.x) * 8;
-    if (i < d) {
+    if (live && i < d) {
       const long off = row * d + i;
 #pragma unroll
       for (int sp = 0; sp < S; ++sp) {
@@ -142,7 +149,7 @@ __global__ __launch_bounds__(256) void split_residual_rmsnorm_kernel(const float
 #pragma unroll
   for (int c = 0; c < VPT; ++c) {
     const int i = (c * 256 + threadIdx.x) * 8;
-    if (i < d) {
+    if (live && i < d) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[c][e] = 0.f;
 #pragma unroll
@@ -161,26 +168,42 @@ __global__ __launch_bounds__(256) void split_residual_rmsnorm_kernel(const float
       *(float4*)(h + off + 4) = make_float4(v[c][4], v[c][5], v[c][6], v[c][7]);
     }
   }
-  rmsnorm_row_out<VPT>(v, g, y + row * d, d, eps);
+  rmsnorm_row_out<VPT, YB>(v, g, y + row * d, d, eps, live);
 }
 
+// Dynamic LDS that leaves a compute unit no room for another workgroup that
+// uses more than 7 KiB.
+constexpr size_t kOwnCuLds = 153 * 1024;
+
 int launch_split_residual_rmsnorm(int rows, int d, int S, const float* part, const void* res, float* h,
-                                  const void* g, float eps, void* y, hipStream_t st) {
+                                  const void* g, float eps, void* y, hipStream_t st, bool own_cu) {
   if (rows == 0) return 0;
   if (d % 8 != 0 || d > 256 * 8 * 4) return -1;
   const long mn = (long)rows * d;
-#define SRR_CASE(S_)                                                                                        \
-  if (S == S_) {                                                                                            \
-    hipLaunchKernelGGL((split_residual_rmsnorm_kernel<4, S_>), dim3(rows), dim3(256), 0, st, part, mn,       \
-                       (const bf16_t*)res, h, (const bf16_t*)g, (bf16_t*)y, d, eps);                        \
-    return 0;                                                                                               \
+  auto go = [&](auto sc) {
+    constexpr int SS = decltype(sc)::value;
+    if constexpr (SS <= 4) {
+      if (own_cu) {
+        constexpr int YB = 2;  // the row's partials in registers allow two rows
+        static const hipError_t attr = hipFuncSetAttribute((const void*)split_residual_rmsnorm_kernel<4, SS, YB>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOwnCuLds);
+        if (attr != hipSuccess) return -1;
+        hipLaunchKernelGGL((split_residual_rmsnorm_kernel<4, SS, YB>), dim3((rows + YB - 1) / YB), dim3(256, YB), kOwnCuLds,
+                           st, part, rows, mn, (const bf16_t*)res, h, (const bf16_t*)g, (bf16_t*)y, d, eps);
+        return 0;
+      }
+    }
+    hipLaunchKernelGGL((split_residual_rmsnorm_kernel<4, SS>), dim3(rows), dim3(256), 0, st, part, rows, mn,
+                       (const bf16_t*)res, h, (const bf16_t*)g, (bf16_t*)y, d, eps);
+    return 0;
+  };
+  switch (S) {
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 8: return go(std::integral_constant<int, 8>{});
+    default: return -1;
   }
-  SRR_CASE(2)
-  SRR_CASE(3)
-  SRR_CASE(4)
-  SRR_CASE(8)
-#undef SRR_CASE
-  return -1;
 }
 
 int launch_rmsnorm(int x_dt, int g_dt, int y_dt, int rows, int d, const void* x, const void* g, float eps,
@@ -192,10 +215,10 @@ int launch_rmsnorm(int x_dt, int g_dt, int y_dt, int rows, int d, const void* x,
   if (g_dt == 1 && y_dt == 1 && d % 8 == 0 && d <= 256 * 8 * 4) {
     if (x_dt == 1) {
       hipLaunchKernelGGL((rmsnorm_vec_kernel<bf16_t, 4>), grid, block, 0, st, (const bf16_t*)x,
-                         (const bf16_t*)g, (bf16_t*)y, d, eps, j);
+                         (const bf16_t*)g, (bf16_t*)y, rows, d, eps, j);
     } else {
       hipLaunchKernelGGL((rmsnorm_vec_kernel<float, 4>), grid, block, 0, st, (const float*)x,
-                         (const bf16_t*)g, (bf16_t*)y, d, eps, j);
+                         (const bf16_t*)g, (bf16_t*)y, rows, d, eps, j);
     }
     return 0;
   }
@@ -215,6 +238,18 @@ int launch_rmsnorm(int x_dt, int g_dt, int y_dt, int rows, int d, const void* x,
   RMS_CASE(bf16_t, float, bf16_t, 1, 0, 1)
 #undef RMS_CASE
   return -1;
+}
+
+int launch_rmsnorm_own_cu(int rows, int d, const float* x, const void* g, float eps, void* y, hipStream_t st) {
+  constexpr int YB = 4;
+  if (rows == 0) return 0;
+  if (d % 8 || d > 256 * 8 * 4) return -1;
+  static const hipError_t attr = hipFuncSetAttribute((const void*)rmsnorm_vec_kernel<float, 4, YB>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOwnCuLds);
+  if (attr != hipSuccess) return -1;
+  hipLaunchKernelGGL((rmsnorm_vec_kernel<float, 4, YB>), dim3((rows + YB - 1) / YB), dim3(256, YB), kOwnCuLds, st, x,
+                     (const bf16_t*)g, (bf16_t*)y, rows, d, eps, UploadJob{});
+  return 0;
 }
 
 // ---------------------------------------------------------------- paging

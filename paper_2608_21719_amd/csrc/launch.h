@@ -13,14 +13,22 @@ namespace ps {
 struct UploadJob;
 int launch_rmsnorm(int x_dt, int g_dt, int y_dt, int rows, int d, const void* x, const void* g, float eps,
                    void* y, hipStream_t st, const UploadJob* up = nullptr);
+// fp32 rows -> bf16, d a multiple of 8 up to 8192, several rows per workgroup
+// and nearly all of a compute unit's LDS: beside another stream's attention
+// the norm's workgroups then run only on units that hold none of it. Spread
+// over all units they share the streaming units' load queues: 2048 rows of
+// 4096 in the mixed step (4 x 512 chunk rows, 32 long contexts) took 83 us,
+// on their own units 20 (the step 1166 -> 1076 us).
+int launch_rmsnorm_own_cu(int rows, int d, const float* x, const void* g, float eps, void* y, hipStream_t st);
 
 // part/splits: when splits > 1 (bf16), the QKV rows are the sum of `splits`
 // fp32 split-K partials at part (see launch_gemm_split), qkv is not read
 int launch_rope_kvwrite(int dt, int rows, const void* qkv, void* q_out, void* pool_layer, const SeqInfo* si,
                         const int32_t* bt, const double* inv_freq, int n_seqs, int n_q, int n_kv, int hd,
                         hipStream_t st, const float* part = nullptr, int splits = 1);
+// own_cu as launch_rmsnorm_own_cu (S <= 4)
 int launch_split_residual_rmsnorm(int rows, int d, int S, const float* part, const void* res, float* h,
-                                  const void* g, float eps, void* y, hipStream_t st);
+                                  const void* g, float eps, void* y, hipStream_t st, bool own_cu = false);
 int launch_kv_append(int dt, int rows, const void* k, const void* v, void* pool_layer, const SeqInfo* si,
                      const int32_t* bt, int n_seqs, int n_kv, int hd, hipStream_t st);
 // Pages [0, n_pages) of one sequence, all n_layers layers, copied whole from
