@@ -372,8 +372,9 @@ ps_status ps_decode_step(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t la
  * the split-K decode path for decode rows. Same result as separate
  * ps_prefill and ps_decode_step calls up to rounding.
  * With more than 64 chunk rows and at most 64 decode rows (bf16, d a
- * multiple of 8 up to 8192) the call forks after the KV write: the decode
- * rows' attention and the rest of their layer (O, SwiGLU and down GEMMs)
+ * multiple of 8 up to 8192) the call may fork after the KV write (where
+ * one pass of the later GEMMs over all rows would cost more than reading
+ * their weights a second time): the decode rows' attention and the rest of their layer (O, SwiGLU and down GEMMs)
  * go to a second stream that the layer handle creates on first use
  * (default priority, on the caller's device), joined back into `stream` by
  * an event before the call returns: the caller sees one stream's ordering.

@@ -12,6 +12,7 @@
 #include <new>
 #include <string>
 #include <thread>
+#include <tuple>
 #include <vector>
 
 #include "../../include/ps.h"
@@ -1135,6 +1136,31 @@ ps_status stage_meta(ps_kv* kv, const Meta& mt, void* ws, UploadJob* job) {
   return kv->staging.prepare(slot, ws, mt.buf.size(), job);
 }
 
+// Whether a mixed step forks its decode rows onto the second stream. One pass
+// of the O, SwiGLU and down GEMMs over all rows reads each weight once; the
+// fork reads them a second time for the decode rows, mostly beside the chunk
+// rows' GEMMs. It pays where the decode rows would cost the tile launches a
+// further tile row or round: where that comes to more than 0.9 of the second
+// weight stream. Measured, one pass / forked, 8B (us): 300 + 32 rows 315 / 372,
+// 800 + 32 522 / 553, 1500 + 32 747 / 763, but 2048 + 32 1020 / 944 and, with
+// contexts of 13000, 1207 / 1090; 70B 600 + 32 1236 / 1440, 1024 + 32 1945 /
+// 1836. How long the decode attention is does not move the line: it overlaps
+// little either way.
+bool mixed_forks(const ps_layer_cfg& c, int32_t chunk_rows, int32_t n_dec) {
+  if (c.dtype != PS_BF16 || c.hidden % 8 || c.hidden > 8192 || n_dec <= 0 || n_dec > 64 || chunk_rows <= 64) return false;
+  const int d = c.hidden, dq = c.n_q_heads * c.head_dim;
+  auto cost = [&](int rows) {
+    double sum = 0, t;
+    for (auto [n, k, splits, swiglu] : {std::tuple{d, dq, 4, false}, {2 * c.ffn, d, 1, true}, {d, c.ffn, 4, false}}) {
+      gemm_tile_plan(rows, n, k, splits, swiglu, &t);
+      sum += t;
+    }
+    return sum;
+  };
+  const double stream = ((double)d * dq + 3.0 * d * c.ffn) * 2.0 / 5.0e6;  // us at 5 TB/s
+  return cost(chunk_rows + n_dec) - cost(chunk_rows) > 0.9 * stream;
+}
+
 // The kernels of one layer: x_in -> x_out for the planned rows.
 // `up`, if given, is the call's metadata upload: the first kernel carries it
 // (every kernel that reads the metadata runs after that one).
@@ -1253,14 +1279,14 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   bad |= launch_rope_kvwrite(dt, rows, qkv, qr, pool, si, bt, (const double*)(W + P.o_fr), P.n_seqs, c.n_q_heads,
                              c.n_kv_heads, c.head_dim, st, (const float*)gws, s_qkv);
 
-  // A mixed batch (prefill chunks + decode rows) splits after the KV write:
-  // the decode rows' attention (HBM-bound over long contexts) and the rest
-  // of their layer (skinny O, SwiGLU and down GEMMs, weight-bandwidth
-  // bound) run on the second stream while the chunk rows' flash attention
-  // and tile GEMMs run on the caller's. The two row sets write disjoint rows
-  // of o, h, xn, m and x_out, and each stream has its own split-K partials.
-  const bool fork = aux && P.n_chunk > 0 && P.n_dec > 0 && P.n_dec <= 64 && P.chunk_rows > 64 && fused_norm;
-  if (!fork) {
+  // A mixed batch (prefill chunks + decode rows) that forks (mixed_forks: `aux`
+  // is given) splits after the KV write: the decode rows' attention (HBM-bound
+  // over long contexts) and the rest of their layer (skinny O, SwiGLU and down
+  // GEMMs, weight-bandwidth bound) run on the second stream while the chunk
+  // rows' flash attention and tile GEMMs run on the caller's. The two row sets
+  // write disjoint rows of o, h, xn, m and x_out, and each stream has its own
+  // split-K partials.
+  if (!aux) {
     if (P.n_chunk > 0) prefill_attn(st);
     if (P.n_dec > 0) decode_attn(st, 0);
     o_proj(0, rows, gws, gws_bytes, st);
@@ -1327,7 +1353,7 @@ ps_status run_layer(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, 
   if (ps_status rc = check_ws(ws, ws_bytes, P.wl.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
   AuxStream* aux = nullptr;
-  if (n_chunk > 0 && n_dec > 0)
+  if (mixed_forks(c, P.chunk_rows, n_dec))
     if (ps_status rc = L->aux.get(st, &aux)) return rc;
   UploadJob up;
   if (ps_status rc = stage_meta(kv, P.mt, ws, &up)) return rc;

@@ -424,8 +424,9 @@ static double tile_cost(const TileCfg& t, int M, int N, int K, int S) {
 // in two splits); that bounds the partials at 256 KiB per tile and split. The
 // outputs of an unsplit launch do not depend on the tile shape: each is one
 // chain of the same MFMAs over K.
-TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu) {
+TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu, double* cost) {
   TilePlan best{0, 1};
+  if (cost) *cost = 0;
   if (M <= skinny::MAXM || N % 256 || K % tile::BK) return best;
   const long tiles256 = (long)((M + 255) / 256) * (N / 256);
   const int T = K / tile::BK;
@@ -438,6 +439,7 @@ TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu) {
       if ((S == 1 && i == 0) || c < best_cost) best = TilePlan{i, S}, best_cost = c;
     }
   }
+  if (cost) *cost = best_cost;
   return best;
 }
 

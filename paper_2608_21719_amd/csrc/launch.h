@@ -87,8 +87,9 @@ struct TilePlan {
   int cfg;  // tile shape, an index into the tile GEMM's table
   int s;    // K splits
 };
-// Tile shape and K splits (up to max_splits) of a tile-path GEMM (M > 64).
-TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu);
+// Tile shape and K splits (up to max_splits) of a tile-path GEMM (M > 64);
+// *cost: the launch's estimated microseconds.
+TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu, double* cost = nullptr);
 // K splits (1..4) for a tile-path GEMM (M > 64) whose fp32 partials a fused
 // consumer sums: chosen to cut the launch's rounds over the compute units,
 // weighed against the partials' traffic. 1 for the skinny path.
