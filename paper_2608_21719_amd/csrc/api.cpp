@@ -492,6 +492,25 @@ struct DecodePlan {
   int32_t n_parts = 0;
 };
 
+// Microseconds of decode attention with one split per sequence, all
+// workgroups resident: they share 6.7 TB/s evenly, at most 27 GB/s each, and
+// leave as they finish. Such a launch needs no combine (5.5 us) and pays one
+// ramp-up per sequence. 70B, 64 sequences at 4096: 159 us, in two splits each
+// and combined 168; 8B, 32 at 600: 15.7 and 21.5; but 64 of 1024 to 4096 tokens
+// 117 and 111: the longest run on alone.
+double whole_walk_us(std::vector<long> pages, int n_kv) {
+  std::sort(pages.begin(), pages.end());
+  constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kChip = 6.7e6, kGroup = 27.0e3;  // bytes per us
+  double us = 0;
+  long done = 0, active = (long)pages.size() * n_kv;
+  for (long p : pages) {
+    us += (p - done) * kPageBytes / std::min(kGroup, kChip / active);
+    done = p;
+    active -= n_kv;
+  }
+  return us;
+}
+
 int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_kv, int phase) {
   (void)phase;
   long total = 0;
@@ -515,8 +534,22 @@ int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_k
   long max_pages = 8;
   for (size_t b = first; b < si.size(); ++b) max_pages = std::max<long>(max_pages, (si[b].kv_before + si[b].n_new + 15) / 16);
   const long target_items = std::max(1, 1024 / std::max(1, n_kv));
+  const long n_seqs = (long)(si.size() - first);
+  if (n_seqs > 0 && n_seqs <= target_items) {
+    std::vector<long> pages;
+    for (size_t b = first; b < si.size(); ++b) pages.push_back((si[b].kv_before + si[b].n_new + 15) / 16);
+    const double split_us = total * n_kv * 8192.0 / 6.4e6 + 5.5;
+    if (whole_walk_us(std::move(pages), n_kv) < split_us) return (int32_t)((max_pages + 3) / 4 * 4);
+  }
   long sp = std::max<long>((total + target_items - 1) / target_items, 8);
   sp = (sp + 3) / 4 * 4;
+  // Short splits: up to 16 pages where a quarter of the workgroups then still
+  // fills the chip (8 sequences of 256 to 2048 tokens: 8 pages 17.0 us, 16
+  // 15.9; one of 2048 keeps 8: 11.0 against 11.5)
+  if (sp < 16) {
+    const long quarter = (total + target_items / 4) / std::max(1L, target_items / 4);
+    sp = std::max(sp, std::min(16L, (quarter + 3) / 4 * 4));
+  }
   if (n_items(sp) > target_items) {  // smallest multiple of 4 in (sp, max_pages] that fits: n_items falls as sp grows
     long lo = sp / 4, hi = (max_pages + 3) / 4;
     while (lo + 1 < hi) {

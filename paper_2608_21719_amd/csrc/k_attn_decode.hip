@@ -26,7 +26,8 @@
 // 4 FLOP per KV byte.
 //
 // A second kernel merges the splits of each (sequence, head) in split order
-// (log-sum-exp), which keeps the result deterministic.
+// (log-sum-exp), which keeps the result deterministic; a sequence in one split
+// is finished by the attention kernel itself.
 #include "common.h"
 #include "launch.h"
 
@@ -43,7 +44,8 @@ template <int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void decode_attn_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool, const SeqInfo* __restrict__ si,
     const int32_t* __restrict__ bt, const DecodeItem* __restrict__ items, float* __restrict__ part_o,
-    float* __restrict__ part_ml, int n_kv, int n_items, float scale_log2) {
+    float* __restrict__ part_ml, const int32_t* __restrict__ part_count, bf16_t* __restrict__ out, int n_kv, int n_items,
+    float scale_log2) {
   static_assert(G <= 16, "one 16-row MFMA tile per KV group");
   constexpr int D = kPrefetch;
   const int kvh = blockIdx.x;
@@ -211,6 +213,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
       if (head < G) s_acc[wave][head][16 * blk + c] = acc[blk][r];
     }
   __syncthreads();
+  // a sequence in one split is finished here (the combine's sums over one part
+  // are exact: weight 2^0)
+  const bool whole = part_count[it.b] == 1;
   const long part = (long)it.part * n_kv + kvh;
   for (int e = threadIdx.x; e < G * kHd; e += 256) {
     const int head = e / kHd, dim = e - head * kHd;
@@ -221,6 +226,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
       const float f = (s_m[w][head] == -INFINITY) ? 0.f : exp2f(s_m[w][head] - M);
       o += s_acc[w][head][dim] * f;
       L += s_l[w][head] * f;
+    }
+    if (whole) {
+      out[((long)it.b * n_q + kvh * G + head) * kHd + dim] = f2bf(o / L);
+      continue;
     }
     part_o[(part * G + head) * kHd + dim] = o;
     if (dim == 0) {
@@ -241,6 +250,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   const int b = blockIdx.x, head = blockIdx.y, dim = threadIdx.x;
   const int kvh = head / G, hg = head - kvh * G;
   const int p0 = part_begin[b], np = part_count[b];
+  if (np == 1) return;  // written by the attention kernel
   const long stride = (long)n_kv * G;  // between consecutive splits of one (sequence, head)
   const long pi0 = ((long)p0 * n_kv + kvh) * G + hg;
   // Loads go four splits at a time so that their latencies overlap; the
@@ -291,14 +301,19 @@ int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, 
   int gy = n_items;
   if (max_wg > 0) gy = std::max(1, std::min(n_items, max_wg / n_kv));
   dim3 grid(n_kv, gy);
+#define PS_DECODE_G(G_)                                                                                                \
+  hipLaunchKernelGGL(decode_attn_kernel<G_>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, \
+                     bt, items, part_o, part_ml, part_count, (bf16_t*)o, n_kv, n_items, scale_log2);
   switch (G) {
-    case 1: hipLaunchKernelGGL(decode_attn_kernel<1>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, bt, items, part_o, part_ml, n_kv, n_items, scale_log2); break;
-    case 2: hipLaunchKernelGGL(decode_attn_kernel<2>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, bt, items, part_o, part_ml, n_kv, n_items, scale_log2); break;
-    case 4: hipLaunchKernelGGL(decode_attn_kernel<4>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, bt, items, part_o, part_ml, n_kv, n_items, scale_log2); break;
-    case 8: hipLaunchKernelGGL(decode_attn_kernel<8>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, bt, items, part_o, part_ml, n_kv, n_items, scale_log2); break;
-    case 16: hipLaunchKernelGGL(decode_attn_kernel<16>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, bt, items, part_o, part_ml, n_kv, n_items, scale_log2); break;
+    case 1: PS_DECODE_G(1) break;
+    case 2: PS_DECODE_G(2) break;
+    case 4: PS_DECODE_G(4) break;
+    case 8: PS_DECODE_G(8) break;
+    case 16: PS_DECODE_G(16) break;
     default: return -1;
   }
+#undef PS_DECODE_G
+  if (n_items == n_seqs) return 0;  // every sequence in one split
   hipLaunchKernelGGL(decode_combine_kernel, dim3(n_seqs, n_kv * G), dim3(kHd), 0, st, part_o, part_ml,
                      part_begin, part_count, (bf16_t*)o, n_kv, G);
   return 0;

@@ -521,6 +521,29 @@ def test_decode_library_split_choice(n_seqs, hist, expect):
     assert np.any(outs[sp - 4] != outs[sp])
 
 
+# sequences of similar length that fill the chip take one split each (finished by the attention kernel, no combine);
+# one long sequence among them, or too few of them, keeps the splits
+@pytest.mark.parametrize("lens,whole", [([350] * 64, True), ([300 + 3 * i for i in range(40)], True),
+                                        ([4000] + [300] * 31, False), ([600] * 4, False)],
+                         ids=["equal", "similar", "one-long", "few"])
+def test_decode_one_split_per_sequence(lens, whole):
+    P = make_pool(S8, sum(-(-(L + 1) // 16) for L in lens) + 8, len(lens), 256, seed=33)
+    seqs, Ks, Vs = fill_kv(P, lens, [1] * len(lens), "bf16", 340)
+    qb = rnd((len(lens), S8.n_q, S8.head_dim), "bf16", 54)
+    q, ws, outs = H.to_dev(qb, "bf16"), H.workspace(1 << 26), {}
+    for split in (0, 256):
+        o = H.empty((len(lens), S8.d_q), "bf16")
+        B.op_decode_attention(P.kv, 0, seqs, q, o, ws, split_pages=split)
+        sync()
+        outs[split] = H.bits(o)
+        got = H.to_f64(o).reshape(len(lens), S8.n_q, S8.head_dim)
+        for b in {0, 1, len(lens) - 1}:
+            ref = O.attention(gen.widen(qb[b:b + 1], "bf16"), gen.widen(Ks[b], "bf16"), gen.widen(Vs[b], "bf16"),
+                              np.array([lens[b]]))
+            H.assert_close_elementwise(got[b:b + 1], ref, H.BF16_TOL_ABS, H.BF16_TOL_REL, f"split {split} seq {b}")
+    assert np.array_equal(outs[0], outs[256]) == whole
+
+
 def test_decode_plan_run_matches_one_call_and_detects_pool_change():
     """Plan once, run for two layers: bit-identical to the one-call op; a
     commit invalidates the plan."""
