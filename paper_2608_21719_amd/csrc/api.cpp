@@ -1220,6 +1220,14 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   // bf16, d a multiple of 8 up to 8192: a row fits the fused split-sum +
   // residual + RMSNorm kernel's registers
   const bool fused_norm = dt == PS_BF16 && d % 8 == 0 && d <= 8192;
+  // A pure decode step whose attention workgroups are all resident (two per
+  // compute unit): that launch does RoPE and the KV write. Every workgroup then
+  // starts about 5 us later, against a launch of 4.7 to 8.6 us saved, so one
+  // round gains (8B, us: one sequence 99.5 -> 96.1, 16 of 1000 tokens 110.2 ->
+  // 106.2) and several rounds lose (64 of 1024 to 4096 214 -> 218, 256 of 512
+  // to 2048 401 -> 412).
+  const bool rope_in_attn = P.dec_mfma && P.n_chunk == 0 && (long)P.n_ditems * c.n_kv_heads <= 2L * compute_units();
+  DecodeRope rope;
   int bad = 0;
 
   // O projection + residual -> h (fp32), then the FFN RMSNorm -> xn, over
@@ -1293,7 +1301,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
       bad |= launch_decode_attn(G, P.n_ditems, c.n_kv_heads, P.n_dec, qd, pool, si + P.n_chunk, bt,
                                 (const DecodeItem*)(W + P.o_di), (float*)(W + wl.apart_o), (float*)(W + wl.apart_ml),
                                 (const int32_t*)(W + P.o_pb), (const int32_t*)(W + P.o_pc), od, scale_log2, s,
-                                max_wg);
+                                max_wg, rope_in_attn ? &rope : nullptr);
     } else {
       bad |= launch_attn_generic(dt, P.chunk_rows, P.n_dec, P.n_seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, qr,
                                  pool, si, bt, o, scale, s);
@@ -1309,8 +1317,16 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
                              gws_bytes, st, &s_qkv);
   else
     bad |= launch_gemm(dt, 0, dt, PS_EPI_STORE, rows, dq + 2 * dkv, d, xn, w->w_qkv, nullptr, qkv, gws, gws_bytes, st);
-  bad |= launch_rope_kvwrite(dt, rows, qkv, qr, pool, si, bt, (const double*)(W + P.o_fr), P.n_seqs, c.n_q_heads,
-                             c.n_kv_heads, c.head_dim, st, (const float*)gws, s_qkv);
+  if (rope_in_attn) {
+    rope.qkv = (const bf16_t*)qkv;
+    rope.part = (const float*)gws;
+    rope.splits = s_qkv;
+    rope.mn = (long)rows * (dq + 2 * dkv);
+    rope.inv_freq = (const double*)(W + P.o_fr);
+  } else {
+    bad |= launch_rope_kvwrite(dt, rows, qkv, qr, pool, si, bt, (const double*)(W + P.o_fr), P.n_seqs, c.n_q_heads,
+                               c.n_kv_heads, c.head_dim, st, (const float*)gws, s_qkv);
+  }
 
   // A mixed batch (prefill chunks + decode rows) that forks (mixed_forks: `aux`
   // is given) splits after the KV write: the decode rows' attention (HBM-bound

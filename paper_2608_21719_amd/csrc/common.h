@@ -54,6 +54,12 @@ template <> struct Elt<bf16_t> {
   __device__ static void store(bf16_t* p, long i, float v) { p[i] = f2bf(v); }
 };
 
+// Rotate-half RoPE of one pair.
+__device__ __forceinline__ void rope_pair(float x1, float x2, float c, float s, float& y1, float& y2) {
+  y1 = x1 * c - x2 * s;
+  y2 = x2 * c + x1 * s;
+}
+
 // Per-call sequence record uploaded with the call's metadata.
 struct SeqInfo {
   int32_t kv_before;  // committed length before this call (first new position)

@@ -40,13 +40,21 @@ constexpr int kPrefetch = 2;  // pages in flight per wave beyond the current one
 
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-template <int G>
+// ROPE: the launch also does RoPE and the KV write of the step's new tokens (a
+// launch of its own takes 4.7 to 8.6 us; taken where one round of workgroups
+// does the batch). Every workgroup rotates its own G query heads from the QKV
+// projection while its first pages are on their way; the one whose range ends
+// with the sequence's last page also rotates the new key, writes key and value
+// to the page, and puts them into its own copy of that page in registers, so
+// no read depends on the write. The arithmetic is rope_kvwrite_kernel's.
+template <int G, bool ROPE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void decode_attn_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ pool, const SeqInfo* __restrict__ si,
+    const bf16_t* __restrict__ q, bf16_t* __restrict__ pool, const SeqInfo* __restrict__ si,
     const int32_t* __restrict__ bt, const DecodeItem* __restrict__ items, float* __restrict__ part_o,
     float* __restrict__ part_ml, const int32_t* __restrict__ part_count, bf16_t* __restrict__ out, int n_kv, int n_items,
-    float scale_log2) {
+    float scale_log2, DecodeRope rp) {
   static_assert(G <= 16, "one 16-row MFMA tile per KV group");
+  __shared__ __attribute__((aligned(16))) bf16_t s_q[ROPE ? G * kHd : 8], s_k[ROPE ? kHd : 8], s_v[ROPE ? kHd : 8];
   constexpr int D = kPrefetch;
   const int kvh = blockIdx.x;
   // items blockIdx.y, + gridDim.y, ...: one each when the grid covers them
@@ -61,9 +69,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4, c = lane & 15;
 
+  const int last_page = (kv_len - 1) / kPageTokens;
+  const bool has_new = ROPE && it.page_end == last_page + 1;  // this range holds the new token
+  // QKV inputs of this workgroup: (x1, x2) of pair j of a head per thread
+  constexpr int QP = ROPE ? (G * (kHd / 2) + 255) / 256 : 1;  // query pairs per thread
+  float qx[QP][2] = {}, kx[2] = {}, vx = 0.f;
+  double ang = 0.0;
+  if constexpr (ROPE) {
+    const long row = (long)it.b * (n_q + 2 * n_kv) * kHd;
+    const int t = threadIdx.x, j = t & 63;
+    ang = (double)s.kv_before * rp.inv_freq[j];
+    auto load = [&](auto get) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < QP; ++u) {
+        const int head = (t >> 6) + 4 * u;
+        if (head < G) {
+          const long col = row + (long)(kvh * G + head) * kHd + j;
+          qx[u][0] = get(col);
+          qx[u][1] = get(col + kHd / 2);
+        }
+      }
+      if (has_new) {
+        if (t < 64) {
+          const long col = row + (long)(n_q + kvh) * kHd + j;
+          kx[0] = get(col);
+          kx[1] = get(col + kHd / 2);
+        } else if (t < 64 + kHd) {
+          vx = get(row + (long)(n_q + n_kv + kvh) * kHd + t - 64);
+        }
+      }
+    };
+    auto sum = [&](auto sc) __attribute__((always_inline)) {
+      load([&](long col) __attribute__((always_inline)) {
+        constexpr int S = decltype(sc)::value;
+        float p[S];
+#pragma unroll
+        for (int i = 0; i < S; ++i) p[i] = rp.part[i * rp.mn + col];
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < S; ++i) a += p[i];
+        return bf2f(f2bf(a));
+      });
+    };
+    switch (rp.splits) {
+      case 2: sum(std::integral_constant<int, 2>{}); break;
+      case 3: sum(std::integral_constant<int, 3>{}); break;
+      case 4: sum(std::integral_constant<int, 4>{}); break;
+      case 8: sum(std::integral_constant<int, 8>{}); break;
+      default: load([&](long col) __attribute__((always_inline)) { return bf2f(rp.qkv[col]); }); break;
+    }
+  }
+
   // Q operand (B of the S^T product): lane holds q[head c][32j + 8g .. +8].
   bf16x8_t qb[4];
-  {
+  if constexpr (!ROPE) {
     const bf16_t* qp = q + ((long)it.b * n_q + kvh * G + (c < G ? c : 0)) * kHd + 8 * g;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -78,7 +137,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   for (int i = 0; i < 8; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const int32_t* btr = bt + s.bt_off;
-  const int last_page = (kv_len - 1) / kPageTokens;
   const int koff = c * kHd + 8 * g;                               // + 32 j
   const int voff = kPageTokens * kHd + c * kPageTokens + 4 * g;   // + 16 blk kPageTokens
   const long head_off = (long)kvh * (2L * kPageTokens * kHd);
@@ -104,8 +162,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
           uint2, __builtin_nontemporal_load((const u32x2_t*)(base + voff + 16 * blk * kPageTokens)));
   };
 
-  // consume one page held in `cur`
-  auto page_compute = [&](int p, PageRegs& cur) {
+  // consume one page held in `cur`; `tailc`: it may be the sequence's last
+  auto page_compute = [&](int p, PageRegs& cur, auto tailc) {
+    if constexpr (ROPE && decltype(tailc)::value) {
+      if (p == last_page) {  // the new token's slot: its key and value from LDS
+        const int slot = (kv_len - 1) % kPageTokens;
+        if (c == slot) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) cur.k[j] = *(const uint4*)(s_k + 32 * j + 8 * g);
+        }
+        if (g == slot >> 2) {
+          const uint32_t keep = (slot & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+          for (int blk = 0; blk < 8; ++blk) {
+            const uint32_t v = (uint32_t)s_v[16 * blk + c] << ((slot & 1) * 16);
+            if (slot & 2) cur.v[blk].y = (cur.v[blk].y & keep) | v;
+            else cur.v[blk].x = (cur.v[blk].x & keep) | v;
+          }
+        }
+      }
+    }
     // tokens past the written length (last page only) hold stale memory:
     // zero their V so 0 * garbage cannot produce NaN (branch-free, so no
     // wait on the page's loads is placed on a path of its own)
@@ -164,6 +240,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   __builtin_amdgcn_sched_barrier(0);  // page p's loads first (the wait for it below counts on that order)
   if (p + 4 < end) load_page(p + 4, r1);
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (ROPE) {
+    const int t = threadIdx.x, j = t & 63;
+    double sd, cd;
+    sincos(ang, &sd, &cd);
+    const float cs = (float)cd, sn = (float)sd;
+    float y1, y2;
+#pragma unroll
+    for (int u = 0; u < QP; ++u) {
+      const int head = (t >> 6) + 4 * u;
+      if (head < G) {
+        rope_pair(qx[u][0], qx[u][1], cs, sn, y1, y2);
+        s_q[head * kHd + j] = f2bf(y1);
+        s_q[head * kHd + j + kHd / 2] = f2bf(y2);
+      }
+    }
+    if (has_new) {
+      bf16_t* pg = pool + (long)btr[last_page] * page_stride + head_off;
+      const int slot = (kv_len - 1) % kPageTokens;
+      if (t < 64) {
+        rope_pair(kx[0], kx[1], cs, sn, y1, y2);
+        const bf16_t k1 = f2bf(y1), k2 = f2bf(y2);
+        s_k[j] = k1;
+        s_k[j + kHd / 2] = k2;
+        pg[slot * kHd + j] = k1;
+        pg[slot * kHd + j + kHd / 2] = k2;
+      } else if (t < 64 + kHd) {
+        const bf16_t v = f2bf(vx);
+        s_v[t - 64] = v;
+        pg[kPageTokens * kHd + (t - 64) * kPageTokens + slot] = v;
+      }
+    }
+    // LDS only: a full fence would wait for the pages in flight
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const uint4 w = (c < G) ? *(const uint4*)(s_q + c * kHd + 32 * jj + 8 * g) : make_uint4(0, 0, 0, 0);
+      qb[jj] = __builtin_bit_cast(bf16x8_t, w);
+    }
+  }
+  constexpr std::false_type kMid{};
+  constexpr std::true_type kTail{};
   // The scheduling barriers keep the order below: left free, the scheduler
   // hoists the next page's score MFMAs above this page's, so every round
   // began by waiting for both pages in flight (vmcnt(0)) and issued its
@@ -171,26 +290,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   for (; p + 16 < end; p += 12) {  // steady state: every request is a real page
     load_page(p + 8, r2);
     __builtin_amdgcn_sched_barrier(0);
-    page_compute(p, r0);
+    page_compute(p, r0, kMid);
     __builtin_amdgcn_sched_barrier(0);
     load_page(p + 12, r0);
     __builtin_amdgcn_sched_barrier(0);
-    page_compute(p + 4, r1);
+    page_compute(p + 4, r1, kMid);
     __builtin_amdgcn_sched_barrier(0);
     load_page(p + 16, r1);
     __builtin_amdgcn_sched_barrier(0);
-    page_compute(p + 8, r2);
+    page_compute(p + 8, r2, kMid);
     __builtin_amdgcn_sched_barrier(0);
   }
   if (p < end) {  // at most four pages left: p, p + 4, p + 8, p + 12
     if (p + 8 < end) load_page(p + 8, r2);
-    page_compute(p, r0);
+    page_compute(p, r0, kTail);
     if (p + 4 < end) {
       if (p + 12 < end) load_page(p + 12, r0);
-      page_compute(p + 4, r1);
+      page_compute(p + 4, r1, kTail);
       if (p + 8 < end) {
-        page_compute(p + 8, r2);
-        if (p + 12 < end) page_compute(p + 12, r0);
+        page_compute(p + 8, r2, kTail);
+        if (p + 12 < end) page_compute(p + 12, r0, kTail);
       }
     }
   }
@@ -292,18 +411,24 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   o[((long)b * n_kv * G + head) * kHd + dim] = f2bf(acc / L);
 }
 
-int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, const void* pool_layer,
+int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, void* pool_layer,
                        const SeqInfo* si, const int32_t* bt, const DecodeItem* items, float* part_o,
                        float* part_ml, const int32_t* part_begin, const int32_t* part_count, void* o,
-                       float scale_log2, hipStream_t st, int max_wg) {
+                       float scale_log2, hipStream_t st, int max_wg, const DecodeRope* rope) {
   if (n_seqs == 0) return 0;
   if (n_items > kMaxDecodeItems) return -1;
   int gy = n_items;
   if (max_wg > 0) gy = std::max(1, std::min(n_items, max_wg / n_kv));
   dim3 grid(n_kv, gy);
-#define PS_DECODE_G(G_)                                                                                                \
-  hipLaunchKernelGGL(decode_attn_kernel<G_>, grid, dim3(256), 0, st, (const bf16_t*)q, (const bf16_t*)pool_layer, si, \
-                     bt, items, part_o, part_ml, part_count, (bf16_t*)o, n_kv, n_items, scale_log2);
+  const DecodeRope rp = rope ? *rope : DecodeRope{};
+  if (rp.splits > 1 && rp.splits != 2 && rp.splits != 3 && rp.splits != 4 && rp.splits != 8) return -1;
+#define PS_DECODE_GO(G_, ROPE_)                                                                                  \
+  hipLaunchKernelGGL((decode_attn_kernel<G_, ROPE_>), grid, dim3(256), 0, st, (const bf16_t*)q,                 \
+                     (bf16_t*)pool_layer, si, bt, items, part_o, part_ml, part_count, (bf16_t*)o, n_kv,       \
+                     n_items, scale_log2, rp);
+#define PS_DECODE_G(G_)                    \
+  if (rp.splits) PS_DECODE_GO(G_, true)    \
+  else PS_DECODE_GO(G_, false)
   switch (G) {
     case 1: PS_DECODE_G(1) break;
     case 2: PS_DECODE_G(2) break;
@@ -313,6 +438,7 @@ int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, 
     default: return -1;
   }
 #undef PS_DECODE_G
+#undef PS_DECODE_GO
   if (n_items == n_seqs) return 0;  // every sequence in one split
   hipLaunchKernelGGL(decode_combine_kernel, dim3(n_seqs, n_kv * G), dim3(kHd), 0, st, part_o, part_ml,
                      part_begin, part_count, (bf16_t*)o, n_kv, G);

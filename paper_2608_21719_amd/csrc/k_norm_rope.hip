@@ -374,10 +374,7 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(const T* __restrict__
       load4(head * hd + j + half, x2);
       float y1[4], y2[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        y1[e] = x1[e] * cs[j + e] - x2[e] * sn[j + e];
-        y2[e] = x2[e] * cs[j + e] + x1[e] * sn[j + e];
-      }
+      for (int e = 0; e < 4; ++e) rope_pair(x1[e], x2[e], cs[j + e], sn[j + e], y1[e], y2[e]);
       T* d = dst_of(head);
       *(uint2*)(d + j) = make_uint2(pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3]));
       *(uint2*)(d + j + half) = make_uint2(pack_bf2(y2[0], y2[1]), pack_bf2(y2[2], y2[3]));

@@ -40,10 +40,22 @@ int launch_kv_copy_pages(size_t page_bytes, int n_pages, int n_layers, const voi
 int launch_kv_gather(int dt, int len, const void* pool_layer, const int32_t* bt, void* k_out, void* v_out,
                      int n_kv, int hd, hipStream_t st);
 
-int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, const void* pool_layer,
+// RoPE + KV write inside the decode attention launch, from the QKV projection
+// of the decode rows: row r is sequence r's, [q heads | k heads | v heads] of
+// 128, bf16 (splits 1: qkv) or the sum of `splits` fp32 partials (part, see
+// launch_gemm_split).
+struct DecodeRope {
+  const bf16_t* qkv = nullptr;
+  const float* part = nullptr;
+  int splits = 0;  // 0: no RoPE here, q is given and K, V are written
+  long mn = 0;     // elements of one partial
+  const double* inv_freq = nullptr;
+};
+int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, void* pool_layer,
                        const SeqInfo* si, const int32_t* bt, const DecodeItem* items, float* part_o,
                        float* part_ml, const int32_t* part_begin, const int32_t* part_count, void* o,
-                       float scale_log2, hipStream_t st, int max_wg = 0);  // max_wg > 0: at most that many workgroups
+                       float scale_log2, hipStream_t st, int max_wg = 0,  // max_wg > 0: at most that many workgroups
+                       const DecodeRope* rope = nullptr);
 int launch_attn_generic(int dt, int row0, int rows, int n_seqs, int n_q, int n_kv, int hd, const void* q,
                         const void* pool_layer, const SeqInfo* si, const int32_t* bt, void* o, float scale,
                         hipStream_t st);

@@ -436,3 +436,57 @@ def test_8b_chunk_behind_long_prefix_split_walks(h8, n):
     for i, (k, v) in enumerate(kvh[1:]):
         ref = O.layer_rows(h8.wf, sh, xf[n + i:n + i + 1], [0], H.to_f64(k), H.to_f64(v))
         check(H.to_f64(out_m)[n + i:n + i + 1], ref, "bf16", f"decode row {i}")
+
+
+# every group size of the fused RoPE + KV write + attention launch; hidden sets the QKV projection's K splits (1024: none,
+# 2048: 2, 3072: 3, 4096: 4, 5120: 5, summed by the GEMM's own reduce, 8192: 8)
+@pytest.mark.parametrize("n_q,n_kv,hidden", [(2, 2, 1024), (4, 2, 2048), (8, 2, 3072), (16, 2, 4096), (32, 2, 5120),
+                                             (4, 1, 8192)])
+def test_decode_step_rope_in_attention_equals_composed_ops_bit_for_bit(n_q, n_kv, hidden):
+    """A one-round decode step (RoPE and the KV write inside the attention
+    launch) against QKV GEMM, RoPE + KV write and attention called one by one:
+    contexts whose new token is a page's first or last slot or the only token,
+    sequences in one split and in many."""
+    from synth.configs import LayerShape, Workload
+    sh = LayerShape(hidden, n_q, n_kv, 128, 512, 1e-5, 500000.0, "bf16")
+    wl = Workload("rope_in_attn", 12, sh)
+    dev = H.DeviceLayer(gen.layer_weights(wl, 0), "bf16")
+    ctx = [0, 15, 16, 31, 40, 1500, 3007]
+    n, dq, dkv, d = len(ctx), sh.n_q * 128, sh.n_kv * 128, hidden
+    pools, seqs = [H.Pool(sh, sum(c // 16 + 1 for c in ctx) + 4, n, 200, seed=12) for _ in range(2)], [[], []]
+    ws = H.workspace(B.Layer.workspace_bytes(pools[0].cfg, n, n, 200) + (1 << 22))
+    g = torch.Generator(device="cuda").manual_seed(321)
+    for c in ctx:
+        k, v = (torch.randn((c, n_kv, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+        for p, ss in zip(pools, seqs):
+            ss.append(p.kv.open())
+            p.kv.alloc(ss[-1], c + 1)
+            if c:
+                p.kv.append(0, [ss[-1]], [c], k, v, ws)
+                p.kv.commit([ss[-1]], [c])
+    x = H.to_dev(gen.decode_input(wl, n, 0), "bf16")
+    out = H.empty((n, d), "bf16")
+    B.Layer(pools[0].cfg).decode_step(dev.w, pools[0].kv, 0, B.PS_PHASE_ANSWER, seqs[0], x, out, ws)
+    t, bf, f32 = dev.t, B.PS_BF16, B.PS_F32
+    xn, qkv, q, o = (H.empty((n, c), "bf16") for c in (d, dq + 2 * dkv, dq, dq))
+    hh, hn, m, ref = H.empty((n, d), "f32"), H.empty((n, d), "bf16"), H.empty((n, sh.ffn), "bf16"), H.empty((n, d), "bf16")
+    B.op_rmsnorm(bf, bf, bf, n, d, x, t["attn_norm"], sh.eps, xn)
+    B.op_gemm(bf, 0, bf, B.PS_EPI_STORE, n, dq + 2 * dkv, d, xn, t["w_qkv"], None, qkv, ws)
+    B.op_rope_kvwrite(pools[1].kv, 0, seqs[1], [1] * n, qkv, q, ws)
+    B.op_decode_attention(pools[1].kv, 0, seqs[1], q, o, ws)
+    B.op_gemm(bf, bf, f32, B.PS_EPI_RESIDUAL, n, d, dq, o, t["w_o"], x, hh, ws)
+    B.op_rmsnorm(f32, bf, bf, n, d, hh, t["ffn_norm"], sh.eps, hn)
+    B.op_gemm(bf, 0, bf, B.PS_EPI_SWIGLU, n, 2 * sh.ffn, d, hn, t["w_gate_up"], None, m, ws)
+    B.op_gemm(bf, f32, bf, B.PS_EPI_RESIDUAL, n, d, sh.ffn, m, t["w_down"], hh, ref, ws)
+    sync()
+    np.testing.assert_array_equal(H.bits(out), H.bits(ref))
+    kvs = []
+    for p, ss in zip(pools, seqs):
+        p.kv.commit(ss, [1] * n)
+        for s, c in zip(ss, ctx):
+            kvs.append([H.empty((c + 1, n_kv, 128), "bf16") for _ in range(2)])
+            p.kv.gather(0, s, *kvs[-1], ws)
+    sync()
+    for a, b in zip(kvs[:n], kvs[n:]):
+        for u, w in zip(a, b):
+            np.testing.assert_array_equal(H.bits(u), H.bits(w))
