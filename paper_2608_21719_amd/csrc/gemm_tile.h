@@ -37,10 +37,13 @@ __device__ __forceinline__ void load_lds16_buf(__amdgpu_buffer_rsrc_t r, uint32_
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voffset, 0, 0, 0);
 }
 // The same with a wave-uniform byte offset in the scalar offset operand: a
-// per-stage step added there costs no vector address arithmetic.
+// per-stage step added there costs no vector address arithmetic. NT: with the
+// non-temporal hint (cache policy bit 1).
+template <bool NT>
 __device__ __forceinline__ void load_lds16_buf_so(__amdgpu_buffer_rsrc_t r, uint32_t voffset, uint32_t soffset,
                                                   bf16_t* lds) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voffset, soffset, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voffset, soffset, 0,
+                                           NT ? 2 : 0);
 }
 // The same with the non-temporal hint (cache policy bit 1), for data read
 // exactly once per call (decode weight streams).
@@ -106,6 +109,13 @@ constexpr int min_c(int a, int b) { return a < b ? a : b; }
 // keep as many stages in flight as LDS holds (128x128 at M 128, N 28672,
 // K 4096: two slots 60 us, four 48, five 51).
 //
+// NT: for one tile row, where every weight is read by one workgroup only (and
+// some launches of two rows, see launch_tile), the weights' loads carry the
+// non-temporal hint and leave the caches to the activations, which all
+// workgroups share (us, without -> with, weights cold): N 28672, K 4096 at 80
+// rows 45.5 -> 41.5, at 256 61.8 -> 57.5; N 57344, K 8192 at 100 rows 160 ->
+// 142, at 256 252 -> 221; N 10240, K 8192 at 128 rows 55 -> 53.
+//
 // Schedule of stage st (slot st % NS), four 16-k slices of QM QN MFMAs each.
 // Every slice interleaves with its MFMAs:
 //  * the reads of the next slice's QM + QN fragments, spread from the first
@@ -152,7 +162,7 @@ struct Geo {
 constexpr int share(int n, int mf, int q) { return n * q / mf; }
 }  // namespace tile
 
-template <int QM, int QN, int NS, int EPI, typename TR, typename TC>
+template <int QM, int QN, int NS, bool NT, int EPI, typename TR, typename TC>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                         const TR* __restrict__ R, TC* __restrict__ C, int M, int N,
                                                         int K, int tiles_n, int group, int splits) {
@@ -213,10 +223,10 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const bf16_t* __restrict
   auto dma = [&](int s, int dslot, int l) __attribute__((always_inline)) {
     bf16_t* st = smem + dslot * STAGE;
     if (l < A_LOADS)
-      load_lds16_buf_so(rA, aoff[l], (s + st0) * BK * 2, st + (wave * A_LOADS + l) * RPL * BK);
+      load_lds16_buf_so<false>(rA, aoff[l], (s + st0) * BK * 2, st + (wave * A_LOADS + l) * RPL * BK);
     else
-      load_lds16_buf_so(rW, boff[l - A_LOADS], (s + st0) * kWTileElts * 2,
-                        st + G::A_ELTS + (wave * B_LOADS + l - A_LOADS) * RPL * BK);
+      load_lds16_buf_so<NT>(rW, boff[l - A_LOADS], (s + st0) * kWTileElts * 2,
+                            st + G::A_ELTS + (wave * B_LOADS + l - A_LOADS) * RPL * BK);
   };
 
   // 32x32x16 operands: lane (h, r) holds row r of a 32-row block, k 8h..8h+7
@@ -449,41 +459,45 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const bf16_t* __restrict
   }
 }
 
-template <int QM, int QN, int NS, int EPI, typename TR, typename TC>
+template <int QM, int QN, int NS, bool NT, int EPI, typename TR, typename TC>
 int launch_tile_g(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st,
                          int splits, int group) {
   using G = tile::Geo<QM, QN, NS>;
-  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tile_kernel<QM, QN, NS, EPI, TR, TC>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tile_kernel<QM, QN, NS, NT, EPI, TR, TC>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES);
   if (attr != hipSuccess) return -1;
   const int tiles_m = (M + G::BM - 1) / G::BM, tiles_n = N / G::BN;
-  hipLaunchKernelGGL((gemm_tile_kernel<QM, QN, NS, EPI, TR, TC>), dim3(tiles_m * tiles_n * splits), dim3(tile::NT),
+  hipLaunchKernelGGL((gemm_tile_kernel<QM, QN, NS, NT, EPI, TR, TC>), dim3(tiles_m * tiles_n * splits), dim3(tile::NT),
                      G::LDS_BYTES, st, (const bf16_t*)A, (const bf16_t*)W, (const TR*)R, (TC*)C, M, N, K, tiles_n,
                      group, splits);
   return 0;
 }
 
-// Every instance the launcher reaches, X(QM, QN, NS, EPI, TR, TC), by the
+// Every instance the launcher reaches, X(QM, QN, NS, NT, EPI, TR, TC), by the
 // source file that compiles it. NS: ring slots that fit 160 KiB of LDS.
-#define PS_TILE_INSTANCES_256(X)                                                                                     \
-  X(4, 4, 2, 0, float, bf16_t) X(4, 4, 2, 0, float, float) X(4, 4, 2, 1, bf16_t, float) X(4, 4, 2, 1, float, bf16_t) \
-  X(4, 4, 2, 1, bf16_t, bf16_t) X(4, 4, 2, 1, float, float) X(4, 4, 2, 2, float, bf16_t) X(4, 4, 2, 2, float, float)
-#define PS_TILE_INSTANCES_ALL(X, QM, QN, NS)                                                              \
-  X(QM, QN, NS, 0, float, bf16_t) X(QM, QN, NS, 0, float, float) X(QM, QN, NS, 1, bf16_t, float)          \
-  X(QM, QN, NS, 1, float, bf16_t)
-#define PS_TILE_INSTANCES_WIDE(X)                                              \
-  PS_TILE_INSTANCES_ALL(X, 3, 4, 2) X(3, 4, 2, 2, float, bf16_t)               \
-  PS_TILE_INSTANCES_ALL(X, 2, 4, 3) X(2, 4, 3, 2, float, bf16_t)
-#define PS_TILE_INSTANCES_TALL(X)                                              \
-  PS_TILE_INSTANCES_ALL(X, 4, 2, 3) X(4, 2, 3, 2, float, bf16_t)               \
-  PS_TILE_INSTANCES_ALL(X, 3, 2, 3) X(3, 2, 3, 2, float, bf16_t)
-#define PS_TILE_INSTANCES_SMALL(X)                                             \
-  PS_TILE_INSTANCES_ALL(X, 2, 2, 4) X(2, 2, 4, 2, float, bf16_t)               \
-  PS_TILE_INSTANCES_ALL(X, 2, 1, 6) PS_TILE_INSTANCES_ALL(X, 1, 1, 5)
+#define PS_TILE_INSTANCES_NT(X, QM, QN, NS, NT)                                                               \
+  X(QM, QN, NS, NT, 0, float, bf16_t) X(QM, QN, NS, NT, 0, float, float) X(QM, QN, NS, NT, 1, bf16_t, float)  \
+  X(QM, QN, NS, NT, 1, float, bf16_t)
+#define PS_TILE_INSTANCES_ALL(X, QM, QN, NS) \
+  PS_TILE_INSTANCES_NT(X, QM, QN, NS, false) PS_TILE_INSTANCES_NT(X, QM, QN, NS, true)
+#define PS_TILE_INSTANCES_SWIGLU(X, QM, QN, NS) \
+  X(QM, QN, NS, false, 2, float, bf16_t) X(QM, QN, NS, true, 2, float, bf16_t)
+#define PS_TILE_INSTANCES_256(X)                                                   \
+  PS_TILE_INSTANCES_ALL(X, 4, 4, 2) PS_TILE_INSTANCES_SWIGLU(X, 4, 4, 2)           \
+  X(4, 4, 2, false, 1, bf16_t, bf16_t) X(4, 4, 2, false, 1, float, float) X(4, 4, 2, false, 2, float, float)
+#define PS_TILE_INSTANCES_WIDE(X)                                                  \
+  PS_TILE_INSTANCES_ALL(X, 3, 4, 2) PS_TILE_INSTANCES_SWIGLU(X, 3, 4, 2)           \
+  PS_TILE_INSTANCES_ALL(X, 2, 4, 3) PS_TILE_INSTANCES_SWIGLU(X, 2, 4, 3)
+#define PS_TILE_INSTANCES_TALL(X)                                                  \
+  PS_TILE_INSTANCES_ALL(X, 4, 2, 3) PS_TILE_INSTANCES_SWIGLU(X, 4, 2, 3)           \
+  PS_TILE_INSTANCES_ALL(X, 3, 2, 3) PS_TILE_INSTANCES_SWIGLU(X, 3, 2, 3)
+#define PS_TILE_INSTANCES_SMALL(X)                                                 \
+  PS_TILE_INSTANCES_ALL(X, 2, 2, 4) PS_TILE_INSTANCES_SWIGLU(X, 2, 2, 4)           \
+  PS_TILE_INSTANCES_ALL(X, 2, 1, 6) PS_TILE_INSTANCES_NT(X, 1, 1, 5, false)
 #define PS_TILE_INSTANCES(X) \
   PS_TILE_INSTANCES_256(X) PS_TILE_INSTANCES_WIDE(X) PS_TILE_INSTANCES_TALL(X) PS_TILE_INSTANCES_SMALL(X)
-#define PS_TILE_INSTANTIATE(QM, QN, NS, EPI, TR, TC)                                                        \
-  template int launch_tile_g<QM, QN, NS, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
-                                                      void*, hipStream_t, int, int);
+#define PS_TILE_INSTANTIATE(QM, QN, NS, NT, EPI, TR, TC)                                                        \
+  template int launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
+                                                          void*, hipStream_t, int, int);
 
 }  // namespace ps

@@ -476,9 +476,9 @@ constexpr bool kTileAllShapes = (EPI == 0 && std::is_same<TR, float>::value) ||
                                 (EPI == 1 && !std::is_same<TR, TC>::value) ||
                                 (EPI == 2 && std::is_same<TC, bf16_t>::value);
 
-#define PS_TILE_EXTERN(QM, QN, NS, EPI, TR, TC)                                                                     \
-  extern template int launch_tile_g<QM, QN, NS, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
-                                                             void*, hipStream_t, int, int);
+#define PS_TILE_EXTERN(QM, QN, NS, NT, EPI, TR, TC)                                                                     \
+  extern template int launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
+                                                                 void*, hipStream_t, int, int);
 PS_TILE_INSTANCES(PS_TILE_EXTERN)
 #undef PS_TILE_EXTERN
 
@@ -487,22 +487,35 @@ static int launch_tile(int M, int N, int K, TilePlan pl, const void* A, const vo
                        hipStream_t st) {
   if (!kTileAllShapes<EPI, TR, TC>) pl.cfg = 0;
   const int group = tile_group(M, N, kTileCfgs[pl.cfg].qm);
-#define PS_TILE_GO(QM, QN, NS) launch_tile_g<QM, QN, NS, EPI, TR, TC>(M, N, K, A, W, R, C, st, pl.s, group)
+  // One tile row: weight loads with the non-temporal hint (see the kernel).
+  // Two rows of 192x256 or 256x256 tiles gain too (us, N 57344, K 8192: 300
+  // rows 358 -> 348, 512 rows 418 -> 401; N 28672, K 4096 at 389 102 -> 99).
+  // Otherwise workgroups that share weights drift apart where the last tile row
+  // is short, and the hint costs up to 20% (N 4096, K 14336 at 300 rows: 70, with
+  // it 88), and from four rows on it gives nothing or loses 1 to 7%.
+  const TileCfg& tc = kTileCfgs[pl.cfg];
+  const bool nt = M <= 64 * tc.qm * (tc.qm >= 3 && tc.qn == 4 ? 2 : 1);
+#define PS_TILE_GO(QM, QN, NS, NT) launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(M, N, K, A, W, R, C, st, pl.s, group)
+#define PS_TILE_GO_NT(QM, QN, NS) (nt ? PS_TILE_GO(QM, QN, NS, true) : PS_TILE_GO(QM, QN, NS, false))
   if constexpr (kTileAllShapes<EPI, TR, TC>) {
     switch (pl.cfg) {
-      case 1: return PS_TILE_GO(3, 4, 2);
-      case 2: return PS_TILE_GO(2, 4, 3);
-      case 3: return PS_TILE_GO(4, 2, 3);
-      case 4: return PS_TILE_GO(3, 2, 3);
-      case 5: return PS_TILE_GO(2, 2, 4);
+      case 0: return PS_TILE_GO_NT(4, 4, 2);
+      case 1: return PS_TILE_GO_NT(3, 4, 2);
+      case 2: return PS_TILE_GO_NT(2, 4, 3);
+      case 3: return PS_TILE_GO_NT(4, 2, 3);
+      case 4: return PS_TILE_GO_NT(3, 2, 3);
+      case 5: return PS_TILE_GO_NT(2, 2, 4);
       default: break;
     }
     if constexpr (EPI != 2) {
-      if (pl.cfg == 6) return PS_TILE_GO(2, 1, 6);
-      if (pl.cfg == 7) return PS_TILE_GO(1, 1, 5);
+      if (pl.cfg == 6) return PS_TILE_GO_NT(2, 1, 6);
+      if (pl.cfg == 7) return PS_TILE_GO(1, 1, 5, false);  // M > 64: two tile rows at least
     }
+    return -1;
+  } else {
+    return PS_TILE_GO(4, 4, 2, false);
   }
-  return PS_TILE_GO(4, 4, 2);
+#undef PS_TILE_GO_NT
 #undef PS_TILE_GO
 }
 

@@ -124,11 +124,13 @@ def test_gemm_swiglu(M, F, K):
 # row counts and widths that each take another workgroup tile: 256x256, 192x256, 128x256, 192x128, 128x128, 128x64,
 # 64x64 (128x128 with SwiGLU for the last two) and, from 17 stages, 256x128, with a partial last tile row in each
 TILE_SHAPES = [(389, 28672), (257, 28672), (577, 12288), (257, 12288), (257, 6144), (129, 6144), (65, 256)]
+# the shapes that one tile row can take (weights read non-temporally), widest first
+ONE_ROW_SHAPES = [(200, 49152), (150, 49152), (97, 49152), (200, 20480), (150, 20480), (97, 20480), (97, 10240)]
 
 
 # 64-k stages: fewer than the LDS ring holds, as many, one more, and the lengths around the end of its unrolled loop
 @pytest.mark.parametrize("M,N,stages", [(m, n, t) for m, n in TILE_SHAPES for t in (1, 2, 3, 4, 5, 6, 7, 9, 11, 12, 13)] +
-                         [(200, 28672, t) for t in (18, 19, 20)])
+                         [(200, 28672, t) for t in (18, 19, 20)] + [(m, n, t) for m, n in ONE_ROW_SHAPES for t in (2, 7, 13)])
 def test_gemm_every_tile_shape_and_ring_remainder(M, N, stages):
     K = 64 * stages
     g = torch.Generator(device="cuda").manual_seed(M * 1000 + stages)
