@@ -580,7 +580,7 @@ DecodePlan plan_decode(const std::vector<SeqInfo>& si, size_t first, int32_t spl
       it.b = (int32_t)(b - first);
       it.page_begin = (int32_t)((long)k * np / ns);
       it.page_end = (int32_t)((long)(k + 1) * np / ns);
-      it.part = p.n_parts + k;
+      it.part = ns == 1 ? -1 : p.n_parts + k;
       p.items.push_back(it);
     }
     p.n_parts += ns;
@@ -1228,6 +1228,14 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   // to 2048 401 -> 412).
   const bool rope_in_attn = P.dec_mfma && P.n_chunk == 0 && (long)P.n_ditems * c.n_kv_heads <= 2L * compute_units();
   DecodeRope rope;
+  // fp32: the norms ride in the GEMMs that read them where their arrangement is
+  // the small one, and a pure decode step's RoPE and KV write in its attention.
+  // Such steps are bound by the number of their launches: the tiny layer's
+  // prefill of 4 x 128 and 16 decode steps of 8 launches took 552 us, with 5
+  // launches per step (6 in the prefill) 473.
+  const bool norm_qkv = dt == PS_F32 && gemm_f32_norm_ok(PS_EPI_STORE, rows, dq + 2 * dkv, d);
+  const bool norm_ffn = dt == PS_F32 && gemm_f32_norm_ok(PS_EPI_SWIGLU, rows, 2 * c.ffn, d);
+  const bool f32_rope = dt == PS_F32 && P.n_chunk == 0;
   int bad = 0;
 
   // O projection + residual -> h (fp32), then the FFN RMSNorm -> xn, over
@@ -1256,6 +1264,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
     } else {
       bad |= launch_gemm(dt, dt, PS_F32, PS_EPI_RESIDUAL, n, d, dq, a, w->w_o, res, hr, ws, ws_bytes, s);
     }
+    if (norm_ffn) return;
     if (S > 1)
       bad |= launch_split_residual_rmsnorm(n, d, S, (const float*)ws, res, hr, w->ffn_norm, c.rms_eps, y, s, own_cu);
     else if (own_cu)
@@ -1302,17 +1311,23 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
                                 (const DecodeItem*)(W + P.o_di), (float*)(W + wl.apart_o), (float*)(W + wl.apart_ml),
                                 (const int32_t*)(W + P.o_pb), (const int32_t*)(W + P.o_pc), od, scale_log2, s,
                                 max_wg, rope_in_attn ? &rope : nullptr);
+    } else if (f32_rope) {
+      bad |= launch_attn_generic_rope(rows, c.n_q_heads, c.n_kv_heads, c.head_dim, (const float*)qkv, pool, si, bt,
+                                      (const double*)(W + P.o_fr), (float*)o, scale, s);
     } else {
       bad |= launch_attn_generic(dt, P.chunk_rows, P.n_dec, P.n_seqs, c.n_q_heads, c.n_kv_heads, c.head_dim, qr,
                                  pool, si, bt, o, scale, s);
     }
   };
 
-  bad |= launch_rmsnorm(dt, dt, dt, rows, d, x_in, w->attn_norm, c.rms_eps, xn, st, up);
+  if (!norm_qkv) bad |= launch_rmsnorm(dt, dt, dt, rows, d, x_in, w->attn_norm, c.rms_eps, xn, st, up);
   // decode-sized QKV: RoPE + KV write sums the split-K partials itself
   // (bf16, head_dim a multiple of 8: the fused reader's vector width)
   int s_qkv = 1;
-  if (dt == PS_BF16 && c.head_dim % 8 == 0)
+  if (norm_qkv)
+    bad |= launch_gemm_f32_norm(PS_EPI_STORE, rows, dq + 2 * dkv, d, (const float*)x_in, (const float*)w->attn_norm,
+                                c.rms_eps, (const float*)w->w_qkv, (float*)qkv, st, up);
+  else if (dt == PS_BF16 && c.head_dim % 8 == 0)
     bad |= launch_gemm_split(dt, 0, dt, PS_EPI_STORE, rows, dq + 2 * dkv, d, xn, w->w_qkv, nullptr, qkv, gws,
                              gws_bytes, st, &s_qkv);
   else
@@ -1323,7 +1338,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
     rope.splits = s_qkv;
     rope.mn = (long)rows * (dq + 2 * dkv);
     rope.inv_freq = (const double*)(W + P.o_fr);
-  } else {
+  } else if (!f32_rope) {
     bad |= launch_rope_kvwrite(dt, rows, qkv, qr, pool, si, bt, (const double*)(W + P.o_fr), P.n_seqs, c.n_q_heads,
                                c.n_kv_heads, c.head_dim, st, (const float*)gws, s_qkv);
   }
@@ -1339,8 +1354,12 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
     if (P.n_chunk > 0) prefill_attn(st);
     if (P.n_dec > 0) decode_attn(st, 0);
     o_proj(0, rows, gws, gws_bytes, st);
-    bad |= launch_gemm(dt, 0, dt, PS_EPI_SWIGLU, rows, 2 * c.ffn, d, xn, w->w_gate_up, nullptr, m, gws, gws_bytes,
-                       st);
+    if (norm_ffn)
+      bad |= launch_gemm_f32_norm(PS_EPI_SWIGLU, rows, 2 * c.ffn, d, (const float*)h, (const float*)w->ffn_norm,
+                                  c.rms_eps, (const float*)w->w_gate_up, (float*)m, st);
+    else
+      bad |= launch_gemm(dt, 0, dt, PS_EPI_SWIGLU, rows, 2 * c.ffn, d, xn, w->w_gate_up, nullptr, m, gws, gws_bytes,
+                         st);
     down_proj(0, rows, gws, gws_bytes, st);
     return bad;
   }

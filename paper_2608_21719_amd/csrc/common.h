@@ -69,7 +69,8 @@ struct SeqInfo {
 };
 
 // One split of decode attention: logical pages [page_begin, page_end) of
-// batch entry b; part is the index of its partial result.
+// batch entry b; part is the index of its partial result, -1 where the range is
+// the whole sequence (finished by the attention kernel).
 struct DecodeItem {
   int32_t b;
   int32_t page_begin;

@@ -242,19 +242,33 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 // SwiGLU: a wave's column block c comes with the matching up block (32 rows
 // of W further on), so gate and up of one output sit in one lane.
 // VEC: A rows can be read 16 bytes at a time (K a multiple of 4).
+// NORM: A is the RMSNorm of the rows given, x / sqrt(mean x^2 + eps) * g. The
+// gain goes onto the operands, the rows' sums of squares come from the same
+// registers, and the root scales the finished sums, so the norm costs no load
+// and no wait of its own; its launch (2.5 us on the stream and 2.3 on the host)
+// goes. The leading workgroups then carry a call's metadata upload.
 namespace f32g {
 constexpr int NT = 256;
 }
-template <int RB, int CB, bool KSPLIT, bool VEC, int EPI, typename TR, typename TC>
+template <int RB, int CB, bool KSPLIT, bool VEC, bool NORM, int EPI, typename TR, typename TC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        const TR* __restrict__ R, TC* __restrict__ C, int M, int N,
-                                                       int K) {
+                                                       int K, const float* __restrict__ gain, float eps, UploadJob up) {
+  static_assert(!NORM || (KSPLIT && VEC), "the fused norm is for the small arrangements");
+  int bx = blockIdx.x;
+  if constexpr (NORM) {
+    bx -= up.blocks;
+    if (bx < 0) {
+      if (blockIdx.y == 0) upload_block(up, blockIdx.x);
+      return;
+    }
+  }
   constexpr int WB = EPI == 2 ? 2 * CB : CB;  // W blocks per wave
   constexpr int MW = KSPLIT ? 1 : 2;          // waves along each side of the workgroup tile
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int h = lane >> 4, r16 = lane & 15;
   const int m0 = (blockIdx.y * MW + (KSPLIT ? 0 : wave >> 1)) * 16 * RB;
-  const int c0 = (blockIdx.x * MW + (KSPLIT ? 0 : wave & 1)) * 16 * CB;  // output column
+  const int c0 = (bx * MW + (KSPLIT ? 0 : wave & 1)) * 16 * CB;  // output column
   const int kt = (K + kWTile - 1) / kWTile;
   const int t0 = KSPLIT ? wave * kt / 4 : 0, t1 = KSPLIT ? (wave + 1) * kt / 4 : kt;
   // W row of block b at this lane's r16 (rows past N read row 0 of the tile
@@ -282,7 +296,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int b = 0; b < WB; ++b) acc[i][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   struct Tile {
-    float4 a[4][RB], w[4][WB];
+    float4 a[4][RB], w[4][WB], g[NORM ? 4 : 1];
   };
   // the four 16-k steps of 64-k tile t; A past K is zero (W is padded)
   auto load = [&](int t, Tile& x) __attribute__((always_inline)) {
@@ -291,6 +305,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       const int k = t * kWTile + 16 * s;
 #pragma unroll
       for (int b = 0; b < WB; ++b) x.w[s][b] = *(const float4*)(wp[b] + (long)t * kWTileElts + 16 * s);
+      if constexpr (NORM) x.g[s] = k + 4 * h < K ? *(const float4*)(gain + k + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int i = 0; i < RB; ++i) {
         const int ke = k + 4 * h;
@@ -303,9 +318,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       }
     }
   };
-  auto mul = [&](const Tile& x) __attribute__((always_inline)) {
+  float ss[RB];  // NORM: this lane's share of its rows' sums of squares
+#pragma unroll
+  for (int i = 0; i < RB; ++i) ss[i] = 0.f;
+  auto mul = [&](Tile& x) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
+      if constexpr (NORM) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+          float4& v = x.a[s][i];
+          ss[i] = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss[i]))));
+          v = make_float4(v.x * x.g[s].x, v.y * x.g[s].y, v.z * x.g[s].z, v.w * x.g[s].w);
+        }
+      }
       auto step = [&](auto pick) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < RB; ++i)
@@ -347,6 +373,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int b = 0; b < WB; ++b) part[wave][i * WB + b][lane] = acc[i][b];
+    __shared__ float s_ss[4][NORM ? 16 * RB : 1];
+    if constexpr (NORM) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        ss[i] += __shfl_xor(ss[i], 16);
+        ss[i] += __shfl_xor(ss[i], 32);
+        if (h == 0) s_ss[wave][16 * i + r16] = ss[i];
+      }
+    }
     __syncthreads();
     // wave w finishes output block w, w + 4, ...
     constexpr int PB = EPI == 2 ? 2 : 1;
@@ -358,7 +393,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
         for (int w = 1; w < 4; ++w) sum[p] += part[w][o * PB + p][lane];
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) store(o / CB, o % CB, e, sum[0][e], sum[PB - 1][e]);
+      for (int e = 0; e < 4; ++e) {
+        float inv = 1.f;
+        if constexpr (NORM) {
+          const int r = 16 * (o / CB) + 4 * h + e;
+          inv = 1.0f / sqrtf(((s_ss[0][r] + s_ss[1][r]) + (s_ss[2][r] + s_ss[3][r])) / (float)K + eps);
+        }
+        store(o / CB, o % CB, e, sum[0][e] * inv, sum[PB - 1][e] * inv);
+      }
     }
   } else {
 #pragma unroll
@@ -657,31 +699,65 @@ static int launch_skinny(int M, int N, int K, const void* A, const void* W, floa
   return launch_skinny_plan<EPI, TR, TC>(M, N, K, gemm_skinny_plan(M, N, K), A, W, part, R, C, st);
 }
 
+// `norm`: the input rows are normalised in the kernel (gemm_f32_norm_ok)
+struct F32Norm {
+  const float* gain;
+  float eps;
+  UploadJob up;
+};
 template <int RB, int CB, bool KSPLIT, int EPI, typename TR, typename TC>
-static int launch_f32_shape(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st) {
+static int launch_f32_shape(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st,
+                            const F32Norm* norm = nullptr) {
   constexpr int MW = KSPLIT ? 1 : 2;
   const int cols = EPI == 2 ? N / 2 : N;
   dim3 grid((cols + 16 * CB * MW - 1) / (16 * CB * MW), (M + 16 * RB * MW - 1) / (16 * RB * MW));
-  auto go = [&](auto vec) {
-    hipLaunchKernelGGL((gemm_f32_kernel<RB, CB, KSPLIT, decltype(vec)::value, EPI, TR, TC>), grid, dim3(f32g::NT), 0, st,
-                       (const float*)A, (const float*)W, (const TR*)R, (TC*)C, M, N, K);
+  auto go = [&](auto vec, auto nc) {
+    const F32Norm n = norm ? *norm : F32Norm{nullptr, 0.f, UploadJob{}};
+    grid.x += n.up.blocks;
+    hipLaunchKernelGGL((gemm_f32_kernel<RB, CB, KSPLIT, decltype(vec)::value, decltype(nc)::value, EPI, TR, TC>), grid,
+                       dim3(f32g::NT), 0, st, (const float*)A, (const float*)W, (const TR*)R, (TC*)C, M, N, K, n.gain,
+                       n.eps, n.up);
   };
-  if (K % 4 == 0) go(std::true_type{});
-  else go(std::false_type{});
+  if constexpr (KSPLIT && EPI != 1) {
+    if (norm) {
+      go(std::true_type{}, std::true_type{});
+      return 0;
+    }
+  }
+  if (norm) return -1;
+  if (K % 4 == 0) go(std::true_type{}, std::false_type{});
+  else go(std::false_type{}, std::false_type{});
   return 0;
 }
 
+// 128 x 128 tiles (64 x 64 per wave) where they reach half the compute units
+// (1024 x 1024 x 1024 in 32 x 32 tiles: 40 us against 64 tiles of 128 x 128 that
+// leave three quarters idle); else K split over the waves.
+static bool f32_large(int epi, int M, int N) {
+  const int cols = epi == 2 ? N / 2 : N;
+  const long tiles = (long)((M + 127) / 128) * ((cols + (epi == 2 ? 63 : 127)) / (epi == 2 ? 64 : 128));
+  return tiles >= compute_units() / 2;
+}
+
 template <int EPI, typename TR, typename TC>
-static int launch_f32(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st) {
-  // 128 x 128 tiles (64 x 64 per wave) where they reach half the compute
-  // units (1024 x 1024 x 1024 in 32 x 32 tiles: 40 us against 64 tiles of
-  // 128 x 128 that leave three quarters idle); else K split over the waves,
-  // 16 rows at a time for decode-sized M.
-  const int cols = EPI == 2 ? N / 2 : N;
-  const long tiles = (long)((M + 127) / 128) * ((cols + (EPI == 2 ? 63 : 127)) / (EPI == 2 ? 64 : 128));
-  if (tiles >= compute_units() / 2) return launch_f32_shape<4, EPI == 2 ? 2 : 4, false, EPI, TR, TC>(M, N, K, A, W, R, C, st);
-  if (M <= 16) return launch_f32_shape<1, 1, true, EPI, TR, TC>(M, N, K, A, W, R, C, st);
-  return launch_f32_shape<2, EPI == 2 ? 1 : 2, true, EPI, TR, TC>(M, N, K, A, W, R, C, st);
+static int launch_f32(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st,
+                      const F32Norm* norm = nullptr) {
+  if (f32_large(EPI, M, N)) return launch_f32_shape<4, EPI == 2 ? 2 : 4, false, EPI, TR, TC>(M, N, K, A, W, R, C, st, norm);
+  // 16 rows at a time for decode-sized M
+  if (M <= 16) return launch_f32_shape<1, 1, true, EPI, TR, TC>(M, N, K, A, W, R, C, st, norm);
+  return launch_f32_shape<2, EPI == 2 ? 1 : 2, true, EPI, TR, TC>(M, N, K, A, W, R, C, st, norm);
+}
+
+bool gemm_f32_norm_ok(int epi, int M, int N, int K) {
+  return epi != 1 && M > 0 && K % 4 == 0 && (epi != 2 || N % 64 == 0) && !f32_large(epi, M, N);
+}
+
+int launch_gemm_f32_norm(int epi, int M, int N, int K, const float* x, const float* gain, float eps, const float* W,
+                         float* C, hipStream_t st, const UploadJob* up) {
+  if (!gemm_f32_norm_ok(epi, M, N, K)) return -1;
+  const F32Norm n{gain, eps, up ? *up : UploadJob{}};
+  if (epi == 0) return launch_f32<0, float, float>(M, N, K, x, W, nullptr, C, st, &n);
+  return launch_f32<2, float, float>(M, N, K, x, W, nullptr, C, st, &n);
 }
 
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K) {

@@ -59,6 +59,10 @@ int launch_decode_attn(int G, int n_items, int n_kv, int n_seqs, const void* q, 
 int launch_attn_generic(int dt, int row0, int rows, int n_seqs, int n_q, int n_kv, int hd, const void* q,
                         const void* pool_layer, const SeqInfo* si, const int32_t* bt, void* o, float scale,
                         hipStream_t st);
+// fp32 decode rows (row r is sequence r's one new token): RoPE, the KV write and
+// the attention in one launch, from the QKV projection.
+int launch_attn_generic_rope(int rows, int n_q, int n_kv, int hd, const float* qkv, void* pool_layer, const SeqInfo* si,
+                             const int32_t* bt, const double* inv_freq, float* o, float scale, hipStream_t st);
 int compute_units();  // of the current device (256 if the query fails)
 int fa_query_tile();  // query rows per prefill work item
 // Where the partial results of split query tiles go: part p's O (fp32,
@@ -87,6 +91,11 @@ int launch_fa_prefill(int G, int n_items, int n_kv, const void* q, const void* p
 int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
                 const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st);
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K);
+// fp32 C = epilogue(RMSNorm(x) W^T) (store or SwiGLU) in one launch, where
+// gemm_f32_norm_ok; its leading workgroups carry `up`.
+bool gemm_f32_norm_ok(int epi, int M, int N, int K);
+int launch_gemm_f32_norm(int epi, int M, int N, int K, const float* x, const float* gain, float eps, const float* W,
+                         float* C, hipStream_t st, const UploadJob* up = nullptr);
 int launch_gemm_split(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
                       const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, int* splits);
 struct SkinnyPlan {

@@ -9,7 +9,7 @@ import pytest
 
 from oracle import layer as O
 from synth import gen
-from synth.configs import CONFIGS
+from synth.configs import CONFIGS, LayerShape, Workload
 from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
@@ -490,3 +490,27 @@ def test_decode_step_rope_in_attention_equals_composed_ops_bit_for_bit(n_q, n_kv
     for a, b in zip(kvs[:n], kvs[n:]):
         for u, w in zip(a, b):
             np.testing.assert_array_equal(H.bits(u), H.bits(w))
+
+
+# hidden, query heads, kv heads, head dim, sequences: K tails and one-tile K of the fused norm, a hidden size it does not
+# take (not a multiple of 4), odd group and head sizes, more than 16 rows, and a batch wide enough for four waves per head
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,batch", [(256, 4, 2, 64, 4), (100, 3, 1, 6, 1), (70, 2, 2, 128, 3),
+                                                      (60, 8, 8, 10, 17), (516, 16, 4, 20, 18)])
+def test_fp32_decode_from_empty_and_long_contexts(hidden, n_q, n_kv, hd, batch):
+    """Fused RMSNorm + GEMM and RoPE + KV write + attention: first tokens, page and 64-key edges, against the oracle."""
+    shape = LayerShape(hidden, n_q, n_kv, hd, 96, 1e-5, 10000.0, "f32")
+    h = Harness(Workload("f32_edges", 11, shape), n_pages=512, max_seqs=batch, max_pages=20, max_rows=2048)
+    lens = [(0, 15, 62, 300, 1, 127)[i % 6] for i in range(batch)]
+    seqs = [h.open(L + 3) for L in lens]
+    with_past = [(s, L) for s, L in zip(seqs, lens) if L]
+    if with_past:
+        x = gen.prefill_input(h.wl, sum(L for _, L in with_past))
+        got, xf, r0 = h.prefill([s for s, _ in with_past], [L for _, L in with_past], x), gen.widen(x, "f32"), 0
+        for s, L in with_past:
+            check(got[r0:r0 + L], h.oracle(s, xf[r0:r0 + L]), "f32", f"prefill of {L}")
+            r0 += L
+    for step in range(3):
+        xd = gen.decode_input(h.wl, batch, step)
+        got, xdf = h.decode(seqs, xd), gen.widen(xd, "f32")
+        ref = np.concatenate([h.oracle(s, xdf[i:i + 1]) for i, s in enumerate(seqs)])
+        check(got, ref, "f32", f"decode step {step}")
