@@ -24,7 +24,7 @@ namespace ps {
 
 // ==================================================================== skinny
 // Decode-sized M (<= 64): the weight stream is the whole cost (AI = M
-// FLOP/byte). A workgroup owns 64 WN weight rows (output columns) and a K
+// FLOP/byte). A workgroup owns 64 WN weight rows (output columns, WN 1, 2 or 4) and a K
 // range; its four waves own 16 WN rows each. Stages of 64 k hold the
 // activation tile [16 MB rows][64] and the weight tile [64 WN rows][64];
 // both are filled by global->LDS DMA into an NS-deep ring, so the bytes in
@@ -38,10 +38,11 @@ namespace ps {
 namespace skinny {
 constexpr int NT = 256;
 constexpr int KS = 64;    // k per stage
-constexpr int NS = 4;     // ring depth
 constexpr int MAXM = 64;
+template <int WN>
+constexpr int ring() { return WN == 4 ? 3 : 4; }  // stages; three of the widest are as many bytes in flight as six of 128 rows
 template <int MB, int WN>
-constexpr size_t lds_bytes() { return (size_t)NS * (16 * MB + 64 * WN) * KS * 2; }
+constexpr size_t lds_bytes() { return (size_t)ring<WN>() * (16 * MB + 64 * WN) * KS * 2; }
 }  // namespace skinny
 
 template <int MB, int WN, int EPI, typename TR, typename TC, bool DIRECT>
@@ -49,7 +50,8 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(const bf16_t* __restri
                                                           float* __restrict__ part, const TR* __restrict__ R,
                                                           TC* __restrict__ C, int M, int N, int K, int S) {
   using namespace skinny;
-  static_assert(!(DIRECT && EPI == 2) || WN == 2, "in-kernel SwiGLU pairs a gate and an up block per wave");
+  static_assert(!(DIRECT && EPI == 2) || WN >= 2, "in-kernel SwiGLU pairs gate and up blocks per wave");
+  constexpr int NS = ring<WN>();
   static_assert(KS == kWTile, "one W tile per stage");
   constexpr int AROWS = 16 * MB, WROWS = 64 * WN;
   constexpr int STAGE = (AROWS + WROWS) * KS;  // bf16 elements
@@ -103,8 +105,9 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(const bf16_t* __restri
     else wait_vmcnt_lgkm0<(NS - 2) * WI>();
   };
   auto swz = [](int row, int ch) { return row * KS + ((ch ^ (row & 7)) << 3); };
-  // weight rows of n-block nb for this wave; for SwiGLU (WN 2) block 0 is a
-  // gate block and block 1 the matching up block of the 32-row interleave
+  // weight rows of n-block nb for this wave; for SwiGLU with WN 2 block 0 is a
+  // gate block and block 1 the matching up block of the 32-row interleave, with
+  // WN 4 a wave's blocks 0, 1 are gate and 2, 3 up as they lie
   auto wrow = [&](int nb) {
     if constexpr (EPI == 2 && WN == 2) {
       const int q = wave >> 1, h = wave & 1;
@@ -163,9 +166,11 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(const bf16_t* __restri
         const int row = 16 * i + 4 * g + r;
         if (row >= M) continue;
         if constexpr (EPI == 2) {
-          const int q = wave >> 1, h = wave & 1;
-          const int col = n0 / 2 + 32 * q + 16 * h + c;
-          st_elt<TC>(C, (long)row * (N / 2) + col, silu_fast(acc[0][i][r]) * acc[1][i][r]);
+#pragma unroll
+          for (int nb = 0; nb < WN / 2; ++nb) {
+            const int col = n0 / 2 + (WN == 4 ? 32 * wave + 16 * nb : 16 * wave) + c;
+            st_elt<TC>(C, (long)row * (N / 2) + col, silu_fast(acc[nb][i][r]) * acc[nb + WN / 2][i][r]);
+          }
         } else {
 #pragma unroll
           for (int nb = 0; nb < WN; ++nb) {
@@ -642,8 +647,15 @@ static int skinny_splits_for(int tiles, int K, int target) {
   return S;
 }
 
+//
+// Four blocks per workgroup (S 1) where two would take more than one round of
+// the compute units: at least 160 workgroups that fit seven eighths of them (us,
+// two -> four blocks: N 57344, K 8192 at 1 row 134.7 -> 130.9, at 64 147 -> 133;
+// N 40960, K 8192 at 8 rows 116 -> 99; N 49152, K 4096 at 64 72 -> 62), and above
+// that from 33 rows on, where halving the activation reads pays (N 128256, K
+// 4096 at 64 rows 196 -> 176; but at 8 rows 157 -> 163, N 65536, K 8192 155 -> 158).
 SkinnyPlan gemm_skinny_plan(int M, int N, int K) {
-  (void)M;
+  if (N % 256 == 0 && N / 128 > 256 && N / 256 >= 160 && (N / 256 <= 224 || M > 32)) return {4, 1};
   if (N % 128 == 0) {
     const int S = skinny_splits_for(N / 128, K, 256);
     if ((N / 128) * S >= 160) return {2, S};
@@ -676,6 +688,7 @@ static int launch_skinny_wn(int M, int N, int K, int S, const void* A, const voi
 template <int MB, int EPI, typename TR, typename TC>
 static int launch_skinny_mb(int M, int N, int K, SkinnyPlan pl, const void* A, const void* W, float* part,
                             const void* R, void* C, hipStream_t st) {
+  if (pl.wn == 4) return launch_skinny_k<MB, 4, EPI, TR, TC, true>(M, N, K, 1, A, W, part, R, C, st);
   if (pl.wn == 2) return launch_skinny_wn<MB, 2, EPI, TR, TC>(M, N, K, pl.s, A, W, part, R, C, st);
   return launch_skinny_wn<MB, 1, EPI, TR, TC>(M, N, K, pl.s, A, W, part, R, C, st);
 }
@@ -683,7 +696,7 @@ static int launch_skinny_mb(int M, int N, int K, SkinnyPlan pl, const void* A, c
 template <int EPI, typename TR, typename TC>
 static int launch_skinny_plan(int M, int N, int K, SkinnyPlan pl, const void* A, const void* W, float* part,
                               const void* R, void* C, hipStream_t st) {
-  if ((pl.wn != 1 && pl.wn != 2) || N % (64 * pl.wn) != 0 || pl.s < 1 || K / skinny::KS < pl.s) return -1;
+  if ((pl.wn != 1 && pl.wn != 2 && (pl.wn != 4 || pl.s != 1)) || N % (64 * pl.wn) != 0 || pl.s < 1 || K / skinny::KS < pl.s) return -1;
   switch ((M + 15) / 16) {
     case 1: return launch_skinny_mb<1, EPI, TR, TC>(M, N, K, pl, A, W, part, R, C, st);
     case 2: return launch_skinny_mb<2, EPI, TR, TC>(M, N, K, pl, A, W, part, R, C, st);
@@ -856,7 +869,7 @@ int launch_gemm_split(int dtype, int r_dt, int c_dt, int epi, int M, int N, int 
 size_t gemm_partials_bytes(int dtype, int epi, int M, int N, int K) {
   if (dtype != 1 || M <= 0 || M > skinny::MAXM || N % 64 != 0 || K % 64 != 0) return 0;
   const SkinnyPlan pl = gemm_skinny_plan(M, N, K);
-  if (pl.s == 1 && (epi != 2 || pl.wn == 2)) return 0;
+  if (pl.s == 1 && (epi != 2 || pl.wn >= 2)) return 0;
   return (size_t)pl.s * M * N * sizeof(float);
 }
 

@@ -99,7 +99,7 @@ int launch_gemm_f32_norm(int epi, int M, int N, int K, const float* x, const flo
 int launch_gemm_split(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
                       const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, int* splits);
 struct SkinnyPlan {
-  int wn;  // 64-row weight blocks per workgroup (1 or 2)
+  int wn;  // 64-row weight blocks per workgroup (1, 2 or 4)
   int s;   // K splits
 };
 SkinnyPlan gemm_skinny_plan(int M, int N, int K);

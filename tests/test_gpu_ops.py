@@ -121,6 +121,31 @@ def test_gemm_swiglu(M, F, K):
     H.assert_close_elementwise(H.to_f64(C), ref, 1e-3, 2 ** -7, "swiglu")
 
 
+# four weight blocks per workgroup: 160 workgroups at any row count, 257 from 33 rows on; one stage to several rings
+@pytest.mark.parametrize("M,N,K", [(1, 40960, 64), (16, 40960, 192), (17, 40960, 128), (33, 65792, 256), (64, 65792, 448)])
+def test_gemm_skinny_four_blocks(M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+    wt = torch.empty(N * K, dtype=torch.bfloat16, device="cuda")
+    B.op_tile_weight(B.PS_BF16, N, K, w, wt)
+    ref = a.double() @ w.double().T
+    absb = (a.double().abs() @ w.double().abs().T) * (2 * K * 2.0 ** -24)  # fp32 accumulation, as gemm_bound
+    ws = H.workspace(B.op_gemm_workspace_bytes(B.PS_BF16, M, N, K))
+    c32 = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    B.op_gemm(B.PS_BF16, 0, B.PS_F32, B.PS_EPI_STORE, M, N, K, a, wt, None, c32, ws)
+    assert bool(((c32.double() - ref).abs() <= absb).all()), "store fp32"
+    r32 = torch.randn((M, N), generator=g, device="cuda")
+    c16 = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    B.op_gemm(B.PS_BF16, B.PS_F32, B.PS_BF16, B.PS_EPI_RESIDUAL, M, N, K, a, wt, r32, c16, ws)
+    assert torch.equal(c16.view(torch.int16), (c32 + r32).to(torch.bfloat16).view(torch.int16)), "residual"
+    m = torch.empty((M, N // 2), dtype=torch.bfloat16, device="cuda")
+    B.op_gemm(B.PS_BF16, 0, B.PS_BF16, B.PS_EPI_SWIGLU, M, N, K, a, wt, None, m, ws)
+    gu = ref.view(M, N // 64, 2, 32)
+    want = (torch.nn.functional.silu(gu[:, :, 0]) * gu[:, :, 1]).reshape(M, N // 2)
+    assert bool(((m.double() - want).abs() <= 1e-3 + 2 ** -7 * want.abs()).all()), "swiglu"
+
+
 # row counts and widths that each take another workgroup tile: 256x256, 192x256, 128x256, 192x128, 128x128, 128x64,
 # 64x64 (128x128 with SwiGLU for the last two) and, from 17 stages, 256x128, with a partial last tile row in each
 TILE_SHAPES = [(389, 28672), (257, 28672), (577, 12288), (257, 12288), (257, 6144), (129, 6144), (65, 256)]
