@@ -304,7 +304,14 @@ __global__ __launch_bounds__(256) void rope_kvwrite_kernel(const T* __restrict__
                                                            long mn) {
   constexpr bool PART = SS > 0;  // SS split-K partials, a compile-time count
   static_assert(!PART || std::is_same<T, bf16_t>::value, "split partials feed the bf16 path");
-  const int row = blockIdx.x;
+  // Consecutive workgroup ids go round-robin over the 8 XCDs: each XCD takes a
+  // contiguous range of rows, so that the rows that fill a page meet in one L2.
+  // Their V^T entries are 2 bytes each, 32 apart, and share every sector.
+  int row = blockIdx.x;
+  if constexpr (!PART) {
+    const int x = row & 7, per = gridDim.x >> 3, rem = gridDim.x & 7;
+    row = x * per + min(x, rem) + (row >> 3);
+  }
   const int half = hd >> 1;
   __shared__ float cs[64], sn[64];
   __shared__ int s_b;
