@@ -486,6 +486,14 @@ ps_status plan_seqs(const ps_kv* kv, int n, const int32_t* seqs, const int32_t* 
   return PS_OK;
 }
 
+// Whether the call's chunks start on page and 16-row boundaries (single rows
+// aside): its groups of 16 rows then fill a page each.
+bool fills_pages(const std::vector<SeqInfo>& si) {
+  for (const SeqInfo& s : si)
+    if (s.n_new >= PS_PAGE_TOKENS && (s.kv_before % PS_PAGE_TOKENS || s.row_start % PS_PAGE_TOKENS)) return false;
+  return true;
+}
+
 struct DecodePlan {
   std::vector<DecodeItem> items;
   std::vector<int32_t> part_begin, part_count;
@@ -1067,7 +1075,7 @@ namespace {
 // every layer.
 struct LayerPlan {
   int32_t rows = 0, chunk_rows = 0, n_chunk = 0, n_dec = 0;
-  bool fa = false, dec_mfma = false;
+  bool fa = false, dec_mfma = false, full_pages = false;
   size_t o_si = 0, o_bt = 0, o_fr = 0, o_pi = 0, o_di = 0, o_pb = 0, o_pc = 0;
   int n_pitems = 0, n_ditems = 0;
   int n_merges = 0;  // > 0: the prefill items are split ones
@@ -1111,6 +1119,7 @@ ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int3
   P.n_chunk = n_chunk;
   P.n_dec = n_dec;
   P.n_seqs = (int32_t)cs.si.size();
+  P.full_pages = fills_pages(cs.si);
   const int d = c.hidden, dq = c.n_q_heads * c.head_dim, dkv = c.n_kv_heads * c.head_dim;
   // every GEMM of the call must be supported before anything is enqueued
   if (P.rows > 0 && (gemm_check(c.dtype, 0, P.rows, dq + 2 * dkv, d) || gemm_check(c.dtype, 1, P.rows, d, dq) ||
@@ -1340,7 +1349,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
     rope.inv_freq = (const double*)(W + P.o_fr);
   } else if (!f32_rope) {
     bad |= launch_rope_kvwrite(dt, rows, qkv, qr, pool, si, bt, (const double*)(W + P.o_fr), P.n_seqs, c.n_q_heads,
-                               c.n_kv_heads, c.head_dim, st, (const float*)gws, s_qkv);
+                               c.n_kv_heads, c.head_dim, P.full_pages, st, (const float*)gws, s_qkv);
   }
 
   // A mixed batch (prefill chunks + decode rows) that forks (mixed_forks: `aux`
@@ -1722,7 +1731,7 @@ extern "C" ps_status ps_op_rope_kvwrite(ps_kv* kv, int32_t layer, int32_t n_seqs
   const ps_layer_cfg& c = kv->cfg;
   launch_rope_kvwrite(c.dtype, cs.rows, qkv, q_out, kv->layer_base(layer), (const SeqInfo*)(W + o_si),
                       (const int32_t*)(W + o_bt), (const double*)(W + o_fr), n_seqs, c.n_q_heads, c.n_kv_heads,
-                      c.head_dim, st);
+                      c.head_dim, fills_pages(cs.si), st);
   return last_launch_error();
   PS_CATCH
 }

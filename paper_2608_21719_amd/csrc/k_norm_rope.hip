@@ -513,7 +513,7 @@ __global__ __launch_bounds__(1024) void rope_kvwrite_rows_kernel(const bf16_t* _
 }
 
 int launch_rope_kvwrite(int dt, int rows, const void* qkv, void* q_out, void* pool_layer, const SeqInfo* si,
-                        const int32_t* bt, const double* inv_freq, int n_seqs, int n_q, int n_kv, int hd,
+                        const int32_t* bt, const double* inv_freq, int n_seqs, int n_q, int n_kv, int hd, bool full_pages,
                         hipStream_t st, const float* part, int splits) {
   if (rows == 0) return 0;
   if (hd > 128) return -1;
@@ -534,11 +534,12 @@ int launch_rope_kvwrite(int dt, int rows, const void* qkv, void* q_out, void* po
     return -1;
   }
   const size_t v_lds = (size_t)kRopeRows * n_kv * hd * sizeof(bf16_t);
-  // 16 rows per workgroup only from 1537 rows: below that its workgroups
-  // leave compute units idle (8B shape, us, one row / 16 rows: 256 decode rows
-  // 6.8 / 18.0, one prompt of 389 7.4 / 10.2, 3 x 373 11.6 / 17.7, 4 x 512
-  // 16.1 / 12.2, 8 x 389 23.7 / 22.0)
-  if (dt == 1 && rows > 1536 && hd % 16 == 0 && v_lds <= 64 * 1024) {
+  // 16 rows per workgroup only where that fills the chip: from 1537 rows where
+  // the groups fill pages, else (2-byte V^T stores either way) from 3585 (us with
+  // the call's upload, one row / 16 rows, 8B shape: 4 x 512 15.7 / 14.8, 2 x 2048
+  // 23.9 / 21.4, 8 x 1024 52.9 / 40.4; 4 x 389 14.3 / 20.5, 8 x 389 20.4 / 24.1, 3
+  // x 1365 23.8 / 26.8; 70B: 3 x 700 21.4 / 25.8, 3 x 1365 40.6 / 40.3)
+  if (dt == 1 && rows > (full_pages ? 1536 : 3584) && hd % 16 == 0 && v_lds <= 64 * 1024) {
     static const hipError_t attr = hipFuncSetAttribute((const void*)rope_kvwrite_rows_kernel,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
     if (attr != hipSuccess) return -1;

@@ -22,9 +22,11 @@ int launch_rmsnorm(int x_dt, int g_dt, int y_dt, int rows, int d, const void* x,
 int launch_rmsnorm_own_cu(int rows, int d, const float* x, const void* g, float eps, void* y, hipStream_t st);
 
 // part/splits: when splits > 1 (bf16), the QKV rows are the sum of `splits`
-// fp32 split-K partials at part (see launch_gemm_split), qkv is not read
+// fp32 split-K partials at part (see launch_gemm_split), qkv is not read.
+// full_pages: the call's groups of 16 rows mostly fill a page each (chooses
+// the kernel only).
 int launch_rope_kvwrite(int dt, int rows, const void* qkv, void* q_out, void* pool_layer, const SeqInfo* si,
-                        const int32_t* bt, const double* inv_freq, int n_seqs, int n_q, int n_kv, int hd,
+                        const int32_t* bt, const double* inv_freq, int n_seqs, int n_q, int n_kv, int hd, bool full_pages,
                         hipStream_t st, const float* part = nullptr, int splits = 1);
 // own_cu as launch_rmsnorm_own_cu (S <= 4)
 int launch_split_residual_rmsnorm(int rows, int d, int S, const float* part, const void* res, float* h,
