@@ -1268,7 +1268,8 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
         }
         bad |= launch_gemm_tile_split(n, d, dq, S, a, w->w_o, (float*)ws, s);
       } else {
-        bad |= launch_gemm_split(dt, dt, PS_F32, PS_EPI_RESIDUAL, n, d, dq, a, w->w_o, res, hr, ws, ws_bytes, s, &S);
+        bad |= launch_gemm_split(dt, dt, PS_F32, PS_EPI_RESIDUAL, n, d, dq, a, w->w_o, res, hr, ws, ws_bytes, s, &S,
+                                 own_cu);
       }
     } else {
       bad |= launch_gemm(dt, dt, PS_F32, PS_EPI_RESIDUAL, n, d, dq, a, w->w_o, res, hr, ws, ws_bytes, s);
@@ -1282,7 +1283,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
       bad |= launch_rmsnorm(PS_F32, dt, dt, n, d, hr, w->ffn_norm, c.rms_eps, y, s);
   };
   // down projection + residual (h) -> x_out over `n` rows from row r0
-  auto down_proj = [&](int r0, int n, void* ws, size_t ws_bytes, hipStream_t s) {
+  auto down_proj = [&](int r0, int n, void* ws, size_t ws_bytes, hipStream_t s, bool beside = false) {
     if (n == 0) return;
     const char* a = m + (size_t)r0 * c.ffn * eb;
     const float* hr = (const float*)(h + (size_t)r0 * d * 4);
@@ -1296,7 +1297,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
       bad |= launch_gemm_tile_split(n, d, c.ffn, S, a, w->w_down, (float*)ws, s);
       bad |= launch_split_residual(PS_F32, dt, n, d, S, (const float*)ws, hr, y, s);
     } else {
-      bad |= launch_gemm(dt, PS_F32, dt, PS_EPI_RESIDUAL, n, d, c.ffn, a, w->w_down, hr, y, ws, ws_bytes, s);
+      bad |= launch_gemm(dt, PS_F32, dt, PS_EPI_RESIDUAL, n, d, c.ffn, a, w->w_down, hr, y, ws, ws_bytes, s, beside);
     }
   };
   auto prefill_attn = [&](hipStream_t s) {
@@ -1380,7 +1381,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   };
   auto swiglu = [&](int r0, int n, void* ws, size_t ws_bytes, hipStream_t s) {
     bad |= launch_gemm(dt, 0, dt, PS_EPI_SWIGLU, n, 2 * c.ffn, d, xn + (size_t)r0 * d * eb, w->w_gate_up, nullptr,
-                       m + (size_t)r0 * c.ffn * eb, ws, ws_bytes, s);
+                       m + (size_t)r0 * c.ffn * eb, ws, ws_bytes, s, true);
   };
   link(st, sb, 0);
   // the decode rows' attention on at most half as many workgroups as compute
@@ -1393,7 +1394,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   prefill_attn(st);
   o_proj(0, cr, gws, gws_bytes, st, true);
   swiglu(0, cr, gws, gws_bytes, st);
-  down_proj(0, cr, gws, gws_bytes, st);
+  down_proj(0, cr, gws, gws_bytes, st, true);
   link(sb, st, 1);  // joined: the call's work is on the caller's stream again
   return bad;
 }

@@ -459,14 +459,15 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(const bf16_t* __restrict
   }
 }
 
+// `cols` of the N output columns: W, R and C point at the first of them.
 template <int QM, int QN, int NS, bool NT, int EPI, typename TR, typename TC>
-int launch_tile_g(int M, int N, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st,
-                         int splits, int group) {
+int launch_tile_g(int M, int N, int cols, int K, const void* A, const void* W, const void* R, void* C, hipStream_t st,
+                  int splits, int group) {
   using G = tile::Geo<QM, QN, NS>;
   static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tile_kernel<QM, QN, NS, NT, EPI, TR, TC>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES);
   if (attr != hipSuccess) return -1;
-  const int tiles_m = (M + G::BM - 1) / G::BM, tiles_n = N / G::BN;
+  const int tiles_m = (M + G::BM - 1) / G::BM, tiles_n = cols / G::BN;
   hipLaunchKernelGGL((gemm_tile_kernel<QM, QN, NS, NT, EPI, TR, TC>), dim3(tiles_m * tiles_n * splits), dim3(tile::NT),
                      G::LDS_BYTES, st, (const bf16_t*)A, (const bf16_t*)W, (const TR*)R, (TC*)C, M, N, K, tiles_n,
                      group, splits);
@@ -497,7 +498,7 @@ int launch_tile_g(int M, int N, int K, const void* A, const void* W, const void*
 #define PS_TILE_INSTANCES(X) \
   PS_TILE_INSTANCES_256(X) PS_TILE_INSTANCES_WIDE(X) PS_TILE_INSTANCES_TALL(X) PS_TILE_INSTANCES_SMALL(X)
 #define PS_TILE_INSTANTIATE(QM, QN, NS, NT, EPI, TR, TC)                                                        \
-  template int launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
-                                                          void*, hipStream_t, int, int);
+  template int launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(int, int, int, int, const void*, const void*,         \
+                                                          const void*, void*, hipStream_t, int, int);
 
 }  // namespace ps

@@ -490,6 +490,34 @@ TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu, double
   return best;
 }
 
+// A launch of several rounds whose last is nearly empty costs less in two
+// parts: as many columns as whole rounds of a large tile take, then the rest in
+// the shape that is cheapest for them. Returns the first part's columns (0: one
+// launch) with both shapes. Taken where the cost model promises 6%, another
+// launch's 4 us included (us, one launch -> two): N 28672, K 4096 at 700 rows 168
+// -> 151, at 1800 378 -> 357, at 3000 558 -> 539; N 57344, K 8192 at 1000 749 ->
+// 706; N 10240, K 8192 at 2048 293 -> 271; N 6144, K 4096 at 3500 164 -> 143.
+// Where it promised 4 to 5% it gave 1 or 2, once -2. Beside another stream's
+// attention it loses (mixed step of 4 x 512 + 32 rows 1074 -> 1081).
+static int tile_columns(int M, int N, int K, bool swiglu, const TilePlan& whole, TilePlan* first, TilePlan* rest) {
+  const long cu = compute_units();
+  auto wgs = [&](const TileCfg& t, int n) { return (long)((M + 64 * t.qm - 1) / (64 * t.qm)) * (n / (64 * t.qn)); };
+  if (whole.s != 1 || wgs(kTileCfgs[whole.cfg], N) <= cu) return 0;
+  double best = tile_cost(kTileCfgs[whole.cfg], M, N, K, 1) / 1.06;
+  int cols = 0;
+  for (int i = 0; i < 4; ++i) {
+    const TileCfg& t = kTileCfgs[i];
+    const long tiles_m = (M + 64 * t.qm - 1) / (64 * t.qm);
+    const int n = (int)(wgs(t, N) / cu * cu / tiles_m * (64 * t.qn) / 256 * 256);
+    if (n <= 0 || n >= N) continue;
+    double c;
+    const TilePlan r = gemm_tile_plan(M, N - n, K, 1, swiglu, &c);
+    c += tile_cost(t, M, n, K, 1) + 4.0;
+    if (c < best) best = c, cols = n, *first = TilePlan{i, 1}, *rest = r;
+  }
+  return cols;
+}
+
 int gemm_tile_splits(int M, int N, int K) { return gemm_tile_plan(M, N, K, 4, false).s; }
 
 size_t gemm_tile_partials_bound(int max_rows, int N, int K) {
@@ -524,16 +552,15 @@ constexpr bool kTileAllShapes = (EPI == 0 && std::is_same<TR, float>::value) ||
                                 (EPI == 2 && std::is_same<TC, bf16_t>::value);
 
 #define PS_TILE_EXTERN(QM, QN, NS, NT, EPI, TR, TC)                                                                     \
-  extern template int launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(int, int, int, const void*, const void*, const void*, \
-                                                                 void*, hipStream_t, int, int);
+  extern template int launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(int, int, int, int, const void*, const void*,         \
+                                                                 const void*, void*, hipStream_t, int, int);
 PS_TILE_INSTANCES(PS_TILE_EXTERN)
 #undef PS_TILE_EXTERN
 
 template <int EPI, typename TR, typename TC>
-static int launch_tile(int M, int N, int K, TilePlan pl, const void* A, const void* W, const void* R, void* C,
-                       hipStream_t st) {
-  if (!kTileAllShapes<EPI, TR, TC>) pl.cfg = 0;
-  const int group = tile_group(M, N, kTileCfgs[pl.cfg].qm);
+static int launch_tile_cols(int M, int N, int cols, int K, TilePlan pl, const void* A, const void* W, const void* R,
+                            void* C, hipStream_t st) {
+  const int group = tile_group(M, cols, kTileCfgs[pl.cfg].qm);
   // One tile row: weight loads with the non-temporal hint (see the kernel).
   // Two rows of 192x256 or 256x256 tiles gain too (us, N 57344, K 8192: 300
   // rows 358 -> 348, 512 rows 418 -> 401; N 28672, K 4096 at 389 102 -> 99).
@@ -542,7 +569,7 @@ static int launch_tile(int M, int N, int K, TilePlan pl, const void* A, const vo
   // it 88), and from four rows on it gives nothing or loses 1 to 7%.
   const TileCfg& tc = kTileCfgs[pl.cfg];
   const bool nt = M <= 64 * tc.qm * (tc.qm >= 3 && tc.qn == 4 ? 2 : 1);
-#define PS_TILE_GO(QM, QN, NS, NT) launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(M, N, K, A, W, R, C, st, pl.s, group)
+#define PS_TILE_GO(QM, QN, NS, NT) launch_tile_g<QM, QN, NS, NT, EPI, TR, TC>(M, N, cols, K, A, W, R, C, st, pl.s, group)
 #define PS_TILE_GO_NT(QM, QN, NS) (nt ? PS_TILE_GO(QM, QN, NS, true) : PS_TILE_GO(QM, QN, NS, false))
   if constexpr (kTileAllShapes<EPI, TR, TC>) {
     switch (pl.cfg) {
@@ -564,6 +591,22 @@ static int launch_tile(int M, int N, int K, TilePlan pl, const void* A, const vo
   }
 #undef PS_TILE_GO_NT
 #undef PS_TILE_GO
+}
+
+template <int EPI, typename TR, typename TC>
+static int launch_tile(int M, int N, int K, TilePlan pl, const void* A, const void* W, const void* R, void* C,
+                       hipStream_t st, bool beside = false) {
+  if constexpr (!kTileAllShapes<EPI, TR, TC>) {
+    return launch_tile_cols<EPI, TR, TC>(M, N, N, K, TilePlan{0, pl.s}, A, W, R, C, st);
+  } else {
+    TilePlan a, b;
+    const int n = beside ? 0 : tile_columns(M, N, K, EPI == 2, pl, &a, &b);
+    if (n == 0) return launch_tile_cols<EPI, TR, TC>(M, N, N, K, pl, A, W, R, C, st);
+    if (launch_tile_cols<EPI, TR, TC>(M, N, n, K, a, A, W, R, C, st)) return -1;
+    const bf16_t* w = (const bf16_t*)W + (long)(n / 64) * (K / 64) * kWTileElts;
+    const void* r = R ? (const TR*)R + n : nullptr;
+    return launch_tile_cols<EPI, TR, TC>(M, N, N - n, K, b, A, w, r, (TC*)C + (EPI == 2 ? n / 2 : n), st);
+  }
 }
 
 int launch_gemm_tile_split(int M, int N, int K, int S, const void* A, const void* W, float* part, hipStream_t st) {
@@ -780,7 +823,7 @@ size_t gemm_workspace_bytes(int dtype, int M, int N, int K) {
 
 // Dispatch on (dtype, r_dtype, c_dtype, epilogue) and on M.
 int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
-                const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st) {
+                const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, bool beside) {
   if (M == 0) return 0;
   if (dtype == 0) {
     if (N % 64 != 0 && epi == 2) return -1;
@@ -817,7 +860,7 @@ int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, con
   if (N % 256 != 0) return -1;
 #define TILE_CASE(E, TR_, TC_, rd, cd) \
   if (epi == E && r_dt == rd && c_dt == cd)  \
-    return launch_tile<E, TR_, TC_>(M, N, K, gemm_tile_plan(M, N, K, 1, E == 2), A, W, R, C, st);
+    return launch_tile<E, TR_, TC_>(M, N, K, gemm_tile_plan(M, N, K, 1, E == 2), A, W, R, C, st, beside);
   TILE_CASE(0, float, bf16_t, 0, 1)
   TILE_CASE(0, float, bf16_t, 1, 1)
   TILE_CASE(0, float, float, 0, 0)
@@ -838,7 +881,7 @@ int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, con
 // summed in split order by the consumer, which fuses the reduction with its
 // own work); *splits = S then, else 1 and C holds the result.
 int launch_gemm_split(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
-                      const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, int* splits) {
+                      const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, int* splits, bool beside) {
   *splits = 1;
   if (dtype == 1 && M > 0 && M <= skinny::MAXM && N % 64 == 0 && K % 64 == 0 && epi != 2) {
     const SkinnyPlan pl = gemm_skinny_plan(M, N, K);
@@ -861,7 +904,7 @@ int launch_gemm_split(int dtype, int r_dt, int c_dt, int epi, int M, int N, int 
       }
     }
   }
-  return launch_gemm(dtype, r_dt, c_dt, epi, M, N, K, A, W, R, C, ws, ws_bytes, st);
+  return launch_gemm(dtype, r_dt, c_dt, epi, M, N, K, A, W, R, C, ws, ws_bytes, st, beside);
 }
 
 // Bytes of split-K partials a bf16 launch actually writes: 0 for the tile

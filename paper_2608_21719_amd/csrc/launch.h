@@ -90,8 +90,10 @@ int launch_fa_prefill(int G, int n_items, int n_kv, const void* q, const void* p
                       const int32_t* bt, const PrefillItem* items, void* o, float scale_log2, hipStream_t st);
 
 // GEMM C = epi(A W^T); ws holds split-K partials for decode-sized M.
+// beside: another stream's kernels hold part of the chip, so a tile launch is
+// not cut into column parts (their shapes count on whole rounds).
 int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
-                const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st);
+                const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, bool beside = false);
 size_t gemm_workspace_bytes(int dtype, int M, int N, int K);
 // fp32 C = epilogue(RMSNorm(x) W^T) (store or SwiGLU) in one launch, where
 // gemm_f32_norm_ok; its leading workgroups carry `up`.
@@ -99,7 +101,8 @@ bool gemm_f32_norm_ok(int epi, int M, int N, int K);
 int launch_gemm_f32_norm(int epi, int M, int N, int K, const float* x, const float* gain, float eps, const float* W,
                          float* C, hipStream_t st, const UploadJob* up = nullptr);
 int launch_gemm_split(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, const void* A, const void* W,
-                      const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, int* splits);
+                      const void* R, void* C, void* ws, size_t ws_bytes, hipStream_t st, int* splits,
+                      bool beside = false);
 struct SkinnyPlan {
   int wn;  // 64-row weight blocks per workgroup (1, 2 or 4)
   int s;   // K splits

@@ -121,6 +121,26 @@ def test_gemm_swiglu(M, F, K):
     H.assert_close_elementwise(H.to_f64(C), ref, 1e-3, 2 ** -7, "swiglu")
 
 
+# launches in two column parts: 256x256 tiles and 192x128, 256x128 or 128x128 for the rest
+@pytest.mark.parametrize("M,N,K", [(577, 28672, 4096), (700, 28672, 4096), (3000, 28672, 4096), (2048, 10240, 8192),
+                                   (3457, 6144, 4096), (4700, 4096, 4096)])
+def test_gemm_in_two_column_parts(M, N, K):
+    """Every output is one chain of products over K whatever tile it falls in: equal bit for bit to calls of 65 rows."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+    wt = torch.empty(N * K, dtype=torch.bfloat16, device="cuda")
+    B.op_tile_weight(B.PS_BF16, N, K, w, wt)
+    r = torch.randn((M, N), generator=g, device="cuda")
+    for epi, rdt, cols in ((B.PS_EPI_STORE, 0, N), (B.PS_EPI_RESIDUAL, B.PS_F32, N), (B.PS_EPI_SWIGLU, 0, N // 2)):
+        c, part = (torch.empty((m, cols), dtype=torch.bfloat16, device="cuda") for m in (M, 65))
+        res = r if epi == B.PS_EPI_RESIDUAL else None
+        B.op_gemm(B.PS_BF16, rdt, B.PS_BF16, epi, M, N, K, a, wt, res, c)
+        for r0 in (0, M // 2, M - 65):
+            B.op_gemm(B.PS_BF16, rdt, B.PS_BF16, epi, 65, N, K, a[r0:r0 + 65], wt, None if res is None else res[r0:r0 + 65], part)
+            assert torch.equal(c[r0:r0 + 65].view(torch.int16), part.view(torch.int16)), (epi, r0)
+
+
 # four weight blocks per workgroup: 160 workgroups at any row count, 257 from 33 rows on; one stage to several rings
 @pytest.mark.parametrize("M,N,K", [(1, 40960, 64), (16, 40960, 192), (17, 40960, 128), (33, 65792, 256), (64, 65792, 448)])
 def test_gemm_skinny_four_blocks(M, N, K):
