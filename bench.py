@@ -132,7 +132,7 @@ def bench_prefill(torch, B, A, wl, steps, warmup):
     # GEMM window above, then 200 are timed (about 0.1 s in all)
     a_ms = timer(attn_run, iters=max(200, steps), warmup=100)
     tel_attn = observe(attn_run)
-    traffic = measured_traffic("gate_up_gemm_8x2048", "paper_2608_21719_amd/csrc/k_gemm.hip")
+    traffic = measured_traffic("gate_up_gemm_8x2048", "paper_2608_21719_amd/csrc/gemm_tile.h")
     res = {
         "tok_s": tokens / (ms * 1e-3), "ms_per_step": ms,
         "layer_tflops": (total_gemm + attn) / (ms * 1e-3) / 1e12,
