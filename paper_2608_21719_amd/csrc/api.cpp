@@ -1505,9 +1505,10 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
   }
   if (ps_status rc = check_ws(ws, ws_bytes, mw.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
-  if (ps_status rc = upload_meta(kv, P.mt, ws, st)) return rc;
+  UploadJob up;
+  if (ps_status rc = stage_meta(kv, P.mt, ws, &up)) return rc;
   char* W = (char*)ws;
-  int bad = launch_embed(P.rows, c.hidden, M->vocab, M->embed, tokens, W + mw.xa, st);
+  int bad = launch_embed(P.rows, c.hidden, M->vocab, M->embed, tokens, W + mw.xa, st, up);
   char* cur = W + mw.xa;
   char* nxt = W + mw.xb;
   for (int l = 0; l < M->n_layers; ++l) {
@@ -1515,9 +1516,13 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
     std::swap(cur, nxt);
   }
   float* logits = logits_out ? logits_out : (float*)(W + mw.logits);
-  bad |= launch_gather_rows(n_out, c.hidden, cur, (const int32_t*)(W + o_last), W + mw.hl, st);
-  bad |= launch_rmsnorm(PS_BF16, PS_BF16, PS_BF16, n_out, c.hidden, W + mw.hl, M->final_norm, c.rms_eps, W + mw.hn,
-                        st);
+  // one row per sequence: every row is its sequence's last already
+  const char* hl = cur;
+  if (n_out != P.rows) {
+    bad |= launch_gather_rows(n_out, c.hidden, cur, (const int32_t*)(W + o_last), W + mw.hl, st);
+    hl = W + mw.hl;
+  }
+  bad |= launch_rmsnorm(PS_BF16, PS_BF16, PS_BF16, n_out, c.hidden, hl, M->final_norm, c.rms_eps, W + mw.hn, st);
   bad |= launch_gemm(PS_BF16, 0, PS_F32, PS_EPI_STORE, n_out, M->vocab, c.hidden, W + mw.hn, M->lm_head, nullptr,
                      logits, W + mw.lm, mw.total - mw.lm, st);
   bad |= launch_argmax(n_out, M->vocab, logits, next, st);

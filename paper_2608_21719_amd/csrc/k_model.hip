@@ -8,10 +8,16 @@ namespace ps {
 
 // x[r, :] = table[tokens[r], :], 16 bytes per thread.
 // Token ids outside [0, vocab) embed as zero rows (ids live on the device,
-// so they cannot be validated on the host before the launch).
+// so they cannot be validated on the host before the launch). The leading
+// up.blocks workgroups carry the step's metadata upload, which nothing here
+// reads (a launch of its own took 4.6 us of an 8-row step).
 __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ table, const int32_t* __restrict__ tokens,
-                                                    bf16_t* __restrict__ x, int d, int vocab) {
-  const long r = blockIdx.x;
+                                                    bf16_t* __restrict__ x, int d, int vocab, UploadJob up) {
+  if ((int)blockIdx.x < up.blocks) {
+    upload_block(up, blockIdx.x);
+    return;
+  }
+  const long r = (long)blockIdx.x - up.blocks;
   const int tok = tokens[r];
   if (tok < 0 || tok >= vocab) {
     for (int i = threadIdx.x * 8; i < d; i += 256 * 8) *(uint4*)(x + r * d + i) = make_uint4(0, 0, 0, 0);
@@ -138,10 +144,12 @@ int launch_tile_weight(int elt_bytes, long N, long K, const void* src, void* dst
   return 0;
 }
 
-int launch_embed(int rows, int d, int vocab, const void* table, const int32_t* tokens, void* x, hipStream_t st) {
+int launch_embed(int rows, int d, int vocab, const void* table, const int32_t* tokens, void* x, hipStream_t st,
+                 const UploadJob& up) {
   if (rows == 0) return 0;
   if (d % 8) return -1;
-  hipLaunchKernelGGL(embed_kernel, dim3(rows), dim3(256), 0, st, (const bf16_t*)table, tokens, (bf16_t*)x, d, vocab);
+  hipLaunchKernelGGL(embed_kernel, dim3(rows + up.blocks), dim3(256), 0, st, (const bf16_t*)table, tokens, (bf16_t*)x, d,
+                     vocab, up);
   return 0;
 }
 

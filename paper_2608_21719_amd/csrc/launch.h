@@ -166,7 +166,8 @@ __device__ inline void upload_block(const UploadJob& j, int b) {
 bool make_upload_job(const void* host_dev_ptr, void* dst, size_t bytes, uint32_t* done, uint32_t tag, UploadJob* j);
 // Enqueues the job as its own kernel.
 int launch_upload(const UploadJob& j, hipStream_t st);
-int launch_embed(int rows, int d, int vocab, const void* table, const int32_t* tokens, void* x, hipStream_t st);
+int launch_embed(int rows, int d, int vocab, const void* table, const int32_t* tokens, void* x, hipStream_t st,
+                 const UploadJob& up);
 int launch_gather_rows(int n, int d, const void* src, const int32_t* rows, void* dst, hipStream_t st);
 int launch_argmax(int rows, int vocab, const float* logits, int32_t* next, hipStream_t st);
 int launch_tile_weight(int elt_bytes, long N, long K, const void* src, void* dst, hipStream_t st);
