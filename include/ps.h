@@ -483,10 +483,11 @@ ps_status ps_op_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, const int32_
  * split_pages = at most that many pages per split: each sequence's pages
  * are cut into ceil(pages / split_pages) splits of near-equal size. 0 =
  * library choice: one split per sequence where that is estimated to be
- * fastest (sequences of similar length that fill the chip, or a batch that
- * alone exceeds 1024 workgroups); else the smallest multiple of 4 pages, at
- * least 8 (up to 16 for short contexts), that keeps the workgroups (splits
- * times KV heads) within about 1024, two full rounds of the chip.
+ * fastest (sequences that load the compute units evenly and need no combine
+ * then, or a batch that alone exceeds 1024 workgroups); else the smallest
+ * multiple of 4 pages, at least 8 (16 where that still fills the chip), that
+ * keeps the workgroups (splits times KV heads) within about 1024, two full
+ * rounds of the chip.
  * PS_E_UNSUPPORTED when the splits come to more than 65535
  * work items (one grid row each). */
 ps_status ps_op_decode_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, const int32_t* seqs,

@@ -8,6 +8,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <initializer_list>
 #include <new>
 #include <string>
@@ -500,29 +501,56 @@ struct DecodePlan {
   int32_t n_parts = 0;
 };
 
-// Microseconds of decode attention with one split per sequence, all
-// workgroups resident: they share 6.7 TB/s evenly, at most 27 GB/s each, and
-// leave as they finish. Such a launch needs no combine (5.5 us) and pays one
-// ramp-up per sequence. 70B, 64 sequences at 4096: 159 us, in two splits each
-// and combined 168; 8B, 32 at 600: 15.7 and 21.5; but 64 of 1024 to 4096 tokens
-// 117 and 111: the longest run on alone.
-double whole_walk_us(std::vector<long> pages, int n_kv) {
-  std::sort(pages.begin(), pages.end());
-  constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kChip = 6.7e6, kGroup = 27.0e3;  // bytes per us
-  double us = 0;
-  long done = 0, active = (long)pages.size() * n_kv;
-  for (long p : pages) {
-    us += (p - done) * kPageBytes / std::min(kGroup, kChip / active);
-    done = p;
-    active -= n_kv;
+// Pages of decode attention's fullest compute unit, from the pages of each work
+// item: the items' n_kv workgroups each go round the units, longest items first,
+// two to a unit, and the rest to whichever unit ends first.
+long fullest_unit_pages(std::vector<long> items, int n_kv) {
+  std::sort(items.begin(), items.end(), std::greater<long>());
+  const size_t groups = std::max(1, compute_units() / std::max(1, n_kv)), resident = std::min(items.size(), 2 * groups);
+  std::vector<long> load(groups, 0);  // units that hold one item's workgroups side by side
+  for (size_t i = 0; i < resident; ++i) load[i % groups] += items[i];
+  if (items.size() > resident) {  // a heap, the emptiest in front
+    std::make_heap(load.begin(), load.end(), std::greater<long>());
+    for (size_t i = resident; i < items.size(); ++i) {
+      std::pop_heap(load.begin(), load.end(), std::greater<long>());
+      load.back() += items[i];
+      std::push_heap(load.begin(), load.end(), std::greater<long>());
+    }
   }
-  return us;
+  return *std::max_element(load.begin(), load.end());
 }
 
-int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_kv, int phase) {
-  (void)phase;
-  long total = 0;
-  for (size_t b = first; b < si.size(); ++b) total += (si[b].kv_before + si[b].n_new + 15) / 16;
+// Microseconds of decode attention where each sequence's pages are cut into
+// splits of at most `split`: the fullest compute unit's pages at the 27 GB/s a
+// unit streams with one workgroup or two, 2 for a round of workgroups, 7 for the
+// combine where a sequence is split, and 8 for RoPE's launch where `rope` (a
+// layer call's decode step) and more than one round leave it outside. Least
+// regret over 1390 batches of 1 to 1000 sequences with 1 to 16 KV heads: the
+// cheapest by this of the splits compared below is 0.5% above the fastest of them
+// on average, in layer calls 0.05%.
+double decode_us(const std::vector<long>& pages, long split, int n_kv, bool rope) {
+  std::vector<long> items;
+  bool cut = false;
+  for (long p : pages) {
+    const long ns = (p + split - 1) / split;
+    cut = cut || ns > 1;
+    for (long k = 0; k < ns; ++k) items.push_back((k + 1) * p / ns - k * p / ns);
+  }
+  const double rounds = (double)items.size() * n_kv / (2.0 * compute_units());
+  constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kUnit = 27.0e3;  // bytes, bytes per us
+  return fullest_unit_pages(std::move(items), n_kv) * kPageBytes / kUnit + 2.0 * rounds + (cut ? 7.0 : 0.0) +
+         (rope && rounds > 1.0 ? 8.0 : 0.0);
+}
+
+int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_kv, bool rope) {
+  std::vector<long> pages;
+  long total = 0, max_pages = 8;
+  for (size_t b = first; b < si.size(); ++b) {
+    pages.push_back((si[b].kv_before + si[b].n_new + 15) / 16);
+    total += pages.back();
+    max_pages = std::max(max_pages, pages.back());
+  }
+  if (pages.empty()) return 8;
   // At most about 1024 workgroups over the chip: two full rounds of the 512
   // that fit at two per CU, at least 8 pages per split, a multiple of 4 (the
   // four waves of a workgroup walk pages w, w + 4, ...). Measured over split
@@ -536,28 +564,12 @@ int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_k
   // one split per sequence.
   auto n_items = [&](long spl) {
     long n = 0;
-    for (size_t b = first; b < si.size(); ++b) n += ((si[b].kv_before + si[b].n_new + 15) / 16 + spl - 1) / spl;
+    for (long p : pages) n += (p + spl - 1) / spl;
     return n;
   };
-  long max_pages = 8;
-  for (size_t b = first; b < si.size(); ++b) max_pages = std::max<long>(max_pages, (si[b].kv_before + si[b].n_new + 15) / 16);
   const long target_items = std::max(1, 1024 / std::max(1, n_kv));
-  const long n_seqs = (long)(si.size() - first);
-  if (n_seqs > 0 && n_seqs <= target_items) {
-    std::vector<long> pages;
-    for (size_t b = first; b < si.size(); ++b) pages.push_back((si[b].kv_before + si[b].n_new + 15) / 16);
-    const double split_us = total * n_kv * 8192.0 / 6.4e6 + 5.5;
-    if (whole_walk_us(std::move(pages), n_kv) < split_us) return (int32_t)((max_pages + 3) / 4 * 4);
-  }
   long sp = std::max<long>((total + target_items - 1) / target_items, 8);
   sp = (sp + 3) / 4 * 4;
-  // Short splits: up to 16 pages where a quarter of the workgroups then still
-  // fills the chip (8 sequences of 256 to 2048 tokens: 8 pages 17.0 us, 16
-  // 15.9; one of 2048 keeps 8: 11.0 against 11.5)
-  if (sp < 16) {
-    const long quarter = (total + target_items / 4) / std::max(1L, target_items / 4);
-    sp = std::max(sp, std::min(16L, (quarter + 3) / 4 * 4));
-  }
   if (n_items(sp) > target_items) {  // smallest multiple of 4 in (sp, max_pages] that fits: n_items falls as sp grows
     long lo = sp / 4, hi = (max_pages + 3) / 4;
     while (lo + 1 < hi) {
@@ -566,6 +578,22 @@ int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_k
       else lo = mid;
     }
     sp = 4 * hi;
+  }
+  // Two more are weighed against it: 16 pages in place of shorter splits (fewer
+  // workgroups, or a single round), and one split per sequence (no combine, but
+  // where the sequences do not spread evenly the units with one more set the
+  // end). Us, 8 KV heads, attention and combine, 8 pages / 16: 8 sequences of 256
+  // to 2048 tokens 17.0 / 15.9, one of 2500 15.2 / 12.5; but 6 of 400 to 1600 13.3 /
+  // 14.9. Split / whole: 32 of 2800 60 / 56, but 33 72 / 92; 64 of 4096 163 / 157,
+  // 48 123 / 141; 64 of 1024 to 4096 111 / 123; 32 of 300 15 / 9.
+  if ((long)pages.size() <= target_items) {
+    const long base = sp, whole = (max_pages + 3) / 4 * 4;
+    double best = decode_us(pages, base, n_kv, rope);
+    for (long c : {16L, whole}) {
+      if (c <= base) continue;
+      const double us = decode_us(pages, c, n_kv, rope);
+      if (us < best) best = us, sp = c;
+    }
   }
   // the work-item index is a grid y coordinate (at most 65535): widen the
   // splits until the items fit (a batch of more sequences than that is
@@ -1148,7 +1176,7 @@ ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int3
     }
   }
   if (P.dec_mfma) {
-    DecodePlan dp = plan_decode(cs.si, n_chunk, choose_split_pages(cs.si, n_chunk, c.n_kv_heads, phase));
+    DecodePlan dp = plan_decode(cs.si, n_chunk, choose_split_pages(cs.si, n_chunk, c.n_kv_heads, n_chunk == 0));
     if ((long)dp.items.size() > kMaxDecodeItems)
       return fail(PS_E_UNSUPPORTED, "decode batch exceeds 65535 attention work items");
     P.n_ditems = (int)dp.items.size();
@@ -1820,7 +1848,7 @@ extern "C" ps_status ps_op_decode_plan(ps_kv* kv, int32_t n_seqs, const int32_t*
   DecodeAttnPlan pl;
   pl.o_si = mt.add(cs.si.data(), cs.si.size() * sizeof(SeqInfo));
   pl.o_bt = mt.add(cs.bt.data(), cs.bt.size() * 4);
-  const int32_t sp = split_pages > 0 ? split_pages : choose_split_pages(cs.si, 0, c.n_kv_heads, PS_PHASE_ANSWER);
+  const int32_t sp = split_pages > 0 ? split_pages : choose_split_pages(cs.si, 0, c.n_kv_heads, false);
   DecodePlan dp = plan_decode(cs.si, 0, sp);
   if ((long)dp.items.size() > kMaxDecodeItems)
     return fail(PS_E_UNSUPPORTED, "more than 65535 attention work items: use larger split_pages");

@@ -573,10 +573,12 @@ def test_decode_library_split_choice(n_seqs, hist, expect):
 
 
 # sequences of similar length that fill the chip take one split each (finished by the attention kernel, no combine);
-# one long sequence among them, or too few of them, keeps the splits
+# one long sequence among them, too few of them, or counts that put two workgroups on a few compute units keep the splits
 @pytest.mark.parametrize("lens,whole", [([350] * 64, True), ([300 + 3 * i for i in range(40)], True),
-                                        ([4000] + [300] * 31, False), ([600] * 4, False)],
-                         ids=["equal", "similar", "one-long", "few"])
+                                        ([4000] + [300] * 31, False), ([600] * 4, False), ([2800] * 32, True),
+                                        ([2800] * 35, False), ([2600 + 9 * i for i in range(44)], False),
+                                        ([2600 + 6 * i for i in range(65)], False)],
+                         ids=["equal", "similar", "one-long", "few", "one-each", "uneven", "uneven-ragged", "third-round"])
 def test_decode_one_split_per_sequence(lens, whole):
     P = make_pool(S8, sum(-(-(L + 1) // 16) for L in lens) + 8, len(lens), 256, seed=33)
     seqs, Ks, Vs = fill_kv(P, lens, [1] * len(lens), "bf16", 340)
