@@ -839,7 +839,7 @@ int launch_gemm(int dtype, int r_dt, int c_dt, int epi, int M, int N, int K, con
   }
   if (K % 64 != 0) return -1;
   if (M <= skinny::MAXM && N % 64 == 0) {
-    if (ws_bytes < gemm_workspace_bytes(dtype, M, N, K)) return -2;
+    if (ws_bytes < gemm_partials_bytes(dtype, epi, M, N, K)) return -2;
     float* part = (float*)ws;
 #define SK_CASE(E, TR_, TC_, rd, cd) \
   if (epi == E && r_dt == rd && c_dt == cd) return launch_skinny<E, TR_, TC_>(M, N, K, A, W, part, R, C, st);

@@ -67,3 +67,11 @@ def test_static_scratch_gemm_equals_workspace_gemm_on_two_calls():
         _, _, _, ref, got = _pair(M, N, K, epi, rdt, cdt, 12 + M)
         bits = torch.int16 if cdt == B.PS_BF16 else torch.int32
         assert torch.equal(ref.view(bits), got.view(bits))
+
+
+@pytest.mark.parametrize("epi,rdt", [(B.PS_EPI_STORE, 0), (B.PS_EPI_RESIDUAL, B.PS_F32), (B.PS_EPI_SWIGLU, 0)])
+@pytest.mark.parametrize("M,N,K", [(8, 28672, 4096), (64, 57344, 128), (3, 192, 64)])
+def test_static_gemm_without_a_k_split(M, N, K, epi, rdt):
+    """Launches that write no partials, or (SwiGLU in 64-row blocks) one set of them."""
+    _, _, _, ref, got = _pair(M, N, K, epi, rdt, B.PS_BF16, M)
+    assert torch.equal(ref.view(torch.int16), got.view(torch.int16))
