@@ -1477,7 +1477,11 @@ struct ModelWs {
   size_t xa, xb, hl, hn, logits, lm, total;
 };
 
-ModelWs model_layout(const ps_layer_cfg& c, int32_t vocab, size_t layer_total, int32_t rows, int32_t n_out) {
+// lm_rows: rows the LM head's partials are sized for: n_out in a call; a bound
+// over calls takes min(n_out, 64), the most that splits K, and covers smaller
+// calls too.
+ModelWs model_layout(const ps_layer_cfg& c, int32_t vocab, size_t layer_total, int32_t rows, int32_t n_out,
+                     int32_t lm_rows) {
   ModelWs m;
   size_t off = align_up(layer_total, 256);
   auto take = [&](size_t bytes) {
@@ -1490,7 +1494,7 @@ ModelWs model_layout(const ps_layer_cfg& c, int32_t vocab, size_t layer_total, i
   m.hl = take((size_t)n_out * c.hidden * 2);
   m.hn = take((size_t)n_out * c.hidden * 2);
   m.logits = take((size_t)n_out * vocab * 4);
-  m.lm = take(gemm_workspace_bytes(PS_BF16, n_out, vocab, c.hidden));
+  m.lm = take(gemm_partials_bytes(PS_BF16, PS_EPI_STORE, lm_rows, vocab, c.hidden));
   m.total = off;
   return m;
 }
@@ -1523,13 +1527,13 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
   }
   size_t o_last = P.mt.add(last.data(), last.size() * 4);
   P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
-  ModelWs mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out);
+  ModelWs mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out, n_out);
   if (P.n_merges > 0 && ws_bytes < mw.total) {  // no room for the longer work list: the unsplit walk
     P = LayerPlan{};
     if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
     o_last = P.mt.add(last.data(), last.size() * 4);
     P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
-    mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out);
+    mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out, n_out);
   }
   if (ps_status rc = check_ws(ws, ws_bytes, mw.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
@@ -1598,7 +1602,7 @@ extern "C" size_t ps_model_workspace_bytes(const ps_layer_cfg* c, int32_t vocab,
   const size_t mb = meta_bound(*c, max_rows, max_seqs, max_pages_per_seq) + align_up(4ull * max_seqs, 256);
   const int32_t parts = max_seqs * ((max_pages_per_seq + 7) / 8);
   const WsLayout wl = layout(*c, mb, max_rows, parts);
-  return model_layout(*c, vocab, wl.total, max_rows, max_seqs).total;
+  return model_layout(*c, vocab, wl.total, max_rows, max_seqs, std::min(max_seqs, 64)).total;
 }
 
 extern "C" ps_status ps_model_prefill(ps_model* M, ps_kv* kv, int32_t n_seqs, const int32_t* seqs,

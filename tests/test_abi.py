@@ -207,6 +207,20 @@ def test_workspace_and_pool_sizes():
     assert B.Layer.workspace_bytes(cfg, 64, 64, 300) > 64 * (4096 + 14336) * 2
 
 
+@pytest.mark.parametrize("vocab", [2048, 32000, 128256])
+def test_workspace_bounds_grow_with_every_argument(vocab):
+    """A workspace sized for a larger call is accepted by every smaller one."""
+    cfg = B.make_cfg(CONFIGS["llama8b_decode"].shape)
+
+    def growing(sizes):
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), sizes
+
+    growing([B.Model.workspace_bytes(cfg, vocab, n, n, 64) for n in range(1, 131)])
+    growing([B.Model.workspace_bytes(cfg, vocab, 512, n, 64) for n in range(1, 131)])
+    growing([B.Layer.workspace_bytes(cfg, n, 8, 64) for n in range(1, 5000, 17)])
+    growing([B.Layer.workspace_bytes(cfg, 64, 8, n) for n in range(1, 300)])
+
+
 def test_decode_run_needs_a_current_plan_and_its_workspace():
     """Host-side checks of plan/run (no sequences, so nothing is launched)."""
     from ctypes import c_void_p
