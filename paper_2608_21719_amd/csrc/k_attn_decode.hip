@@ -206,12 +206,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     const float m_new = fmaxf(m, mx);
-    const float alpha = exp2f(m - m_new);
+    const float base = m_new == -INFINITY ? 0.f : m_new;  // only scores of -inf yet: their weights are 0, not NaN
+    const float alpha = exp2f(m - base);
     float pr[4];
     uint32_t pk[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-      pk[r] = pack_bf2(exp2f(sc[2 * r] - m_new), exp2f(sc[2 * r + 1] - m_new));
+      pk[r] = pack_bf2(exp2f(sc[2 * r] - base), exp2f(sc[2 * r + 1] - base));
       pr[2 * r] = bf_lo(pk[r]);
       pr[2 * r + 1] = bf_hi(pk[r]);
     }
@@ -558,7 +559,8 @@ __global__ __launch_bounds__(64 * WK) void attn_generic_kernel(const T* __restri
     float mx = sc;
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     const float m_new = fmaxf(m, mx);
-    const float alpha = expf(m - m_new), p = expf(sc - m_new);
+    const float base = m_new == -INFINITY ? 0.f : m_new;  // only scores of -inf yet: their weights are 0, not NaN
+    const float alpha = expf(m - base), p = expf(sc - base);
     float ps = p;
     for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
     l = l * alpha + ps;

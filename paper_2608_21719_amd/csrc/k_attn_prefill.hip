@@ -206,12 +206,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     }
     // P = 2^(s scale - mb) against the row's exponent base mb, and this
     // lane's partial row sum of the bf16 P values. The first tile sets the
-    // base from its own row max (its first key is visible to every query row,
-    // so that max is finite). After it, the sum doubles as the test of the base: past
-    // 2^32 (or infinite or NaN, where an exponent overflowed) the tile takes
-    // the slow path, which takes the row's true max over the tile, rescales O
-    // and l to it and redoes the exponentials. While the base stands no max
-    // is taken at all.
+    // base from its own row max (its first key is visible to every query row).
+    // After it, the sum doubles as the test of the base: past 2^32 (or infinite
+    // or NaN, where an exponent overflowed) the tile takes the slow path, which
+    // takes the row's true max over the tile, rescales O and l to it and redoes
+    // the exponentials. While the base stands no max is taken at all.
     uint32_t pk[8];
     auto exps = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -231,24 +230,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
       return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     };
+    // Where every score so far is -inf, the exponentials are taken against 0 (all
+    // are 0 then) and the base stays -inf, which sends the next tile to the slow
+    // path: its exponentials overflow, or are NaN if its scores are -inf too.
     float lt;
     if constexpr (FIRST) {
       m = row_max();
-      mb = m * scale_log2;
+      const bool none = m == -INFINITY;
+      mb = none ? 0.f : m * scale_log2;
       lt = exps();
+      if (none) mb = -INFINITY;
     } else {
       lt = exps();
       if (__any(!(lt <= 0x1p32f))) {
         const float m_new = fmaxf(m, row_max());
-        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * scale_log2);
+        const bool none = m_new == -INFINITY;
+        const float alpha = none ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * scale_log2);
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
           for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
         lsum *= alpha;
         m = m_new;
-        mb = m * scale_log2;
+        mb = none ? 0.f : m * scale_log2;
         lt = exps();
+        if (none) mb = -INFINITY;
       }
     }
     lsum += lt;

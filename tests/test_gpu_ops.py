@@ -458,8 +458,9 @@ def test_rope_kvwrite_large_batch_equals_per_sequence_calls_bit_for_bit(shape, h
 
 
 # ------------------------------------------------------------------ attention
-def fill_kv(P, lens_hist, n_new, dtype, seed, ones_v=False):
-    """Open sequences, write history (committed) and new rows (uncommitted)."""
+def fill_kv(P, lens_hist, n_new, dtype, seed, ones_v=False, masked=None):
+    """Open sequences, write history (committed) and new rows (uncommitted).
+    masked: keys [lo, hi) get -inf in dimension 0."""
     kv, shape = P.kv, P.shape
     seqs = [kv.open() for _ in lens_hist]
     ws = H.workspace(1 << 22)
@@ -468,6 +469,8 @@ def fill_kv(P, lens_hist, n_new, dtype, seed, ones_v=False):
         kv.alloc(s, L + n)
         k = rnd((L + n, shape.n_kv, shape.head_dim), dtype, seed + 2 * i)
         v = rnd((L + n, shape.n_kv, shape.head_dim), dtype, seed + 2 * i + 1)
+        if masked:
+            k[slice(*masked), :, 0] = gen.to_storage(np.full(1, -np.inf, np.float32), dtype)[0]
         if ones_v:
             v = gen.to_storage(np.ones((L + n, shape.n_kv, shape.head_dim), np.float32), dtype)
         Ks.append(k)
@@ -809,3 +812,43 @@ def test_prefill_attention_split_ones_v_gives_exactly_one():
     B.op_attention(P.kv, 0, seqs, [70, 5], H.to_dev(q, "bf16"), o, H.workspace(1 << 27))
     sync()
     assert np.all(H.to_f64(o) == 1.0)
+
+
+# keys masked by -inf scores over whole 64-key blocks, pages, key tiles and key ranges of split walks; the walk's own start
+# among them (0) or not
+@pytest.mark.parametrize("lo", [0, 5, 32])
+@pytest.mark.parametrize("dtype,n_q,n_kv,hd,hist,new,hi", [
+    ("f32", 4, 2, 64, 1500, 1, 1400), ("f32", 8, 2, 64, 300, 70, 290), ("bf16", 6, 2, 64, 700, 5, 640),
+    ("f32", 2, 2, 6, 400, 3, 390), ("bf16", 32, 8, 128, 6000, 33, 5900), ("bf16", 32, 8, 128, 200, 300, 190),
+    ("bf16", 64, 8, 128, 3000, 64, 2990)])
+@pytest.mark.parametrize("room", [1 << 27, 1 << 17], ids=["roomy", "unsplit"])
+def test_attention_past_blocks_of_masked_keys(dtype, n_q, n_kv, hd, hist, new, hi, lo, room):
+    """A block whose scores are all -inf adds nothing, wherever a wave, a tile or a range begins."""
+    shape = LayerShape(n_q * hd, n_q, n_kv, hd, 64, 1e-5, 10000.0, dtype)
+    P = make_pool(shape, 512, 1, 500, seed=9)
+    seqs, Ks, Vs = fill_kv(P, [hist], [new], dtype, 910, masked=(lo, hi))
+    q = rnd((new, n_q, hd), dtype, 67, 2.0)
+    q[:, :, 0] = gen.to_storage(np.ones(1, np.float32), dtype)[0]
+    o = H.empty((new, n_q * hd), dtype)
+    B.op_attention(P.kv, 0, seqs, [new], H.to_dev(q, dtype), o, H.workspace(room))
+    sync()
+    rows = sorted({0, new // 2, new - 1})
+    with np.errstate(invalid="ignore"):
+        ref = O.attention(gen.widen(q, dtype)[rows], gen.widen(Ks[0], dtype), gen.widen(Vs[0], dtype), hist + np.array(rows))
+    atol, rtol = (H.BF16_TOL_ABS, H.BF16_TOL_REL) if dtype == "bf16" else (1e-5, 1e-5)
+    H.assert_close_elementwise(H.to_f64(o).reshape(new, n_q, hd)[rows], ref, atol, rtol, "masked keys")
+
+
+@pytest.mark.parametrize("split", [0, 1, 8, 20, 256])
+@pytest.mark.parametrize("lo,hi", [(0, 2400), (16, 80), (5, 2490), (1000, 1300)])
+def test_decode_attention_past_pages_of_masked_keys(split, lo, hi):
+    P = make_pool(S8, 180, 1, 180, seed=9)
+    seqs, Ks, Vs = fill_kv(P, [2500], [1], "bf16", 920, masked=(lo, hi))
+    q = rnd((1, S8.n_q, S8.head_dim), "bf16", 68, 2.0)
+    q[:, :, 0] = gen.to_storage(np.ones(1, np.float32), "bf16")[0]
+    o = H.empty((1, S8.d_q), "bf16")
+    B.op_decode_attention(P.kv, 0, seqs, H.to_dev(q, "bf16"), o, H.workspace(1 << 24), split_pages=split)
+    sync()
+    with np.errstate(invalid="ignore"):
+        ref = O.attention(gen.widen(q, "bf16"), gen.widen(Ks[0], "bf16"), gen.widen(Vs[0], "bf16"), np.array([2500]))
+    H.assert_close_elementwise(H.to_f64(o).reshape(1, S8.n_q, S8.head_dim), ref, H.BF16_TOL_ABS, H.BF16_TOL_REL, "masked keys")
