@@ -275,13 +275,25 @@ struct AuxStream {
   }
 };
 
+// A layer's tile GEMMs that may split K (bf16): O and down.
+struct SplitGemms {
+  TilePartials o, down;
+  explicit SplitGemms(const ps_layer_cfg& c, int32_t max_rows = INT32_MAX)
+      : o(c.hidden, c.n_q_heads * c.head_dim, c.dtype == PS_BF16 ? max_rows : 0),
+        down(c.hidden, c.ffn, c.dtype == PS_BF16 ? max_rows : 0) {}
+};
+
 struct ps_layer {
   ps_layer_cfg cfg;
+  SplitGemms split;
   AuxStream aux;
+  explicit ps_layer(const ps_layer_cfg& c) : cfg(c), split(c) {}
 };
 
 struct ps_model {
   ps_layer_cfg cfg;
+  SplitGemms split;
+  explicit ps_model(const ps_layer_cfg& c) : cfg(c), split(c) {}
   int32_t n_layers = 0, vocab = 0;
   const void* embed = nullptr;
   const void* final_norm = nullptr;
@@ -649,18 +661,20 @@ struct PrefillSplit {
   int32_t n_parts = 0;
 };
 
-// `groups`: workgroups per query tile (4 query heads each); `max_parts`: room
-// for partial results. For one, two and three workgroups per compute unit, the
-// shortest split length (at least 24 key tiles) whose items fit that many and
-// whose parts fit the room; the cheapest of them and the whole walk is taken,
-// each tile's walk cut into near-equal ranges. Costs in us, measured: a key
+// `groups`: workgroups per query tile (4 query heads each); `max_parts_of()`:
+// room for partial results, asked only where a walk is long enough. For one,
+// two and three workgroups per compute unit, the shortest split length (at
+// least 24 key tiles) whose items fit that many and whose parts fit the room;
+// the cheapest of them and the whole walk is taken, each tile's walk cut into
+// near-equal ranges. Costs in us, measured: a key
 // tile of a workgroup's walk takes 0.65, 0.95 and 1.5 with one, two and three
 // workgroups on a compute unit; the merge is a launch (8) and its partials'
 // traffic. Whole walk -> split and merged, 8B shape: 64 rows behind 16000
 // tokens 324 -> 51 us, 512 behind 4000 96 -> 64, three of 300 to 512 behind
 // 6000 to 12000 306 -> 199; 1024 behind 2000 stays whole (68; cut to fill three
 // workgroups per unit it took 72).
-PrefillSplit plan_prefill_split(const std::vector<SeqInfo>& si, size_t count, int groups, int n_q, int max_parts) {
+template <typename MaxParts>
+PrefillSplit plan_prefill_split(const std::vector<SeqInfo>& si, size_t count, int groups, int n_q, MaxParts&& max_parts_of) {
   PrefillSplit P;
   const int qt = fa_query_tile(), kt = fa_key_tile();
   struct Tile {
@@ -678,6 +692,7 @@ PrefillSplit plan_prefill_split(const std::vector<SeqInfo>& si, size_t count, in
   for (const Tile& x : t) longest = std::max(longest, x.tiles);
   constexpr int kMinTiles = 24;
   if (longest < 2 * kMinTiles) return P;
+  const int max_parts = max_parts_of();
   auto count_items = [&](int len, int* parts) {
     int n = 0;
     *parts = 0;
@@ -745,12 +760,41 @@ std::vector<double> inv_freq(const ps_layer_cfg& c) {
   return f;
 }
 
+// Bytes of a layer call's GEMM partials, on the caller's stream and on the
+// second one.
+struct GemmRoom {
+  size_t main = 0, second = 0;
+};
+
+GemmRoom gemm_room(const ps_layer_cfg& c, const SplitGemms& split, int32_t rows) {
+  const size_t d = c.hidden, dq = (size_t)c.n_q_heads * c.head_dim, dkv = (size_t)c.n_kv_heads * c.head_dim;
+  GemmRoom r;
+  // split-K partials of the decode-sized GEMMs, sized for min(rows, 64)
+  // rows so that a bound taken for more rows also covers smaller calls
+  const int gm = std::min(rows, 64);
+  if (gm > 0) {
+    // O, SwiGLU and down: also the decode rows' when they run on the second
+    // stream beside the chunk rows
+    r.second = std::max(r.second, gemm_workspace_bytes(c.dtype, gm, (int)d, (int)dq));
+    r.second = std::max(r.second, gemm_workspace_bytes(c.dtype, gm, 2 * c.ffn, (int)d));
+    r.second = std::max(r.second, gemm_workspace_bytes(c.dtype, gm, (int)d, c.ffn));
+    r.main = std::max(r.second, gemm_workspace_bytes(c.dtype, gm, (int)(dq + 2 * dkv), (int)d));
+  }
+  // K-split partials of the tile-path O and down GEMMs, for any row count
+  // up to `rows` (a call's chunk rows included)
+  if (c.dtype == PS_BF16 && rows > 0) {
+    r.main = std::max(r.main, split.o.bytes(rows));
+    r.main = std::max(r.main, split.down.bytes(rows));
+  }
+  return r;
+}
+
 // Workspace carve-out for a layer call (after the metadata region).
 struct WsLayout {
   size_t xn, qkv, qr, o, h, m, gemm, gemm_b, apart_o, apart_ml, total;
 };
 
-WsLayout layout(const ps_layer_cfg& c, size_t meta_bytes, int32_t rows, int32_t n_parts_max) {
+WsLayout layout(const ps_layer_cfg& c, size_t meta_bytes, int32_t rows, int32_t n_parts_max, const GemmRoom& gemm) {
   const size_t eb = elt_bytes(c.dtype);
   const size_t d = c.hidden, dq = (size_t)c.n_q_heads * c.head_dim, dkv = (size_t)c.n_kv_heads * c.head_dim;
   WsLayout L;
@@ -766,32 +810,8 @@ WsLayout layout(const ps_layer_cfg& c, size_t meta_bytes, int32_t rows, int32_t 
   L.o = take(rows * dq * eb);
   L.h = take(rows * d * 4);
   L.m = take(rows * (size_t)c.ffn * eb);
-  // split-K partials of the decode-sized GEMMs, sized for min(rows, 64)
-  // rows so that a bound taken for more rows also covers smaller calls
-  size_t g = 0;
-  const int gm = std::min(rows, 64);
-  if (gm > 0) {
-    g = std::max(g, gemm_workspace_bytes(c.dtype, gm, (int)(dq + 2 * dkv), (int)d));
-    g = std::max(g, gemm_workspace_bytes(c.dtype, gm, (int)d, (int)dq));
-    g = std::max(g, gemm_workspace_bytes(c.dtype, gm, 2 * c.ffn, (int)d));
-    g = std::max(g, gemm_workspace_bytes(c.dtype, gm, (int)d, c.ffn));
-  }
-  // K-split partials of the tile-path O and down GEMMs, for any row count
-  // up to `rows` (a call's chunk rows included)
-  if (c.dtype == PS_BF16 && rows > 0) {
-    g = std::max(g, gemm_tile_partials_bound(rows, (int)d, (int)dq));
-    g = std::max(g, gemm_tile_partials_bound(rows, (int)d, c.ffn));
-  }
-  L.gemm = take(g);
-  // the decode rows' O, SwiGLU and down partials when they run on the
-  // second stream beside the chunk rows
-  size_t gb = 0;
-  if (gm > 0) {
-    gb = std::max(gb, gemm_workspace_bytes(c.dtype, gm, (int)d, (int)dq));
-    gb = std::max(gb, gemm_workspace_bytes(c.dtype, gm, 2 * c.ffn, (int)d));
-    gb = std::max(gb, gemm_workspace_bytes(c.dtype, gm, (int)d, c.ffn));
-  }
-  L.gemm_b = take(gb);
+  L.gemm = take(gemm.main);
+  L.gemm_b = take(gemm.second);
   L.apart_o = take((size_t)n_parts_max * dq * 4);
   L.apart_ml = take((size_t)n_parts_max * c.n_q_heads * 2 * 4);
   L.total = off;
@@ -1073,9 +1093,7 @@ extern "C" ps_status ps_layer_create(const ps_layer_cfg* c, ps_layer** out) {
   PS_TRY
   if (ps_status rc = check_cfg(c)) return rc;
   if (!out) return fail(PS_E_INVALID, "null out");
-  ps_layer* L = new ps_layer;
-  L->cfg = *c;
-  *out = L;
+  *out = new ps_layer(*c);
   return PS_OK;
   PS_CATCH
 }
@@ -1090,12 +1108,33 @@ extern "C" ps_status ps_layer_destroy(ps_layer* L) {
 extern "C" size_t ps_workspace_bytes(const ps_layer_cfg* c, int32_t max_rows, int32_t max_seqs,
                                      int32_t max_pages_per_seq) {
   if (!c || max_rows < 0 || max_seqs < 0 || max_pages_per_seq < 0) return 0;
-  const size_t mb = meta_bound(*c, max_rows, max_seqs, max_pages_per_seq);
-  const int32_t parts = max_seqs * ((max_pages_per_seq + 7) / 8);
-  return layout(*c, mb, max_rows, parts).total;
+  try {
+    const size_t mb = meta_bound(*c, max_rows, max_seqs, max_pages_per_seq);
+    const int32_t parts = max_seqs * ((max_pages_per_seq + 7) / 8);
+    return layout(*c, mb, max_rows, parts, gemm_room(*c, SplitGemms(*c, max_rows), max_rows)).total;
+  } catch (...) {  // out of host memory
+    return 0;
+  }
 }
 
 namespace {
+
+// Room for split prefill attention's partial results in a layer call, all of
+// it idle while attention runs: the chunk rows of h and m, which nothing holds
+// yet, and the caller stream's GEMM partials, whose last reader was RoPE, take
+// the parts' O; the chunk rows of xn, read by the QKV GEMM before, their bases
+// and sums.
+struct FaRoom {
+  int end[2] = {0, 0};  // slots in h, in h and m
+  int parts = 0;
+};
+FaRoom fa_layer_parts(const ps_layer_cfg& c, int32_t chunk_rows, const GemmRoom& gemm) {
+  const size_t part = fa_part_bytes(c.n_q_heads);
+  const size_t h = (size_t)chunk_rows * c.hidden * 4 / part, m = (size_t)chunk_rows * c.ffn * 2 / part;
+  const size_t g = gemm.main / part;
+  const size_t ml = (size_t)chunk_rows * c.hidden * 2 / fa_part_ml_bytes(c.n_q_heads);
+  return FaRoom{{(int)h, (int)(h + m)}, (int)std::min(h + m + g, ml)};
+}
 
 // Everything a layer call needs besides weights, pool and activations: the
 // call's sequence tables and work lists (uploaded once to the workspace head)
@@ -1111,28 +1150,12 @@ struct LayerPlan {
   int32_t n_parts = 0;
   int32_t n_seqs = 0;
   Meta mt;
+  GemmRoom gemm;
+  FaRoom fa_room;  // where the prefill items are split
   WsLayout wl;
 };
 
-// Room for split prefill attention's partial results in a layer call, all of
-// it idle while attention runs: the chunk rows of h and m, which nothing holds
-// yet, and the caller stream's GEMM partials, whose last reader was RoPE, take
-// the parts' O; the chunk rows of xn, read by the QKV GEMM before, their bases
-// and sums.
-struct FaRoom {
-  int end[2];  // slots in h, in h and m
-  int parts;
-};
-FaRoom fa_layer_parts(const ps_layer_cfg& c, int32_t chunk_rows, int32_t rows) {
-  const size_t part = fa_part_bytes(c.n_q_heads);
-  const WsLayout wl = layout(c, 0, rows, 0);
-  const size_t h = (size_t)chunk_rows * c.hidden * 4 / part, m = (size_t)chunk_rows * c.ffn * 2 / part;
-  const size_t g = (wl.gemm_b - wl.gemm) / part;
-  const size_t ml = (size_t)chunk_rows * c.hidden * 2 / fa_part_ml_bytes(c.n_q_heads);
-  return FaRoom{{(int)h, (int)(h + m)}, (int)std::min(h + m + g, ml)};
-}
-
-ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int32_t n_chunk,
+ps_status plan_layer(const ps_layer_cfg& c, const SplitGemms& split, const ps_kv* kv, int32_t phase, int32_t n_chunk,
                      const int32_t* chunk_seqs, const int32_t* chunk_tok, int32_t n_dec, const int32_t* dec_seqs,
                      bool may_split, LayerPlan& P) {
   if (phase < PS_PHASE_PREFILL || phase > PS_PHASE_ANSWER) return fail(PS_E_INVALID, "bad phase");
@@ -1153,6 +1176,7 @@ ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int3
   if (P.rows > 0 && (gemm_check(c.dtype, 0, P.rows, dq + 2 * dkv, d) || gemm_check(c.dtype, 1, P.rows, d, dq) ||
                      gemm_check(c.dtype, 2, P.rows, 2 * c.ffn, d) || gemm_check(c.dtype, 1, P.rows, d, c.ffn)))
     return fail(PS_E_UNSUPPORTED, "GEMM shape not supported by libps");
+  P.gemm = gemm_room(c, split, P.rows);
   P.o_si = P.mt.add(cs.si.data(), cs.si.size() * sizeof(SeqInfo));
   P.o_bt = P.mt.add(cs.bt.data(), cs.bt.size() * 4);
   const std::vector<double> fr = inv_freq(c);
@@ -1162,8 +1186,10 @@ ps_status plan_layer(const ps_layer_cfg& c, const ps_kv* kv, int32_t phase, int3
   if (P.fa) {
     PrefillSplit sp;
     if (may_split)
-      sp = plan_prefill_split(cs.si, n_chunk, c.n_kv_heads * (group_of(c) / 4), c.n_q_heads,
-                              fa_layer_parts(c, P.chunk_rows, P.rows).parts);
+      sp = plan_prefill_split(cs.si, n_chunk, c.n_kv_heads * (group_of(c) / 4), c.n_q_heads, [&] {
+        P.fa_room = fa_layer_parts(c, P.chunk_rows, P.gemm);
+        return P.fa_room.parts;
+      });
     if (!sp.items.empty()) {
       P.n_pitems = (int)sp.items.size();
       P.n_merges = (int)sp.merges.size();
@@ -1330,7 +1356,7 @@ int launch_layer(const ps_layer_cfg& c, const LayerPlan& P, const ps_layer_w* w,
   };
   auto prefill_attn = [&](hipStream_t s) {
     if (P.fa && P.n_merges > 0) {
-      const FaRoom room = fa_layer_parts(c, P.chunk_rows, P.rows);
+      const FaRoom& room = P.fa_room;
       bad |= launch_fa_prefill_split(G, P.n_pitems, P.n_merges, c.n_kv_heads, qr, pool, si, bt,
                                      (const PrefillSplitItem*)(W + P.o_pi), (const PrefillMerge*)(W + P.o_mg),
                                      FaPartials{{(float*)h, (float*)m, (float*)gws}, {room.end[0], room.end[1]}, (float*)xn}, o, scale_log2, s);
@@ -1446,15 +1472,15 @@ ps_status run_layer(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, 
     return fail(PS_E_INVALID, "layer and KV pool configurations differ");
   if (ps_status rc = check_layer(kv, layer)) return rc;
   LayerPlan P;
-  if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
+  if (ps_status rc = plan_layer(c, L->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
   if (P.rows == 0) return PS_OK;
   if (!x_in || !x_out) return fail(PS_E_INVALID, "null activation pointer");
   if (ps_status rc = check_aligned({x_in, x_out})) return rc;
-  P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+  P.wl = layout(c, P.mt.size(), P.rows, P.n_parts, P.gemm);
   if (P.n_merges > 0 && ws_bytes < P.wl.total) {  // no room for the longer work list: the unsplit walk
     P = LayerPlan{};
-    if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
-    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+    if (ps_status rc = plan_layer(c, L->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
+    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts, P.gemm);
   }
   if (ps_status rc = check_ws(ws, ws_bytes, P.wl.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
@@ -1508,7 +1534,7 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
   if (!same_cfg(c, kv->cfg)) return fail(PS_E_INVALID, "model and KV pool configurations differ");
   if (kv->n_layers < M->n_layers) return fail(PS_E_INVALID, "KV pool has fewer layers than the model");
   LayerPlan P;
-  if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
+  if (ps_status rc = plan_layer(c, M->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
   if (P.rows == 0) return PS_OK;
   if (!tokens || !next) return fail(PS_E_INVALID, "null token pointer");
   if (ps_status rc = check_aligned({logits_out})) return rc;
@@ -1526,13 +1552,13 @@ ps_status run_model(ps_model* M, ps_kv* kv, int32_t phase, int32_t n_chunk, cons
     for (int i = 0; i < n_dec; ++i) last[n_chunk + i] = r + i;
   }
   size_t o_last = P.mt.add(last.data(), last.size() * 4);
-  P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+  P.wl = layout(c, P.mt.size(), P.rows, P.n_parts, P.gemm);
   ModelWs mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out, n_out);
   if (P.n_merges > 0 && ws_bytes < mw.total) {  // no room for the longer work list: the unsplit walk
     P = LayerPlan{};
-    if (ps_status rc = plan_layer(c, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
+    if (ps_status rc = plan_layer(c, M->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
     o_last = P.mt.add(last.data(), last.size() * 4);
-    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts);
+    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts, P.gemm);
     mw = model_layout(c, M->vocab, P.wl.total, P.rows, n_out, n_out);
   }
   if (ps_status rc = check_ws(ws, ws_bytes, mw.total)) return rc;
@@ -1576,8 +1602,7 @@ extern "C" ps_status ps_model_create(const ps_layer_cfg* c, int32_t n_layers, in
   for (int l = 0; l < n_layers; ++l)
     if (ps_status rc = check_weights(&layers[l])) return rc;
   if (ps_status rc = check_aligned({embed, final_norm, lm_head})) return rc;
-  ps_model* M = new ps_model;
-  M->cfg = *c;
+  ps_model* M = new ps_model(*c);
   M->n_layers = n_layers;
   M->vocab = vocab;
   M->embed = embed;
@@ -1599,10 +1624,14 @@ extern "C" ps_status ps_model_destroy(ps_model* M) {
 extern "C" size_t ps_model_workspace_bytes(const ps_layer_cfg* c, int32_t vocab, int32_t max_rows, int32_t max_seqs,
                                            int32_t max_pages_per_seq) {
   if (!c || vocab <= 0 || max_rows < 0 || max_seqs < 0 || max_pages_per_seq < 0) return 0;
-  const size_t mb = meta_bound(*c, max_rows, max_seqs, max_pages_per_seq) + align_up(4ull * max_seqs, 256);
-  const int32_t parts = max_seqs * ((max_pages_per_seq + 7) / 8);
-  const WsLayout wl = layout(*c, mb, max_rows, parts);
-  return model_layout(*c, vocab, wl.total, max_rows, max_seqs, std::min(max_seqs, 64)).total;
+  try {
+    const size_t mb = meta_bound(*c, max_rows, max_seqs, max_pages_per_seq) + align_up(4ull * max_seqs, 256);
+    const int32_t parts = max_seqs * ((max_pages_per_seq + 7) / 8);
+    const WsLayout wl = layout(*c, mb, max_rows, parts, gemm_room(*c, SplitGemms(*c, max_rows), max_rows));
+    return model_layout(*c, vocab, wl.total, max_rows, max_seqs, std::min(max_seqs, 64)).total;
+  } catch (...) {  // out of host memory
+    return 0;
+  }
 }
 
 extern "C" ps_status ps_model_prefill(ps_model* M, ps_kv* kv, int32_t n_seqs, const int32_t* seqs,
@@ -1797,7 +1826,7 @@ extern "C" ps_status ps_op_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, c
     const size_t fixed = mt.size() + 2 * align_up(sizeof(PrefillSplitItem) * 3 * compute_units(), 256) + 1024;
     if (ws_bytes > fixed)
       sp = plan_prefill_split(cs.si, cs.si.size(), c.n_kv_heads * (group_of(c) / 4), c.n_q_heads,
-                              (int)std::min<size_t>((ws_bytes - fixed) / (part + ml), 1 << 20));
+                              [&] { return (int)std::min<size_t>((ws_bytes - fixed) / (part + ml), 1 << 20); });
     if (!sp.items.empty()) {
       o_pi = mt.add(sp.items.data(), sp.items.size() * sizeof(PrefillSplitItem));
       o_mg = mt.add(sp.merges.data(), sp.merges.size() * sizeof(PrefillMerge));

@@ -463,23 +463,28 @@ static double tile_cost(const TileCfg& t, int M, int N, int K, int S) {
   return std::max(work, stream) + 0.3 * std::min(work, stream) + (S > 1 ? (double)S * rows * N * 8.0 / 6.0e6 : 0.0);
 }
 
+// The most K splits a tile launch may take: 4, of at least 16 stages each, and no
+// more of them than fill one round of 256x256 tiles (two above 2048 rows, where an
+// unsplit launch ends in a nearly empty round: down at 2257 rows 295 us unsplit,
+// 287 with its reduce in two splits); that bounds the partials at 256 KiB per tile
+// and split.
+static int tile_most_splits(int M, int N, int K) {
+  const long tiles256 = (long)((M + 255) / 256) * (N / 256), fit = (M > 2048 ? 2 : 1) * compute_units();
+  int S = 1;
+  while (S < 4 && K / tile::BK / (S + 1) >= 16 && tiles256 * (S + 1) <= fit) ++S;
+  return S;
+}
+
 // The cheapest tile shape and, up to max_splits, K splits. SwiGLU pairs a
-// gate and an up block within a wave, so its tiles are at least 128 wide. At
-// most 4 splits of at least 16 stages each, and no more of them than fill one
-// round of 256x256 tiles (two above 2048 rows, where an unsplit launch ends in
-// a nearly empty round: down at 2257 rows 295 us unsplit, 287 with its reduce
-// in two splits); that bounds the partials at 256 KiB per tile and split. The
+// gate and an up block within a wave, so its tiles are at least 128 wide. The
 // outputs of an unsplit launch do not depend on the tile shape: each is one
 // chain of the same MFMAs over K.
 TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu, double* cost) {
   TilePlan best{0, 1};
   if (cost) *cost = 0;
   if (M <= skinny::MAXM || N % 256 || K % tile::BK) return best;
-  const long tiles256 = (long)((M + 255) / 256) * (N / 256);
-  const int T = K / tile::BK;
   double best_cost = 0;
-  for (int S = 1; S <= std::min(max_splits, 4); ++S) {
-    if (S > 1 && (T / S < 16 || tiles256 * S > (M > 2048 ? 2 : 1) * compute_units())) break;
+  for (int S = 1, most = std::min(max_splits, tile_most_splits(M, N, K)); S <= most; ++S) {
     for (int i = 0; i < kTileCfgCount; ++i) {
       if (swiglu && kTileCfgs[i].qn % 2) continue;
       const double c = tile_cost(kTileCfgs[i], M, N, K, S);
@@ -520,15 +525,23 @@ static int tile_columns(int M, int N, int K, bool swiglu, const TilePlan& whole,
 
 int gemm_tile_splits(int M, int N, int K) { return gemm_tile_plan(M, N, K, 4, false).s; }
 
-size_t gemm_tile_partials_bound(int max_rows, int N, int K) {
-  size_t b = 0;
-  for (int m = 64;; m += 64) {
-    const int mm = std::min(m, max_rows);
-    const int S = gemm_tile_splits(mm, N, K);
-    if (S > 1) b = std::max(b, (size_t)S * mm * N * sizeof(float));
-    if (mm == max_rows) break;
+TilePartials::TilePartials(int N, int K, int max_rows) : n_(N), k_(K) {
+  if (N <= 0 || N % 256 || K % tile::BK) return;
+  // past as many rows nothing is split: two splits would take more than two rounds
+  const long last = std::min<long>(max_rows, 256L * (compute_units() / (N / 256)));
+  rows_.assign(2, 0);  // up to 64 rows: the skinny path
+  for (int m = 128; m <= last; m += 64) {
+    const int S = gemm_tile_splits(m, N, K);
+    rows_.push_back(std::max(rows_.back(), S > 1 ? S * m : 0));
   }
-  return b;
+}
+
+size_t TilePartials::bytes(int max_rows) const {
+  if (rows_.empty() || max_rows <= skinny::MAXM) return 0;
+  int rows = rows_[std::min<size_t>(max_rows / 64, rows_.size() - 1)];
+  if (max_rows % 64)
+    if (const int S = gemm_tile_splits(max_rows, n_, k_); S > 1) rows = std::max(rows, S * max_rows);
+  return (size_t)rows * n_ * sizeof(float);
 }
 
 // Tile rows walked per group (see the kernel). Few rows (up to ~2300): groups

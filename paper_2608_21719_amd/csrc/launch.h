@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include <vector>
+
 #include "common.h"
 
 namespace ps {
@@ -120,8 +122,21 @@ TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu, double
 // consumer sums: chosen to cut the launch's rounds over the compute units,
 // weighed against the partials' traffic. 1 for the skinny path.
 int gemm_tile_splits(int M, int N, int K);
-// Largest partial bytes gemm_tile_splits leads to for any M <= max_rows.
-size_t gemm_tile_partials_bound(int max_rows, int N, int K);
+// Partial bytes that gemm_tile_splits leads to for M rows or fewer. The split
+// count is constant between multiples of 64 rows, so a table of those, made
+// once for the shape, and M's own plan are enough (8B layer call, host time of
+// its planning with every multiple planned anew / so: 10.4 / 4.0 us at 389 rows,
+// 33 / 6.6 at 2048, 118 / 16 at 16384).
+class TilePartials {
+ public:
+  // for up to max_rows rows
+  TilePartials(int N, int K, int max_rows);
+  size_t bytes(int max_rows) const;
+
+ private:
+  int n_, k_;
+  std::vector<int> rows_;  // [i]: largest splits x rows over 64, 128 .. 64 i rows
+};
 // The tile GEMM's K-split partials: fp32 part[S][M][N] (A W^T over split s's
 // near-equal stage range), summed in split order by the consumer.
 int launch_gemm_tile_split(int M, int N, int K, int S, const void* A, const void* W, float* part, hipStream_t st);
