@@ -513,49 +513,123 @@ struct DecodePlan {
   int32_t n_parts = 0;
 };
 
-// Pages of decode attention's fullest compute unit, from the pages of each work
-// item: the items' n_kv workgroups each go round the units, longest items first,
-// two to a unit, and the rest to whichever unit ends first.
-long fullest_unit_pages(std::vector<long> items, int n_kv) {
-  std::sort(items.begin(), items.end(), std::greater<long>());
-  const size_t groups = std::max(1, compute_units() / std::max(1, n_kv)), resident = std::min(items.size(), 2 * groups);
-  std::vector<long> load(groups, 0);  // units that hold one item's workgroups side by side
-  for (size_t i = 0; i < resident; ++i) load[i % groups] += items[i];
-  if (items.size() > resident) {  // a heap, the emptiest in front
-    std::make_heap(load.begin(), load.end(), std::greater<long>());
-    for (size_t i = resident; i < items.size(); ++i) {
-      std::pop_heap(load.begin(), load.end(), std::greater<long>());
-      load.back() += items[i];
-      std::push_heap(load.begin(), load.end(), std::greater<long>());
-    }
-  }
-  return *std::max_element(load.begin(), load.end());
-}
+// Estimates of decode attention's time over ways to cut the sequences' pages.
+class DecodeCost {
+ public:
+  DecodeCost(const std::vector<long>& pages, int n_kv, bool rope) : pages_(pages), n_kv_(n_kv), rope_(rope) {}
 
-// Microseconds of decode attention where each sequence's pages are cut into
-// splits of at most `split`: the fullest compute unit's pages at the 27 GB/s a
-// unit streams with one workgroup or two, 2 for a round of workgroups, 7 for the
-// combine where a sequence is split, and 8 for RoPE's launch where `rope` (a
-// layer call's decode step) and more than one round leave it outside. Least
-// regret over 1390 batches of 1 to 1000 sequences with 1 to 16 KV heads: the
-// cheapest by this of the splits compared below is 0.5% above the fastest of them
-// on average, in layer calls 0.05%.
-double decode_us(const std::vector<long>& pages, long split, int n_kv, bool rope) {
-  std::vector<long> items;
-  bool cut = false;
-  for (long p : pages) {
-    const long ns = (p + split - 1) / split;
-    cut = cut || ns > 1;
-    for (long k = 0; k < ns; ++k) items.push_back((k + 1) * p / ns - k * p / ns);
+  // Microseconds where each sequence's pages are cut into splits of at most
+  // `split`: the fullest compute unit's pages at the 27 GB/s a unit streams with
+  // one workgroup or two, 2 for a round of workgroups, 7 for the combine where a
+  // sequence is split, and 8 for RoPE's launch where `rope` (a layer call's decode
+  // step) and more than one round leave it outside. Least regret over 1390 batches
+  // of 1 to 1000 sequences with 1 to 16 KV heads: the cheapest by this of the
+  // splits compared below is 0.5% above the fastest of them on average, in layer
+  // calls 0.05%.
+  double us(long split) {
+    const long items = cut(split);
+    const double rounds = (double)items * n_kv_ / (2.0 * compute_units());
+    constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kUnit = 27.0e3;  // bytes, bytes per us
+    return fullest_unit_pages() * kPageBytes / kUnit + 2.0 * rounds + (items > (long)pages_.size() ? 7.0 : 0.0) +
+           (rope_ && rounds > 1.0 ? 8.0 : 0.0);
   }
-  const double rounds = (double)items.size() * n_kv / (2.0 * compute_units());
-  constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kUnit = 27.0e3;  // bytes, bytes per us
-  return fullest_unit_pages(std::move(items), n_kv) * kPageBytes / kUnit + 2.0 * rounds + (cut ? 7.0 : 0.0) +
-         (rope && rounds > 1.0 ? 8.0 : 0.0);
-}
+
+ private:
+  struct Run {  // `n` work items or compute units' shares, of `pages` pages each
+    long pages, n;
+    bool operator>(const Run& o) const { return pages > o.pages; }
+  };
+
+  // The work items, longest first: each sequence's ns splits have two lengths at
+  // most. Short splits are counted by length (sorting 64 sequences' took 2 us of a
+  // layer call's host time). Returns their number.
+  long cut(long split) {
+    long items = 0;
+    const bool by_length = split <= 512;
+    runs_.clear();
+    if (by_length) count_.assign(split + 1, 0);
+    auto add = [&](long len, long n) {
+      if (n == 0) return;
+      if (by_length) count_[len] += n;
+      else runs_.push_back(Run{len, n});
+    };
+    for (long p : pages_) {
+      const long ns = (p + split - 1) / split, longer = p % ns;
+      items += ns;
+      add(p / ns + 1, longer);
+      add(p / ns, ns - longer);
+    }
+    if (!by_length) std::sort(runs_.begin(), runs_.end(), std::greater<Run>());
+    for (long len = by_length ? split : 0; len > 0; --len)
+      if (count_[len]) runs_.push_back(Run{len, count_[len]});
+    return items;
+  }
+
+  // Pages of the fullest compute unit: the items' n_kv workgroups each go round
+  // the units, longest items first, two to a unit, and the rest to whichever unit
+  // ends first. Units that hold one item's workgroups side by side count once, and
+  // those with equal loads together.
+  long fullest_unit_pages() {
+    const long units = std::max(1, compute_units() / std::max(1, n_kv_));
+    struct Cursor {
+      const std::vector<Run>& r;
+      size_t i = 0;
+      long left;  // of run i
+      explicit Cursor(const std::vector<Run>& r) : r(r), left(r.empty() ? 0 : r[0].n) {}
+      bool end() const { return i == r.size(); }
+      void take(long n) {
+        while (n > 0 && !end()) {
+          const long m = std::min(n, left);
+          n -= m;
+          if ((left -= m) == 0 && ++i < r.size()) left = r[i].n;
+        }
+      }
+    } one(runs_), two(runs_);
+    two.take(units);
+    load_.clear();
+    for (long u = 0; u < units && !one.end();) {
+      long m = std::min(units - u, one.left);
+      long pages = one.r[one.i].pages;
+      if (!two.end()) {
+        m = std::min(m, two.left);
+        pages += two.r[two.i].pages;
+      }
+      load_.push_back(Run{pages, m});
+      one.take(m);
+      two.take(m);
+      u += m;
+    }
+    if (!two.end()) {  // a heap, the emptiest in front
+      std::make_heap(load_.begin(), load_.end(), std::greater<Run>());
+      while (!two.end()) {
+        std::pop_heap(load_.begin(), load_.end(), std::greater<Run>());
+        Run& e = load_.back();
+        const long m = std::min(e.n, two.left), pages = e.pages + two.r[two.i].pages;
+        const Run rest{e.pages, e.n - m};
+        e = Run{pages, m};
+        std::push_heap(load_.begin(), load_.end(), std::greater<Run>());
+        if (rest.n > 0) {
+          load_.push_back(rest);
+          std::push_heap(load_.begin(), load_.end(), std::greater<Run>());
+        }
+        two.take(m);
+      }
+    }
+    long most = 0;
+    for (const Run& r : load_) most = std::max(most, r.pages);
+    return most;
+  }
+
+  const std::vector<long>& pages_;
+  const int n_kv_;
+  const bool rope_;
+  std::vector<Run> runs_, load_;
+  std::vector<long> count_;
+};
 
 int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_kv, bool rope) {
   std::vector<long> pages;
+  pages.reserve(si.size() - first);
   long total = 0, max_pages = 8;
   for (size_t b = first; b < si.size(); ++b) {
     pages.push_back((si[b].kv_before + si[b].n_new + 15) / 16);
@@ -600,10 +674,11 @@ int32_t choose_split_pages(const std::vector<SeqInfo>& si, size_t first, int n_k
   // 48 123 / 141; 64 of 1024 to 4096 111 / 123; 32 of 300 15 / 9.
   if ((long)pages.size() <= target_items) {
     const long base = sp, whole = (max_pages + 3) / 4 * 4;
-    double best = decode_us(pages, base, n_kv, rope);
+    DecodeCost cost(pages, n_kv, rope);
+    double best = whole > base ? cost.us(base) : 0.0;
     for (long c : {16L, whole}) {
-      if (c <= base) continue;
-      const double us = decode_us(pages, c, n_kv, rope);
+      if (c <= base || c > whole) continue;
+      const double us = cost.us(c);
       if (us < best) best = us, sp = c;
     }
   }

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2608_21719_amd import binding as B
-from synth.configs import CONFIGS
+from synth.configs import CONFIGS, LayerShape
 
 HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "ps.h")
 FAKE_POOL = 0x10000  # never dereferenced by host-only calls
@@ -243,6 +243,32 @@ def test_planning_a_long_prefill_costs_little_more_than_a_short_one():
         return min(t)
 
     assert best(4096) < 5 * best(64)
+
+
+def test_planning_a_decode_step_costs_little_more_with_more_splits():
+    """Host time of a decode step's planning, 64 sequences of 1000 to 4000 tokens: with one KV head eight times as many
+    splits are planned and weighed, 1.4 times the time in all (22 us for 16); 2.7 times where each split is weighed by
+    itself."""
+    import time
+    from ctypes import byref, c_void_p
+
+    def best(n_kv):
+        cfg = B.make_cfg(LayerShape(2048, 16, n_kv, 128, 5632, 1e-5, 1e4, "bf16"))
+        kv, layer = B.KV(cfg, 1, 64 * 251, 64, 251, FAKE_POOL, 0), B.Layer(cfg)
+        seqs = [kv.open() for _ in range(64)]
+        for i, q in enumerate(seqs):
+            kv.alloc(q, 4001)
+            kv.commit([q], [1000 + (i * 1237) % 3000])
+        ids, w, p, t = B.ints(seqs), B.LayerW(*[0x10000] * 6), c_void_p(0x10000), []
+        for _ in range(500):
+            t0 = time.perf_counter()
+            rc = B.lib.ps_decode_step(layer.h, byref(w), kv.h, 0, B.PS_PHASE_ANSWER, 64, ids, p, p, p, 0, None)
+            t.append(time.perf_counter() - t0)
+            assert rc == B.PS_E_INVALID
+        assert "workspace too small" in B.last_error()
+        return min(t)
+
+    assert best(1) < 2 * best(8)
 
 
 def test_decode_run_needs_a_current_plan_and_its_workspace():
