@@ -384,6 +384,18 @@ ps_status ps_mixed_step(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t lay
                         const int32_t* dec_seqs, const void* x_in, void* x_out, void* ws,
                         size_t ws_bytes, void* stream);
 
+/* What a layer call would do with these sequences as they are now and a
+ * workspace of ws_bytes (ps_prefill: n_dec 0): host-only, launches nothing.
+ * Results are the same whichever way a call takes, up to rounding. */
+typedef struct ps_step_plan {
+  int32_t forks;       /* 1: the decode rows go to the second stream (ps_mixed_step) */
+  int32_t split_walks; /* 32-row query tiles whose walk over the keys is split over workgroups */
+  int32_t o_splits;    /* K splits of the O projection's tile GEMM (over the chunk rows where the call forks) */
+} ps_step_plan;
+ps_status ps_step_plan_query(ps_layer* L, ps_kv* kv, int32_t n_chunk, const int32_t* chunk_seqs,
+                             const int32_t* chunk_tok, int32_t n_dec, const int32_t* dec_seqs, size_t ws_bytes,
+                             ps_step_plan* out);
+
 /* ------------------------------------------------------------------ model
  * A stack of n_layers layers (bf16) with token embedding, final RMSNorm,
  * LM head and greedy decoding, as served for the paper's 70B-class models

@@ -60,6 +60,10 @@ DVFS_LOCK_FN = ctypes.CFUNCTYPE(c_int32, c_void_p, c_int32)
 DVFS_LIMIT_FN = ctypes.CFUNCTYPE(c_int32, c_void_p, c_int32)
 
 
+class StepPlan(ctypes.Structure):
+    _fields_ = [("forks", c_int32), ("split_walks", c_int32), ("o_splits", c_int32)]
+
+
 class LayerW(ctypes.Structure):
     _fields_ = [("attn_norm", c_void_p), ("w_qkv", c_void_p), ("w_o", c_void_p), ("ffn_norm", c_void_p),
                 ("w_gate_up", c_void_p), ("w_down", c_void_p)]
@@ -130,6 +134,7 @@ _SIGS = {
     "ps_prefill": (_I, [_P, POINTER(LayerW), _P, _I, _I, _IP, _IP, _P, _P, _P, c_size_t, _P]),
     "ps_decode_step": (_I, [_P, POINTER(LayerW), _P, _I, _I, _I, _IP, _P, _P, _P, c_size_t, _P]),
     "ps_mixed_step": (_I, [_P, POINTER(LayerW), _P, _I, _I, _IP, _IP, _I, _IP, _P, _P, _P, c_size_t, _P]),
+    "ps_step_plan_query": (_I, [_P, _P, _I, _IP, _IP, _I, _IP, c_size_t, POINTER(StepPlan)]),
     "ps_op_rmsnorm": (_I, [_I, _I, _I, _I, _I, _P, _P, c_float, _P, _P]),
     "ps_op_gemm_workspace_bytes": (c_size_t, [_I, _I, _I, _I]),
     "ps_op_gemm": (_I, [_I, _I, _I, _I, _I, _I, _I, _P, _P, _P, _P, _P, c_size_t, _P]),
@@ -457,6 +462,12 @@ class Layer:
         check(lib.ps_mixed_step(self.h, ctypes.byref(w), kv.h, layer, len(chunk_seqs), ints(chunk_seqs),
                                 ints(chunk_tok), len(dec_seqs), ints(dec_seqs), ptr(x_in), ptr(x_out), ptr(ws),
                                 ws.numel() * ws.element_size(), stream_handle(stream)))
+
+    def step_plan(self, kv: KV, chunk_seqs, chunk_tok, dec_seqs, ws_bytes) -> StepPlan:
+        out = StepPlan()
+        check(lib.ps_step_plan_query(self.h, kv.h, len(chunk_seqs), ints(chunk_seqs), ints(chunk_tok), len(dec_seqs),
+                                     ints(dec_seqs), ws_bytes, ctypes.byref(out)))
+        return out
 
 
 class Model:

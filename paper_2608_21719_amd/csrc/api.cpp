@@ -1534,6 +1534,19 @@ ps_status check_weights(const ps_layer_w* w) {
   return check_aligned({w->attn_norm, w->w_qkv, w->w_o, w->ffn_norm, w->w_gate_up, w->w_down});
 }
 
+// Lays out the workspace of a planned layer call; without room for a split
+// walk's longer work list the call is planned anew with the whole walk.
+ps_status fit_plan(const ps_layer* L, const ps_kv* kv, int32_t phase, int32_t n_chunk, const int32_t* chunk_seqs,
+                   const int32_t* chunk_tok, int32_t n_dec, const int32_t* dec_seqs, size_t ws_bytes, LayerPlan& P) {
+  P.wl = layout(L->cfg, P.mt.size(), P.rows, P.n_parts, P.gemm);
+  if (P.n_merges == 0 || ws_bytes >= P.wl.total) return PS_OK;
+  P = LayerPlan{};
+  if (ps_status rc = plan_layer(L->cfg, L->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P))
+    return rc;
+  P.wl = layout(L->cfg, P.mt.size(), P.rows, P.n_parts, P.gemm);
+  return PS_OK;
+}
+
 // One layer over n_chunk prefill sequences (chunk_tok rows each) followed by
 // n_dec decode sequences (one row each).
 ps_status run_layer(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, int32_t phase, int32_t n_chunk,
@@ -1551,12 +1564,7 @@ ps_status run_layer(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, 
   if (P.rows == 0) return PS_OK;
   if (!x_in || !x_out) return fail(PS_E_INVALID, "null activation pointer");
   if (ps_status rc = check_aligned({x_in, x_out})) return rc;
-  P.wl = layout(c, P.mt.size(), P.rows, P.n_parts, P.gemm);
-  if (P.n_merges > 0 && ws_bytes < P.wl.total) {  // no room for the longer work list: the unsplit walk
-    P = LayerPlan{};
-    if (ps_status rc = plan_layer(c, L->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, false, P)) return rc;
-    P.wl = layout(c, P.mt.size(), P.rows, P.n_parts, P.gemm);
-  }
+  if (ps_status rc = fit_plan(L, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, ws_bytes, P)) return rc;
   if (ps_status rc = check_ws(ws, ws_bytes, P.wl.total)) return rc;
   hipStream_t st = (hipStream_t)stream;
   AuxStream* aux = nullptr;
@@ -1760,6 +1768,28 @@ extern "C" ps_status ps_mixed_step(ps_layer* L, const ps_layer_w* w, ps_kv* kv, 
   PS_TRY
   return run_layer(L, w, kv, layer, PS_PHASE_THINK, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, x_in, x_out,
                    ws, ws_bytes, stream);
+  PS_CATCH
+}
+
+extern "C" ps_status ps_step_plan_query(ps_layer* L, ps_kv* kv, int32_t n_chunk, const int32_t* chunk_seqs,
+                                        const int32_t* chunk_tok, int32_t n_dec, const int32_t* dec_seqs,
+                                        size_t ws_bytes, ps_step_plan* out) {
+  PS_TRY
+  if (!L || !out) return fail(PS_E_INVALID, "null argument");
+  CHECK_KV(kv);
+  const ps_layer_cfg& c = L->cfg;
+  if (!same_cfg(c, kv->cfg)) return fail(PS_E_INVALID, "layer and KV pool configurations differ");
+  *out = ps_step_plan{0, 0, 1};
+  LayerPlan P;
+  const int32_t phase = n_chunk > 0 ? PS_PHASE_PREFILL : PS_PHASE_ANSWER;
+  if (ps_status rc = plan_layer(c, L->split, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, true, P)) return rc;
+  if (P.rows == 0) return PS_OK;
+  if (ps_status rc = fit_plan(L, kv, phase, n_chunk, chunk_seqs, chunk_tok, n_dec, dec_seqs, ws_bytes, P)) return rc;
+  out->forks = mixed_forks(c, P.chunk_rows, n_dec);
+  out->split_walks = P.n_merges;
+  if (c.dtype == PS_BF16)
+    out->o_splits = gemm_tile_splits(out->forks ? P.chunk_rows : P.rows, c.hidden, c.n_q_heads * c.head_dim);
+  return PS_OK;
   PS_CATCH
 }
 

@@ -221,6 +221,34 @@ def test_workspace_bounds_grow_with_every_argument(vocab):
     growing([B.Layer.workspace_bytes(cfg, 64, 8, n) for n in range(1, 300)])
 
 
+def test_step_plan_query():
+    """The schedule a mixed step would take, without a GPU: forks only where a further tile row costs more than the weights
+    again, split walks only for few rows behind long prefixes and with room for their work list; the same checks as a call."""
+    cfg = B.make_cfg(CONFIGS["llama8b_decode"].shape)
+    kv, layer = B.KV(cfg, 1, 2048, 8, 900, FAKE_POOL, 0), B.Layer(cfg)
+    chunk, decs = kv.open(), [kv.open() for _ in range(3)]
+    kv.alloc(chunk, 13056)
+    for d in decs:
+        kv.alloc(d, 901)
+        kv.commit([d], [900])
+
+    def plan(rows, dec=decs, room=1 << 40):
+        p = layer.step_plan(kv, [chunk] if rows else [], [rows] if rows else [], dec, room)
+        return p.forks, p.split_walks, p.o_splits
+
+    assert plan(64) == (0, 0, 2) and plan(1027) == (0, 0, 1)
+    assert plan(1022) == (1, 0, 1) and plan(1022, []) == (0, 0, 1) and plan(2048) == (1, 0, 1)
+    assert plan(0) == (0, 0, 1) and plan(0, []) == (0, 0, 1)
+    kv.commit([chunk], [12000])
+    assert plan(1023) == (1, 32, 1) and plan(1023, room=0) == (1, 0, 1) and plan(80)[:2] == (0, 3)
+    for bad in (lambda: plan(1100), lambda: plan(80, [chunk]), lambda: plan(80, [99])):
+        with pytest.raises(B.PsError):
+            bad()
+    other = B.Layer(B.make_cfg(CONFIGS["tiny_f32"].shape))
+    with pytest.raises(B.PsError):
+        other.step_plan(kv, [chunk], [8], [], 0)
+
+
 def test_planning_a_long_prefill_costs_little_more_than_a_short_one():
     """Host time of a call's planning (the empty workspace is refused after it, before any launch): 4096 rows plan page
     tables and work lists 64 times as long as 64 rows, 1.9 times the time in all; 16 times with the GEMM plans of every

@@ -79,13 +79,14 @@ def test_prefill_8x2048_sampled_sequences(layer8b):
         normwise_ok(got[(b + 1) * T - 1], ref, f"seq {b} row {T - 1}")
 
 
-def test_prefill_5x416_three_way_k_split(layer8b):
-    """2080 prefill rows: nine 256-row tile rows, so the down GEMM's 144
-    tiles are split three ways in K (432 workgroups, two rounds instead of
-    one at full K) and summed with the residual by the reduce kernel. The
-    last prompt is compared in full, every other prompt on its last row."""
+@pytest.mark.parametrize("T", [416, 480])
+def test_prefill_5_prompts_k_split_above_2048_rows(layer8b, T):
+    """2080 and 2400 prefill rows: the down GEMM is split two and three ways in
+    K, as far as it may be above 2048 rows (two rounds of 256x256 tiles), and
+    summed with the residual by the reduce kernel. The last prompt is compared
+    in full, every other prompt on its last row."""
     wl, sh = layer8b["wl"], layer8b["wl"].shape
-    n, T = 5, 416
+    n = 5
     pool = H.Pool(sh, n * T // 16 + 8, n, T // 16, seed=gen.page_order_seed(wl))
     layer = B.Layer(pool.cfg)
     seqs = [pool.kv.open() for _ in range(n)]
@@ -164,6 +165,7 @@ def _decode_fullsize(layer8b, wl, sample, phase, mixed=False):
         xc = gen.mixed_input(wl, nc * chunk)
         x = np.concatenate([xc, xd])
         out = H.empty((rows, sh.hidden), "bf16")
+        assert layer.step_plan(kv, new, [chunk] * nc, seqs, ws.numel()).forks
         layer.mixed_step(layer8b["dev"].w, kv, 0, new, [chunk] * nc, seqs, H.to_dev(x, "bf16"), out, ws)
     else:
         x = xd
@@ -179,7 +181,7 @@ def _decode_fullsize(layer8b, wl, sample, phase, mixed=False):
         normwise_ok(got[off + b], ref, f"decode seq {b} ctx {ctx[b]}", tol)
     if mixed:
         # every chunk: together they span every tile row of the chunk rows'
-        # K-split O and down launches
+        # launches
         for i in range(nc):
             ref = O.layer_sequence(layer8b["wf"], sh, xf[i * chunk:(i + 1) * chunk])["out"]
             normwise_ok(got[i * chunk:(i + 1) * chunk], ref, f"mixed chunk {i}")
@@ -329,20 +331,22 @@ def test_70b_ragged_decode_and_short_prefill(layer70b):
     normwise_ok(H.to_f64(outp), ref, "prefill 256", layer70b["tol"])
 
 
-def test_70b_forked_mixed_step(layer70b):
-    """A forked mixed step at the 70B shape (G = 8: two flash workgroups per KV
-    head, the capped decode attention over 8 KV heads): a 200-row chunk after
-    a 3000-token cached prefix beside four decode rows. The chunk rows and the
+@pytest.mark.parametrize("n,forks", [(200, 0), (1023, 1)])
+def test_70b_mixed_step_chunk_behind_prefix(layer70b, n, forks):
+    """Mixed steps at the 70B shape (G = 8: two flash workgroups per KV head; the
+    forked one with the capped decode attention over 8 KV heads and the chunk
+    rows' norm on compute units of its own): a chunk after a 3000-token cached
+    prefix beside four decode rows. The chunk rows and the
     K/V they write equal ps_prefill of the same chunk on a second pool with
     the same history, bit for bit; the decode rows and the chunk's first and
     last rows match the oracle."""
     wl = layer70b["wl"]
     sh = wl.shape
-    pre, n = 3000, 200
+    pre = 3000
     decs = [4096, 2000, 17, 900]
     hist_len = [pre] + decs
-    pools = [H.Pool(sh, sum((L + 216) // 16 for L in hist_len) + 8, 8, 260, seed=31 + i) for i in range(2)]
-    ws = [H.workspace(B.Layer.workspace_bytes(p.cfg, 256, 8, 260)) for p in pools]
+    pools = [H.Pool(sh, sum((L + n + 16) // 16 for L in hist_len) + 8, 8, 260, seed=31 + i) for i in range(2)]
+    ws = [H.workspace(B.Layer.workspace_bytes(p.cfg, n + 56, 8, 260)) for p in pools]
     layers = [B.Layer(p.cfg) for p in pools]
     g = torch.Generator(device="cuda").manual_seed(2024)
     kvh = [(torch.randn((L, sh.n_kv, sh.head_dim), generator=g, device="cuda").to(torch.bfloat16),
@@ -357,6 +361,7 @@ def test_70b_forked_mixed_step(layer70b):
             p.kv.commit([s], [L])
             ss.append(s)
         seqs.append(ss)
+    assert layers[0].step_plan(pools[0].kv, seqs[0][:1], [n], seqs[0][1:], ws[0].numel()).forks == forks
     xm = gen.mixed_input(wl, n + len(decs))
     x = H.to_dev(xm, "bf16")
     out_m = H.empty((n + len(decs), sh.hidden), "bf16")

@@ -198,6 +198,7 @@ def test_8b_unforked_mixed_step_matches_oracle(n_chunk, n_dec):
         if i in checked:
             h.oracle(s, xpf[r0:r0 + L])
         r0 += L
+    assert not h.layer.step_plan(h.kv, [c], [n_chunk], decs, h.ws.numel()).forks
     xm = gen.mixed_input(h.wl, n_chunk + n_dec, layer=n_dec)
     xmf = gen.widen(xm, "bf16")
     out = H.empty((n_chunk + n_dec, h.shape.hidden), "bf16")
@@ -210,20 +211,24 @@ def test_8b_unforked_mixed_step_matches_oracle(n_chunk, n_dec):
         check(got[n_chunk + i:n_chunk + i + 1], ref, "bf16", f"unforked decode {i} ({n_chunk} + {n_dec})")
 
 
-def test_8b_forked_mixed_step_chunk_rows_equal_prefill_bit_for_bit(h8):
-    """The forked mixed step (more than 64 chunk rows beside decode rows: the
-    decode rows' attention, O, SwiGLU and down on the second stream, their
-    attention on a capped grid) against ps_prefill of the same chunks on a
-    second pool with the same history: the chunk rows take the same kernels
-    and plans either way, so their output and written K/V must match bit for
-    bit, whatever the decode rows do beside them on the other stream."""
+# (cached prefix, chunk rows) of the chunks: in one pass, and forked, with 1022 chunk rows (the last workgroup of their
+# norm, four rows each, holds two) and 2048
+@pytest.mark.parametrize("chunks,forks", [([(0, 150), (37, 96)], 0), ([(0, 600), (37, 422)], 1),
+                                          ([(0, 512), (37, 1024), (16, 512)], 1)], ids=["one-pass", "1022", "2048"])
+def test_8b_mixed_step_chunk_rows_equal_prefill_bit_for_bit(h8, chunks, forks):
+    """A mixed step (forked: the decode rows' attention, O, SwiGLU and down on
+    the second stream, their attention on a capped grid, the chunk rows' norm on
+    compute units of its own) against ps_prefill of the same chunks on a second
+    pool with the same history: the chunk rows' sums are the same either way, so
+    their output and written K/V must match bit for bit, whatever the decode
+    rows do beside them. The decode rows match the oracle."""
     h = h8
     sh = h.shape
-    chunks = [(0, 150), (37, 96)]   # (cached prefix, chunk rows)
     decs = [700, 1500, 90]          # decode rows' history lengths
     hist = [p for p, _ in chunks] + decs
-    pools = [H.Pool(sh, sum((L + 160) // 16 for L in hist) + 8, 8, 128, seed=5 + i) for i in range(2)]
-    ws = [H.workspace(B.Layer.workspace_bytes(p.cfg, 512, 8, 128)) for p in pools]
+    n_new = [n for _, n in chunks] + [1] * len(decs)
+    pools = [H.Pool(sh, sum((L + n + 16) // 16 for L, n in zip(hist, n_new)) + 8, 8, 128, seed=5 + i) for i in range(2)]
+    ws = [H.workspace(B.Layer.workspace_bytes(p.cfg, 2560, 8, 128)) for p in pools]
     g = torch.Generator(device="cuda").manual_seed(77)
     kvh = [(torch.randn((L, sh.n_kv, sh.head_dim), generator=g, device="cuda").to(torch.bfloat16),
             torch.randn((L, sh.n_kv, sh.head_dim), generator=g, device="cuda").to(torch.bfloat16)) for L in hist]
@@ -248,13 +253,20 @@ def test_8b_forked_mixed_step_chunk_rows_equal_prefill_bit_for_bit(h8):
     xm = gen.mixed_input(h.wl, n_chunk + len(decs))
     x = H.to_dev(xm, "bf16")
     a, b = pools
+    nc, tok = len(chunks), [n for _, n in chunks]
+    assert h.layer.step_plan(a.kv, seqs[0][:nc], tok, seqs[0][nc:], ws[0].numel()).forks == forks
     out_m = H.empty((n_chunk + len(decs), sh.hidden), "bf16")
-    h.layer.mixed_step(h.dev.w, a.kv, 0, seqs[0][:2], [n for _, n in chunks], seqs[0][2:], x, out_m, ws[0])
+    h.layer.mixed_step(h.dev.w, a.kv, 0, seqs[0][:nc], tok, seqs[0][nc:], x, out_m, ws[0])
     out_p = H.empty((n_chunk, sh.hidden), "bf16")
-    h.layer.prefill(h.dev.w, b.kv, 0, seqs[1][:2], [n for _, n in chunks], x[:n_chunk].contiguous(), out_p, ws[1])
+    h.layer.prefill(h.dev.w, b.kv, 0, seqs[1][:nc], tok, x[:n_chunk].contiguous(), out_p, ws[1])
     sync()
     assert torch.equal(out_m[:n_chunk].view(torch.int16), out_p.view(torch.int16)), "chunk rows differ"
-    for (pre, n), sa, sb in zip(chunks, seqs[0][:2], seqs[1][:2]):
+    xf = gen.widen(xm, "bf16")
+    for i, (k, v) in enumerate(kvh[nc:]):
+        r = n_chunk + i
+        ref = O.layer_rows(h.wf, sh, xf[r:r + 1], [0], H.to_f64(k), H.to_f64(v))
+        check(H.to_f64(out_m)[r:r + 1], ref, "bf16", f"decode row {i}")
+    for (pre, n), sa, sb in zip(chunks, seqs[0][:nc], seqs[1][:nc]):
         a.kv.commit([sa], [n])
         b.kv.commit([sb], [n])
         ka = torch.empty((pre + n, sh.n_kv, sh.head_dim), dtype=torch.bfloat16, device="cuda")
@@ -385,28 +397,33 @@ def test_admitted_mixed_batch_matches_oracle():
     assert sched.running() == 0 and h.kv.free_pages() == 200
 
 
-@pytest.mark.parametrize("n", [80, 1024])
-def test_8b_chunk_behind_long_prefix_split_walks(h8, n):
-    """Rows behind 3000 cached tokens: the key walks are split (80 rows), their
-    partial results in the call's own workspace (idle rows of h, m, xn and the
-    GEMM partials). Alone, and as the chunk of a mixed step beside three decode
-    rows, in one pass (80 rows) or forked (1024 rows, which a fourth tile row
-    would follow): the same bits. The workspace a call without the split needs is
-    still accepted and takes the whole walk. All against the oracle."""
+@pytest.mark.parametrize("n,pre,split,forks", [(80, 3000, 1, 0), (1024, 3000, 0, 1), (1023, 12000, 1, 1)])
+def test_8b_chunk_behind_long_prefix_split_walks(h8, n, pre, split, forks):
+    """Rows behind a long cached prefix: the key walks are split (80 rows behind
+    3000 tokens, 1023 behind 12000), their partial results in the call's own
+    workspace (idle rows of h, m, xn and the GEMM partials). Alone, and as the
+    chunk of a mixed step beside three decode rows, in one pass (80 rows) or
+    forked (1023 and 1024 rows, which a fifth tile row would follow; the second
+    stream then writes the decode rows of h, m and xn beside the split walks): the
+    same bits. The workspace a call without the split needs is still accepted and
+    takes the whole walk. All against the oracle."""
     sh, g = h8.shape, torch.Generator(device="cuda").manual_seed(81)
-    pre, decs = 3000, [700, 90, 1500]
+    decs = [700, 90, 1500]
     hist = [pre] + decs
     kvh = [tuple(torch.randn((L, sh.n_kv, sh.head_dim), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
            for L in hist]
-    pools, seqs = [H.Pool(sh, 700, 4, 260, seed=31 + i) for i in range(3)], []
-    nbytes = B.Layer.workspace_bytes(pools[0].cfg, n + len(decs), 4, 260)
+    pages = (pre + n) // 16 + 1
+    pools, seqs = [H.Pool(sh, pages + 500, 4, pages, seed=31 + i) for i in range(3)], []
+    nbytes = B.Layer.workspace_bytes(pools[0].cfg, n + len(decs), 4, pages)
     ws = H.workspace(nbytes)
     for p in pools:
         seqs.append([p.kv.open() for _ in hist])
         for s, L, (k, v) in zip(seqs[-1], hist, kvh):
-            p.kv.alloc(s, L + n)
+            p.kv.alloc(s, L + (n if L == pre else 1))
             p.kv.append(0, [s], [L], k, v, ws)
             p.kv.commit([s], [L])
+    plan = h8.layer.step_plan(pools[0].kv, seqs[0][:1], [n], seqs[0][1:], nbytes)
+    assert (plan.split_walks > 0, plan.forks) == (split, forks)
     xb = gen.mixed_input(h8.wl, n + len(decs))
     x = H.to_dev(xb, "bf16")
     out_m, out_p, out_w = (H.empty((r, sh.hidden), "bf16") for r in (n + len(decs), n, n))
@@ -425,7 +442,8 @@ def test_8b_chunk_behind_long_prefix_split_walks(h8, n):
             lo = mid + 1
     h8.layer.prefill(h8.dev.w, pools[2].kv, 0, seqs[2][:1], [n], x[:n].contiguous(), out_w, ws[:hi])
     sync()
-    if n == 80:
+    assert h8.layer.step_plan(pools[2].kv, seqs[2][:1], [n], [], hi).split_walks == 0
+    if split:
         assert not torch.equal(out_w, out_p), "the smallest workspace was expected to take the whole walk"
     xf = gen.widen(xb, "bf16")
     rows = [0, 31, 32, 63, 64, n - 1]
@@ -436,6 +454,36 @@ def test_8b_chunk_behind_long_prefix_split_walks(h8, n):
     for i, (k, v) in enumerate(kvh[1:]):
         ref = O.layer_rows(h8.wf, sh, xf[n + i:n + i + 1], [0], H.to_f64(k), H.to_f64(v))
         check(H.to_f64(out_m)[n + i:n + i + 1], ref, "bf16", f"decode row {i}")
+
+
+# hidden, query heads, kv heads, ffn, chunk rows (odd: the last workgroup of the norm, two rows each, holds one), K splits
+@pytest.mark.parametrize("hidden,n_q,n_kv,ffn,n,splits", [(1024, 16, 4, 1024, 455, 2), (1536, 24, 6, 2304, 1291, 3),
+                                                          (2048, 32, 8, 5120, 707, 4)])
+def test_forked_mixed_step_with_a_split_o_projection(hidden, n_q, n_kv, ffn, n, splits):
+    """Forked mixed steps (64 decode rows) whose chunk rows' O projection is split in K, its sums and the norm on compute
+    units of their own: the chunk rows' bits are ps_prefill's, which runs the same sums without that; both against the
+    oracle."""
+    sh = LayerShape(hidden, n_q, n_kv, 128, ffn, 1e-5, 500000.0, "bf16")
+    h = Harness(Workload("split_o", 14, sh), n_pages=400, max_seqs=68, max_pages=90, max_rows=n + 1280)
+    ctx = [1 + 3 * (i % 13) for i in range(64)]
+    decs = [h.open(L + 1) for L in ctx]
+    xp = gen.prefill_input(h.wl, sum(ctx))
+    h.prefill(decs, ctx, xp)
+    c, p = h.open(n), h.open(n)
+    plan = h.layer.step_plan(h.kv, [c], [n], decs, h.ws.numel())
+    assert (plan.forks, plan.o_splits) == (1, splits)
+    xm = gen.mixed_input(h.wl, n + 64)
+    x, out_m, out_p = H.to_dev(xm, "bf16"), H.empty((n + 64, hidden), "bf16"), H.empty((n, hidden), "bf16")
+    h.layer.mixed_step(h.dev.w, h.kv, 0, [c], [n], decs, x, out_m, h.ws)
+    h.layer.prefill(h.dev.w, h.kv, 0, [p], [n], x[:n].contiguous(), out_p, h.ws)
+    sync()
+    assert torch.equal(out_m[:n].view(torch.int16), out_p.view(torch.int16)), "chunk rows differ from the plain prefill"
+    got, xf, xpf = H.to_f64(out_m), gen.widen(xm, "bf16"), gen.widen(xp, "bf16")
+    check(got[:n], h.oracle(c, xf[:n]), "bf16", "chunk rows")
+    for i in (0, 1, 31, 63):
+        r0 = sum(ctx[:i])
+        h.oracle(decs[i], xpf[r0:r0 + ctx[i]])
+        check(got[n + i:n + i + 1], h.oracle(decs[i], xf[n + i:n + i + 1]), "bf16", f"decode row {i}")
 
 
 # every group size of the fused RoPE + KV write + attention launch; hidden sets the QKV projection's K splits (1024: none,
