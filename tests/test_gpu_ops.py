@@ -418,19 +418,20 @@ def test_rope_kvwrite(dtype, shape):
 
 # 1769 odd rows: one row per workgroup either way; 3789 odd rows and 1605 rows in whole pages: 16 per workgroup together
 @pytest.mark.parametrize("hist,new", [([0, 5, 300, 32, 0], [7, 16, 41, 900, 805]),
-                                      ([0, 5, 300, 32, 0], [7, 16, 41, 1900, 1825]),
+                                      ([0, 5, 300, 32, 0, 64, 7], [7, 16, 41, 900, 1000, 825, 1000]),
                                       ([0, 48, 16, 100, 0], [1024, 16, 560, 1, 4])])
 @pytest.mark.parametrize("shape", [S8, S70], ids=["8B", "70B"])
 def test_rope_kvwrite_large_batch_equals_per_sequence_calls_bit_for_bit(shape, hist, new):
     """More than 1536 rows in whole pages, or 3584 odd ones, take 16 rows per
     workgroup (groups that fill a page, groups that straddle sequences or pages,
-    a partial last group); each sequence alone takes one row per workgroup.
-    Same bits either way."""
+    a partial last group); each sequence alone, of at most 1536 rows, takes one
+    row per workgroup. Same bits either way."""
     rows = sum(new)
+    assert max(new) <= 1536
     qkv = H.to_dev(rnd((rows, (shape.n_q + 2 * shape.n_kv) * shape.head_dim), "bf16", 43), "bf16")
     ws, res = H.workspace(1 << 22), []
     for together in (True, False):
-        P = H.Pool(shape, 300, 5, 128, seed=6)
+        P = H.Pool(shape, 300, len(hist), 128, seed=6)
         seqs = [P.kv.open() for _ in hist]
         for s, L, n in zip(seqs, hist, new):
             P.kv.alloc(s, L + n)
