@@ -132,7 +132,9 @@ def bench_prefill(torch, B, A, wl, steps, warmup):
     # GEMM window above, then 200 are timed (about 0.1 s in all)
     a_ms = timer(attn_run, iters=max(200, steps), warmup=100)
     tel_attn = observe(attn_run)
-    traffic = measured_traffic("gate_up_gemm_8x2048", "paper_2608_21719_amd/csrc/gemm_tile.h")
+    # the kernel, and the tile order, shape choice, column parts and load hints of its launch
+    traffic = measured_traffic("gate_up_gemm_8x2048", "paper_2608_21719_amd/csrc/gemm_tile.h",
+                               "paper_2608_21719_amd/csrc/k_gemm.hip")
     res = {
         "tok_s": tokens / (ms * 1e-3), "ms_per_step": ms,
         "layer_tflops": (total_gemm + attn) / (ms * 1e-3) / 1e12,
@@ -587,10 +589,11 @@ def observe(run, seconds=None):
     return TEL.observe(run, torch.cuda.synchronize, seconds=seconds)
 
 
-def measured_traffic(kernel_key, source_file):
+def measured_traffic(kernel_key, *source_files):
     """HBM bytes per launch of a kernel from profiles/traffic.json (two rocprof
     --pmc passes, FETCH_SIZE and WRITE_SIZE, scaled by a known-size copy), or
-    None when the kernel's source has changed since the counters were taken."""
+    None when a source file that sets the launch's traffic has changed since the
+    counters were taken (source_sha256: of the files in order)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
@@ -598,8 +601,10 @@ def measured_traffic(kernel_key, source_file):
     rec = json.load(open(path)).get(kernel_key)
     if not rec:
         return None
-    src = os.path.join(ROOT, source_file)
-    if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec.get("source_sha256"):
+    digest = hashlib.sha256()
+    for f in source_files:
+        digest.update(open(os.path.join(ROOT, f), "rb").read())
+    if digest.hexdigest() != rec.get("source_sha256"):
         return None
     return rec["fetch_bytes"] + rec["write_bytes"]
 

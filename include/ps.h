@@ -348,7 +348,9 @@ size_t ps_workspace_bytes(const ps_layer_cfg* cfg, int32_t max_rows, int32_t max
  * x_in [sum n_tok, d] at positions [len_i, len_i + n_tok[i]); its K/V for
  * `layer` are written there (capacity must be reserved) and every row
  * attends causally over positions 0..pos (cached prefix included). x_out
- * [sum n_tok, d]. len is unchanged (call ps_kv_commit). */
+ * [sum n_tok, d]. len is unchanged (call ps_kv_commit). Few rows behind long
+ * prefixes split the walk over their keys (ps_step_plan_query) unless ws is
+ * too small for the longer work list: another order of the same sums. */
 ps_status ps_prefill(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, int32_t n_seqs,
                      const int32_t* seqs, const int32_t* n_tok, const void* x_in, void* x_out, void* ws,
                      size_t ws_bytes, void* stream);
@@ -372,12 +374,13 @@ ps_status ps_decode_step(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t la
  * the split-K decode path for decode rows. Same result as separate
  * ps_prefill and ps_decode_step calls up to rounding.
  * With more than 64 chunk rows and at most 64 decode rows (bf16, d a
- * multiple of 8 up to 8192) the call may fork after the KV write (where
- * one pass of the later GEMMs over all rows would cost more than reading
- * their weights a second time): the decode rows' attention and the rest of their layer (O, SwiGLU and down GEMMs)
- * go to a second stream that the layer handle creates on first use
- * (default priority, on the caller's device), joined back into `stream` by
- * an event before the call returns: the caller sees one stream's ordering.
+ * multiple of 8 up to 8192) the call may fork after the KV write, where one
+ * pass of the later GEMMs over all rows would cost more than reading their
+ * weights a second time (ps_step_plan_query tells): the decode rows'
+ * attention and the rest of their layer (O, SwiGLU and down GEMMs) go to a
+ * second stream that the layer handle creates on first use (default
+ * priority, on the caller's device), joined back into `stream` by an event
+ * before the call returns: the caller sees one stream's ordering.
  * A layer handle is used by one host thread at a time. */
 ps_status ps_mixed_step(ps_layer* L, const ps_layer_w* w, ps_kv* kv, int32_t layer, int32_t n_chunk,
                         const int32_t* chunk_seqs, const int32_t* chunk_tok, int32_t n_dec,
@@ -436,7 +439,7 @@ ps_status ps_op_rmsnorm(int32_t x_dtype, int32_t g_dtype, int32_t y_dtype, int32
                         const void* x, const void* g, float eps, void* y, void* stream);
 
 /* C = epilogue(A W^T): A [M, K] row-major, W [N, K] tiled, both `dtype`
- * (bf16 uses the MFMA path, fp32 a vector path), fp32 accumulation.
+ * (bf16 and fp32 MFMA), fp32 accumulation.
  *   PS_EPI_STORE     C[M, N] (c_dtype)
  *   PS_EPI_RESIDUAL  C[M, N] = R + A W^T, R of r_dtype (R may alias C when
  *                    the dtypes match)
@@ -484,7 +487,10 @@ ps_status ps_op_rope_kvwrite(ps_kv* kv, int32_t layer, int32_t n_seqs, const int
 /* Causal attention of q [rows, n_q, hd] (rows grouped by sequence as in
  * ps_prefill, at positions [len, len + n_tok)) over the sequence's cached
  * keys 0..pos in the pages (the rows' own K/V must already be written).
- * o [rows, n_q * hd]. Uses the prefill kernel. */
+ * o [rows, n_q * hd]. Uses the prefill kernel. Few rows behind long prefixes
+ * are walked by several workgroups each as far as ws has room for their
+ * partial results beside the call's metadata; so the order of a row's sums,
+ * and with it the rounding, depends on ws_bytes. */
 ps_status ps_op_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, const int32_t* seqs,
                           const int32_t* n_tok, const void* q, void* o, void* ws, size_t ws_bytes,
                           void* stream);

@@ -1312,11 +1312,13 @@ ps_status stage_meta(ps_kv* kv, const Meta& mt, void* ws, UploadJob* job) {
 // fork reads them a second time for the decode rows, mostly beside the chunk
 // rows' GEMMs. It pays where the decode rows would cost the tile launches a
 // further tile row or round: where that comes to more than 0.9 of the second
-// weight stream. Measured, one pass / forked, 8B (us): 300 + 32 rows 315 / 372,
-// 800 + 32 522 / 553, 1500 + 32 747 / 763, but 2048 + 32 1020 / 944 and, with
-// contexts of 13000, 1207 / 1090; 70B 600 + 32 1236 / 1440, 1024 + 32 1945 /
-// 1836. How long the decode attention is does not move the line: it overlaps
-// little either way.
+// weight stream. Measured with contexts of 1000 and of 13000, one pass / forked,
+// 8B (us): 800 + 32 rows 437 / 502 and 675 / 759, 1500 + 32 651 / 715 and 885 /
+// 917, 1900 + 32 786 / 865 and 1008 / 1122, but 2048 + 32 928 / 880 and 1144 /
+// 1047; with 8000, 1500 + 64 1015 / 970; 70B, 1000: 600 + 32 1145 / 1353, 1024 +
+// 32 1813 / 1674. Long attention moves the difference by up to 50 us either way,
+// but none of 47 steps (4 to 64 decode rows, 128 to 3000 chunk rows) across the
+// line.
 bool mixed_forks(const ps_layer_cfg& c, int32_t chunk_rows, int32_t n_dec) {
   if (c.dtype != PS_BF16 || c.hidden % 8 || c.hidden > 8192 || n_dec <= 0 || n_dec > 64 || chunk_rows <= 64) return false;
   const int d = c.hidden, dq = c.n_q_heads * c.head_dim;

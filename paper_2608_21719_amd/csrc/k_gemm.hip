@@ -499,9 +499,9 @@ TilePlan gemm_tile_plan(int M, int N, int K, int max_splits, bool swiglu, double
 // parts: as many columns as whole rounds of a large tile take, then the rest in
 // the shape that is cheapest for them. Returns the first part's columns (0: one
 // launch) with both shapes. Taken where the cost model promises 6%, another
-// launch's 4 us included (us, one launch -> two): N 28672, K 4096 at 700 rows 168
-// -> 151, at 1800 378 -> 357, at 3000 558 -> 539; N 57344, K 8192 at 1000 749 ->
-// 706; N 10240, K 8192 at 2048 293 -> 271; N 6144, K 4096 at 3500 164 -> 143.
+// launch's 4 us included (us, one launch -> two): N 28672, K 4096 at 700 rows 169
+// -> 151, at 1800 378 -> 356, at 3000 555 -> 535; N 57344, K 8192 at 1000 747 ->
+// 702; N 10240, K 8192 at 2048 296 -> 268; N 6144, K 4096 at 3500 144 -> 139.
 // Where it promised 4 to 5% it gave 1 or 2, once -2. Beside another stream's
 // attention it loses (mixed step of 4 x 512 + 32 rows 1074 -> 1081).
 static int tile_columns(int M, int N, int K, bool swiglu, const TilePlan& whole, TilePlan* first, TilePlan* rest) {

@@ -291,7 +291,8 @@ __device__ __forceinline__ int find_seq_wave(const SeqInfo* __restrict__ si, int
 // One row per workgroup: rotate the row's q and k heads (rotate-half, angle
 // pos * inv_freq[j] evaluated in fp64), write q to q_out and k, v into the
 // row's page slot. bf16 rows move four pairs per thread with 8-byte accesses;
-// up to 1536 rows (above, rope_kvwrite_rows_kernel takes 16 at a time).
+// up to 1536 or 3584 rows (above, rope_kvwrite_rows_kernel takes 16 at a time:
+// see launch_rope_kvwrite).
 // PART (bf16, decode): the QKV row is not materialised; it is the sum of the
 // GEMM's S split-K partials (fp32 [S][rows][n_q + 2 n_kv][hd]) in split order,
 // rounded to bf16, exactly what the separate reduce kernel would have stored.

@@ -104,3 +104,28 @@ def test_context_length_laws(name):
         assert L.min() >= 1024 and L.max() <= 4096
     else:
         assert L.min() >= 4096 and L.max() <= 32768
+
+
+@pytest.mark.parametrize("kernel,sets_it", [("gate_up_gemm_8x2048", "k_gemm.hip"), ("gate_up_gemm_8x2048", "gemm_tile.h"),
+                                            ("decode_attention_b64", "k_attn_decode.hip")])
+def test_stored_traffic_goes_stale_with_the_sources_that_set_it(kernel, sets_it, tmp_path, monkeypatch):
+    import hashlib
+    import re
+
+    import bench
+    call = re.search(r'measured_traffic\("%s",([^)]*)\)' % kernel, open(bench.__file__).read()).group(1)
+    files = re.findall(r'"([^"]+)"', call)
+    digest = hashlib.sha256()
+    for f in files:
+        (tmp_path / f).parent.mkdir(parents=True, exist_ok=True)
+        (tmp_path / f).write_bytes(open(os.path.join(bench.ROOT, f), "rb").read())
+        digest.update((tmp_path / f).read_bytes())
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / "profiles" / "traffic.json").write_text(json.dumps(
+        {kernel: {"fetch_bytes": 3, "write_bytes": 4, "source_sha256": digest.hexdigest()}}))
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.measured_traffic(kernel, *files) == 7
+    changed = [f for f in files if os.path.basename(f) == sets_it]
+    assert changed, (sets_it, files)
+    (tmp_path / changed[0]).write_text("// edited\n")
+    assert bench.measured_traffic(kernel, *files) is None
