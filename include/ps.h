@@ -503,9 +503,9 @@ ps_status ps_op_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, const int32_
  * library choice: one split per sequence where that is estimated to be
  * fastest (sequences that load the compute units evenly and need no combine
  * then, or a batch that alone exceeds 1024 workgroups); else the smallest
- * multiple of 4 pages, at least 8 (16 where that still fills the chip), that
- * keeps the workgroups (splits times KV heads) within about 1024, two full
- * rounds of the chip.
+ * multiple of 4 pages, at least 8, that keeps the workgroups (splits times KV
+ * heads) within about 1024, two full rounds of the chip, or 16 pages where
+ * the fewer splits are estimated to be faster.
  * PS_E_UNSUPPORTED when the splits come to more than 65535
  * work items (one grid row each). */
 ps_status ps_op_decode_attention(ps_kv* kv, int32_t layer, int32_t n_seqs, const int32_t* seqs,

@@ -519,18 +519,19 @@ class DecodeCost {
   DecodeCost(const std::vector<long>& pages, int n_kv, bool rope) : pages_(pages), n_kv_(n_kv), rope_(rope) {}
 
   // Microseconds where each sequence's pages are cut into splits of at most
-  // `split`: the fullest compute unit's pages at the 27 GB/s a unit streams with
-  // one workgroup or two, 2 for a round of workgroups, 7 for the combine where a
-  // sequence is split, and 8 for RoPE's launch where `rope` (a layer call's decode
-  // step) and more than one round leave it outside. Least regret over 1390 batches
-  // of 1 to 1000 sequences with 1 to 16 KV heads: the cheapest by this of the
-  // splits compared below is 0.5% above the fastest of them on average, in layer
-  // calls 0.05%.
+  // `split`: the fullest compute unit's pages at the 29 GB/s a unit streams with
+  // one workgroup or two, 2.5 for a round of workgroups, 4 for the combine where
+  // a sequence is split and 0.2 for each split of the longest, and 8 for RoPE's
+  // launch where `rope` (a layer call's decode step) and more than one round leave
+  // it outside. Fitted over 5065 batches of 1 to 96 sequences of 20 to 9000 tokens
+  // with 1 to 32 KV heads; over 4180 others the cheapest by this of the splits
+  // compared below is 0.1% above the fastest of them on average in layer calls
+  // (one KV head 0.3%) and in the attention alone 0.1%, at worst 8%.
   double us(long split) {
     const long items = cut(split);
     const double rounds = (double)items * n_kv_ / (2.0 * compute_units());
-    constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kUnit = 27.0e3;  // bytes, bytes per us
-    return fullest_unit_pages() * kPageBytes / kUnit + 2.0 * rounds + (items > (long)pages_.size() ? 7.0 : 0.0) +
+    constexpr double kPageBytes = 2.0 * PS_PAGE_TOKENS * 128 * 2, kUnit = 28.7e3;  // bytes, bytes per us
+    return fullest_unit_pages() * kPageBytes / kUnit + 2.5 * rounds + (most_splits_ > 1 ? 4.0 + 0.2 * most_splits_ : 0.0) +
            (rope_ && rounds > 1.0 ? 8.0 : 0.0);
   }
 
@@ -547,6 +548,7 @@ class DecodeCost {
     long items = 0;
     const bool by_length = split <= 512;
     runs_.clear();
+    most_splits_ = 1;
     if (by_length) count_.assign(split + 1, 0);
     auto add = [&](long len, long n) {
       if (n == 0) return;
@@ -556,6 +558,7 @@ class DecodeCost {
     for (long p : pages_) {
       const long ns = (p + split - 1) / split, longer = p % ns;
       items += ns;
+      most_splits_ = std::max(most_splits_, ns);
       add(p / ns + 1, longer);
       add(p / ns, ns - longer);
     }
@@ -623,6 +626,7 @@ class DecodeCost {
   const std::vector<long>& pages_;
   const int n_kv_;
   const bool rope_;
+  long most_splits_ = 1;  // of one sequence
   std::vector<Run> runs_, load_;
   std::vector<long> count_;
 };

@@ -299,6 +299,47 @@ def test_planning_a_decode_step_costs_little_more_with_more_splits():
     assert best(1) < 2 * best(8)
 
 
+# attention alone, 8 KV heads (us, 8 pages / 16 / one split): two sequences of 4960 tokens 20.4 / 16.8 / 66.5, one of 3950
+# 14.2 / 12.5 / 52, three of 1000 9.9 / 11 / 17; 64 of 350 fill the chip in one split each
+@pytest.mark.parametrize("lens,split", [([4950] * 2, 16), ([3950], 16), ([1000] * 3, 8), ([350] * 64, 1000)])
+def test_decode_attention_split_choice(lens, split):
+    """The choice, told by the workspace that a plan asks for (one partial result per split), against plans of given splits."""
+    cfg = B.make_cfg(CONFIGS["llama8b_decode"].shape)
+    kv = B.KV(cfg, 1, 2500, 64, 400, FAKE_POOL, 0)
+    seqs = [kv.open() for _ in lens]
+    for s, n in zip(seqs, lens):
+        kv.alloc(s, n + 1)
+        kv.commit([s], [n])
+
+    def needs(pages):
+        assert B.lib.ps_op_decode_plan(kv.h, len(seqs), B.ints(seqs), pages, 0x10000, 0, None) == B.PS_E_INVALID
+        return int(re.search(r"too small: 0 < (\d+)", B.last_error()).group(1))
+
+    assert needs(0) == needs(split)
+    assert all(needs(0) != needs(p) for p in (8, 16, 1000) if p != split)
+
+
+@pytest.mark.parametrize("n_seqs", [1, 2, 4, 8])
+def test_decode_step_splits_short_contexts_from_about_400_tokens(n_seqs):
+    """A layer's decode step of a few sequences: one split up to about 20 pages, then 8-page splits (8B shape, us, one split
+    / 8 pages: 300 tokens 92.5 / 94.0, 400 93.9 / 92.6, 500 95.7 / 93.4; four sequences of 500 95.9 / 93.7)."""
+    from ctypes import byref, c_void_p
+    cfg = B.make_cfg(CONFIGS["llama8b_decode"].shape)
+    w, p, needs = B.LayerW(*[0x10000] * 6), c_void_p(0x10000), {}
+    for ctx in (100, 300, 450, 500):
+        kv, layer = B.KV(cfg, 1, 64 * n_seqs, n_seqs, 64, FAKE_POOL, 0), B.Layer(cfg)
+        seqs = [kv.open() for _ in range(n_seqs)]
+        for s in seqs:
+            kv.alloc(s, ctx + 1)
+            kv.commit([s], [ctx])
+        assert B.lib.ps_decode_step(layer.h, byref(w), kv.h, 0, B.PS_PHASE_ANSWER, n_seqs, B.ints(seqs), p, p, p, 0,
+                                    None) == B.PS_E_INVALID
+        needs[ctx] = int(re.search(r"too small: 0 < (\d+)", B.last_error()).group(1))
+    part = 4096 * 4  # bytes of one partial result
+    assert needs[300] - needs[100] < part  # one split each: a longer block table only
+    assert needs[450] - needs[300] > 2 * n_seqs * part and needs[500] - needs[300] > 2 * n_seqs * part
+
+
 def test_decode_run_needs_a_current_plan_and_its_workspace():
     """Host-side checks of plan/run (no sequences, so nothing is launched)."""
     from ctypes import c_void_p
